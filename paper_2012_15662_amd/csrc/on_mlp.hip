@@ -412,161 +412,403 @@ __global__ __launch_bounds__(64) void k_on_warm(const OnProblem* __restrict__ pr
 }
 
 // ---- MLP ---------------------------------------------------------------------
-// Layer GEMMs run on the FP32 MFMA engine with 64x64 tiles.  Each weight block
-// is stored augmented: W_aug = [W (I x O); b (O)], so input rows carry an
-// implicit trailing 1.
-using MCfg = TileCfg<64, 64, 16, 32, 32>;
-using ME = EngF32;
+// FP32 MFMA (v_mfma_f32_16x16x4: A row / B column lane % 16, k = lane / 16; D
+// row 4 (lane / 16) + r, column lane % 16).  Each weight block is stored
+// augmented: W_aug = [W (I x O); b (O)].  FP32 partial sums over at most 128 k
+// are folded into FP64, where the bias, tanh, the softmax and the loss are.
+//
+// The network is tiny (39 k weights, 157 KB) and its rows are many, so what
+// counts is passes and launches: one workgroup carries 16 RT rows through every
+// layer with the activations in LDS and the weights read from L2 (each
+// fragment once per workgroup), forward and backward alike, and the weight
+// gradients are one split contraction over the rows for all four layers.  Going
+// back, a 16-deep slice of k is dealt to the lane groups as k = 4 (lane / 16) +
+// m, m = 0..3 the MFMA step, so a k-contiguous operand is one 16-byte read per
+// lane; going forward k runs in its natural order (the FP64 loss keeps the
+// digits of logits summed that way).
+// At 19,553 rows (an epoch of the 2000-molecule training set) forward, backward
+// and Adam took 3665 us with a launch per layer and the weight gradients as 6
+// workgroups of 64 x 64 tiles walking all the rows (864 us a layer); now 119 us
+// (forward 44, activations' gradients 34, weights' 41 + 7, Adam 5).
+constexpr int kActLd = kNhid + 4;   // LDS row of an activation: 16-byte aligned, rows 4 banks apart
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // 16 bytes at any float address
 
-// A operand of y = x_aug W_aug: rows of x (k-contiguous) with x[row][I] = 1.
-struct AugRows {
-  using S = KCSrc<float, MCfg::BM, ME::BK, MCfg::NT, ME::KV>;
-  static constexpr int NP = S::NP, R = S::R, RR = S::RR;
-  using type = float;
-  S s;
-  int I;
-  __device__ void init(const float* X, int nrows, int I_, int row0) {
-    I = I_;
-    s.init([&](int x) -> const float* { return row0 + x < nrows ? X + (long)(row0 + x) * I : nullptr; }, X, I + 1);
-  }
-  __device__ int xl(int p) const { return s.xl(p); }
-  __device__ int kl(int p) const { return s.kl(p); }
-  __device__ bool valid(int p, int i, int kt) const { return s.valid(p, i, kt); }
-  __device__ void fetch(int kt, float (&r)[RR]) const {
+constexpr int kMlpThreads = 512;    // eight waves, one 16-column strip of a hidden layer each
+__host__ __device__ constexpr long mlp_in(int l) { return l == 0 ? kNin : kNhid; }
+__host__ __device__ constexpr long mlp_out(int l) { return l == 3 ? kNout : kNhid; }
+__host__ __device__ constexpr long layer_off(int l) {
+  long o = 0;
+  for (int i = 0; i < l; ++i) o += (mlp_in(i) + 1) * mlp_out(i);
+  return o;
+}
+
+// acc[i] += x rows (16 i ..) . B over K, x in LDS ([row][k], zero from K up to
+// a multiple of 16); bval(k, b) gives this lane's column of B at the four steps
+// of a slice: k + 4 m (natural order) or k + m.
+template <int RT, int K, bool kNatural, class BV>
+__device__ __forceinline__ void mlp_strip(const float* x, f4 (&acc)[RT], BV&& bval) {
+  const int lane = threadIdx.x & 63, kr = lane >> 4, xc = lane & 15;
 #pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      const int k = kt * ME::BK + s.kl(p);
-      r[p] = k >= I ? 1.f : s.rp[p][k];
+  for (int c = 0; c < (K + 15) / 16; ++c) {
+    f4 a[RT];
+    float b[4];
+    bval(16 * c + (kNatural ? kr : 4 * kr), b);
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      const float* xr = x + (16 * i + xc) * kActLd + 16 * c;
+      if constexpr (kNatural) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) a[i][m] = xr[4 * m + kr];
+      } else {
+        a[i] = *(const f4*)(xr + 4 * kr);
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+      for (int i = 0; i < RT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][m], b[m], acc[i], 0, 0, 0);
+  }
+}
+
+// tanh |x| = E / (E + 2), E = exp(2|x|) - 1 = 2^n expm1(r) + (2^n - 1) with 2|x| =
+// n ln 2 + r, |r| <= ln 2 / 2, expm1 from its Taylor series to r^11 (the next
+// term is 2e-13 of it) and the quotient from the reciprocal with two Newton
+// steps: good to 1e-12 relative down to x = 0, so its FP32 rounding is the
+// library tanh's, at about a third of the FP64 instructions.  1 from |x| = 20 on.
+__device__ __forceinline__ double tanh_for_f32(double x) {
+  double y = 2.0 * fabs(x);
+  y = y > 40.0 ? 40.0 : y;   // (a NaN stays)
+  const double n = rint(y * 1.4426950408889634);
+  const double r = fma(n, -1.9082149292705877e-10, fma(n, -0.69314718036912381, y));   // ln 2 in two parts
+  double q = 1.0 / 39916800.0;
+  q = fma(q, r, 1.0 / 3628800.0);
+  q = fma(q, r, 1.0 / 362880.0);
+  q = fma(q, r, 1.0 / 40320.0);
+  q = fma(q, r, 1.0 / 5040.0);
+  q = fma(q, r, 1.0 / 720.0);
+  q = fma(q, r, 1.0 / 120.0);
+  q = fma(q, r, 1.0 / 24.0);
+  q = fma(q, r, 1.0 / 6.0);
+  q = fma(q, r, 0.5);
+  q = fma(q, r, 1.0);
+  const double two_n = ldexp(1.0, (int)n);
+  const double E = fma(two_n * q, r, two_n - 1.0), d = E + 2.0;
+  double c = __builtin_amdgcn_rcp(d);
+  c = fma(fma(-d, c, 1.0), c, c);
+  c = fma(fma(-d, c, 1.0), c, c);
+  return copysign(E * c, x);
+}
+
+// masked softmax of one row of logits
+__device__ __forceinline__ void masked_softmax(const float* z, const float* m, double (&p)[kNout]) {
+  double zmax = -1e300, e = 0.0;
+#pragma unroll
+  for (int k = 0; k < kNout; ++k)
+    if (m[k] > 0.f) zmax = fmax(zmax, (double)z[k]);
+#pragma unroll
+  for (int k = 0; k < kNout; ++k) {
+    p[k] = m[k] > 0.f ? exp((double)z[k] - zmax) : 0.0;
+    e += p[k];
+  }
+#pragma unroll
+  for (int k = 0; k < kNout; ++k) p[k] /= e;
+}
+
+// Forward, all layers: hidden y = tanh(x_aug W_aug), logits, masked softmax.
+template <int RT>
+__global__ __launch_bounds__(kMlpThreads) void k_mlp_fwd(int nrows, const float* __restrict__ X,
+                                                         const float* __restrict__ M,
+                                                         const float* __restrict__ theta, float* __restrict__ H,
+                                                         float* __restrict__ Z, float* __restrict__ Pout) {
+  constexpr int ROWS = 16 * RT;
+  __shared__ __attribute__((aligned(16))) float act[2][ROWS * kActLd];
+  __shared__ float zs[ROWS][kNout];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kr = lane >> 4, xc = lane & 15;
+  const long r0 = (long)blockIdx.x * ROWS;
+  for (int i = tid; i < ROWS * 48; i += kMlpThreads) {
+    const int r = i / 48, k = i - r * 48;
+    // column kNin: the 1 that meets the bias row
+    act[0][r * kActLd + k] = r0 + r >= nrows || k > kNin ? 0.f : k == kNin ? 1.f : X[(r0 + r) * kNin + k];
+  }
+  __syncthreads();
+  auto hidden = [&](auto layer) {
+    constexpr int l = decltype(layer)::value, I = (int)mlp_in(l);
+    const float* W = theta + layer_off(l) + 16 * wave + xc;   // this lane's column
+    f4 acc[RT] = {};
+    // layer 0's 40 rows of W_aug are one sum; with 128 inputs the bias joins in FP64
+    constexpr int K = I % 16 == 0 ? I : I + 1;
+    mlp_strip<RT, K, true>(act[l & 1], acc, [&](int k0, float (&b)[4]) {
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int k = k0 + 4 * m;
+        b[m] = K % 16 == 0 || k < K ? W[(long)(K % 16 == 0 || k < K ? k : 0) * kNhid] : 0.f;
+      }
+    });
+    const double bias = K == I ? (double)W[(long)I * kNhid] : 0.0;
+    float* y = act[(l + 1) & 1];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * i + 4 * kr + r;
+        const float v = (float)tanh_for_f32((double)acc[i][r] + bias);
+        y[row * kActLd + 16 * wave + xc] = v;
+        if (r0 + row < nrows) H[((long)l * nrows + r0 + row) * kNhid + 16 * wave + xc] = v;
+      }
+    __syncthreads();
+  };
+  hidden(std::integral_constant<int, 0>());
+  hidden(std::integral_constant<int, 1>());
+  hidden(std::integral_constant<int, 2>());
+  if (wave < RT) {   // logits: one wave per 16 rows, columns past the last unused
+    const float* W = theta + layer_off(3) + (xc < kNout ? xc : 0);
+    f4 acc[1] = {};
+    mlp_strip<1, kNhid, true>(act[1] + 16 * wave * kActLd, acc, [&](int k0, float (&b)[4]) {
+#pragma unroll
+      for (int m = 0; m < 4; ++m) b[m] = W[(long)(k0 + 4 * m) * kNout];
+    });
+    const double bias = W[(long)kNhid * kNout];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * wave + 4 * kr + r;
+      const float v = (float)((double)acc[0][r] + bias);
+      if (xc < kNout) {
+        zs[row][xc] = v;
+        if (r0 + row < nrows) Z[(r0 + row) * kNout + xc] = v;
+      }
     }
   }
-  __device__ double val(const float (&r)[RR], int p, int i) const { return (double)r[p + i]; }
-};
-
-// A operand of dW_aug = x_aug^T dY: element (x = i, k = row) = x[row][i], 1 for i = I.
-struct AugCols {
-  using S = XCSrc<float, MCfg::BM, ME::BK, MCfg::NT, ME::KV>;
-  static constexpr int NP = S::NP, R = S::R, RR = S::RR;
-  using type = float;
-  S s;
-  bool ones;
-  __device__ void init(const float* X, int nrows, int I, int i0) {
-    s.init(X, I, nrows, [&](int x, long& o) { o = i0 + x < I ? i0 + x : 0; return i0 + x <= I; });
-    ones = (i0 + s.x == I);
+  __syncthreads();
+  if (tid < ROWS && r0 + tid < nrows) {
+    double p[kNout];
+    masked_softmax(zs[tid], M + (r0 + tid) * kNout, p);
+#pragma unroll
+    for (int k = 0; k < kNout; ++k) Pout[(r0 + tid) * kNout + k] = (float)p[k];
   }
-  __device__ int xl(int p) const { return s.xl(p); }
-  __device__ int kl(int p) const { return s.kl(p); }
-  __device__ bool valid(int p, int i, int kt) const { return s.valid(p, i, kt); }
-  __device__ void fetch(int kt, float (&r)[RR]) const { s.fetch(kt, r); }
-  __device__ double val(const float (&r)[RR], int p, int i) const { return ones ? 1.0 : (double)r[p + i]; }
-};
-
-// y[row][o] = act(x_aug W_aug), act = tanh (hidden) or identity (output)
-__global__ __launch_bounds__(MCfg::NT) void k_mlp_fwd(int nrows, int I, int O, const float* __restrict__ X,
-                                                      const float* __restrict__ W, float* __restrict__ Y,
-                                                      int act_tanh) {
-  __shared__ __attribute__((aligned(16))) char smem[smem_bytes<ME, MCfg>()];
-  const int r0 = blockIdx.x * MCfg::BM, o0 = blockIdx.y * MCfg::BN;
-  AugRows la;
-  la.init(X, nrows, I, r0);
-  XCSrc<float, MCfg::BN, ME::BK, MCfg::NT, ME::KV> lb;
-  lb.init(W, O, I + 1, [&](int x, long& o) { o = o0 + x; return o0 + x < O; });
-  ME::Acc<MCfg> acc;
-  gemm_mainloop<ME, MCfg>(la, lb, cdiv_i(I + 1, ME::BK), acc, smem);
-  acc.for_each([&](int m, int n, double v) {
-    if (r0 + m < nrows && o0 + n < O) Y[(long)(r0 + m) * O + o0 + n] = act_tanh ? (float)tanh(v) : (float)v;
-  });
 }
 
-// dW_aug[i][o] = sum_row x_aug[row][i] dY[row][o]
-__global__ __launch_bounds__(MCfg::NT) void k_mlp_wgrad(int nrows, int I, int O, const float* __restrict__ X,
-                                                        const float* __restrict__ dY, float* __restrict__ dW) {
-  __shared__ __attribute__((aligned(16))) char smem[smem_bytes<ME, MCfg>()];
-  const int i0 = blockIdx.x * MCfg::BM, o0 = blockIdx.y * MCfg::BN;
-  AugCols la;
-  la.init(X, nrows, I, i0);
-  XCSrc<float, MCfg::BN, ME::BK, MCfg::NT, ME::KV> lb;
-  lb.init(dY, O, nrows, [&](int x, long& o) { o = o0 + x; return o0 + x < O; });
-  ME::Acc<MCfg> acc;
-  gemm_mainloop<ME, MCfg>(la, lb, cdiv_i(nrows, ME::BK), acc, smem);
-  acc.for_each([&](int m, int n, double v) {
-    if (i0 + m <= I && o0 + n < O) dW[(long)(i0 + m) * O + o0 + n] = (float)v;
-  });
-}
-
-// dA[row][i] = (sum_o dY[row][o] W[i][o]) * (1 - h[row][i]^2), h = tanh output of the layer below
-__global__ __launch_bounds__(MCfg::NT) void k_mlp_dgrad(int nrows, int I, int O, const float* __restrict__ dY,
-                                                        const float* __restrict__ W, const float* __restrict__ h,
-                                                        float* __restrict__ dA) {
-  __shared__ __attribute__((aligned(16))) char smem[smem_bytes<ME, MCfg>()];
-  const int r0 = blockIdx.x * MCfg::BM, i0 = blockIdx.y * MCfg::BN;
-  KCSrc<float, MCfg::BM, ME::BK, MCfg::NT, ME::KV> la;
-  la.init([&](int x) -> const float* { return r0 + x < nrows ? dY + (long)(r0 + x) * O : nullptr; }, dY, O);
-  KCSrc<float, MCfg::BN, ME::BK, MCfg::NT, ME::KV> lb;
-  lb.init([&](int x) -> const float* { return i0 + x < I ? W + (long)(i0 + x) * O : nullptr; }, W, O);
-  ME::Acc<MCfg> acc;
-  gemm_mainloop<ME, MCfg>(la, lb, cdiv_i(O, ME::BK), acc, smem);
-  acc.for_each([&](int m, int n, double v) {
-    const int r = r0 + m, i = i0 + n;
-    if (r < nrows && i < I) {
-      const float hv = h[(long)r * I + i];
-      dA[(long)r * I + i] = (float)(v * (1.0 - (double)hv * hv));
-    }
-  });
-}
-
-// masked softmax of the logits, loss partial per block, dZ of the loss
-__global__ __launch_bounds__(256) void k_mlp_softmax_loss(int nrows, const float* __restrict__ Z,
-                                                          const float* __restrict__ T, const float* __restrict__ M,
-                                                          float* __restrict__ Pout, float* __restrict__ dZ,
-                                                          double* __restrict__ lpart) {
-  __shared__ double red[256];
-  const int row = blockIdx.x * 256 + threadIdx.x;
-  double l = 0.0;
-  if (row < nrows) {
-    const float* z = Z + (long)row * kNout;
-    const float* m = M + (long)row * kNout;
-    double zmax = -1e300, p[kNout], e = 0.0;
-    for (int k = 0; k < kNout; ++k)
-      if (m[k] > 0.f) zmax = fmax(zmax, (double)z[k]);
-    for (int k = 0; k < kNout; ++k) {
-      p[k] = m[k] > 0.f ? exp((double)z[k] - zmax) : 0.0;
-      e += p[k];
-    }
-    double dp[kNout], sdp = 0.0;
-    for (int k = 0; k < kNout; ++k) {
-      p[k] /= e;
-      if (Pout) Pout[(long)row * kNout + k] = (float)p[k];
-      if (T) {
-        const double t = T[(long)row * kNout + k];
+// Backward through the activations: loss partials (one per workgroup), dZ of
+// the loss, then dA_l[row][i] = (sum_o dY[row][o] W[i][o]) (1 - h[row][i]^2) for
+// l = 2, 1, 0 (the gradients at the pre-activations, which the weight
+// gradients read; a null one is not stored).
+template <int RT>
+__global__ __launch_bounds__(kMlpThreads) void k_mlp_bwd(int nrows, const float* __restrict__ T,
+                                                         const float* __restrict__ M,
+                                                         const float* __restrict__ theta,
+                                                         const float* __restrict__ H, const float* __restrict__ Z,
+                                                         float* __restrict__ dZ, float* __restrict__ dA2,
+                                                         float* __restrict__ dA1, float* __restrict__ dA0,
+                                                         double* __restrict__ lpart) {
+  constexpr int ROWS = 16 * RT;
+  __shared__ __attribute__((aligned(16))) float act[2][ROWS * kActLd];
+  __shared__ double red[ROWS];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kr = lane >> 4, xc = lane & 15;
+  const long r0 = (long)blockIdx.x * ROWS;
+  if (tid < ROWS) {
+    const long row = r0 + tid;
+    double l = 0.0;
+    float g[16] = {};
+    if (row < nrows) {
+      const float* m = M + row * kNout;
+      double p[kNout], dp[kNout], sdp = 0.0;
+      masked_softmax(Z + row * kNout, m, p);
+#pragma unroll
+      for (int k = 0; k < kNout; ++k) {
+        const double t = T[row * kNout + k];
         l += m[k] * (p[k] - t) * (p[k] - t);
         dp[k] = 2.0 * m[k] * (p[k] - t) / nrows;
         sdp += dp[k] * p[k];
       }
+#pragma unroll
+      for (int k = 0; k < kNout; ++k) dZ[row * kNout + k] = g[k] = (float)(p[k] * (dp[k] - sdp));
     }
-    if (T && dZ)
-      for (int k = 0; k < kNout; ++k) dZ[(long)row * kNout + k] = (float)(p[k] * (dp[k] - sdp));
+#pragma unroll
+    for (int k = 0; k < 16; ++k) act[0][tid * kActLd + k] = g[k];
+    red[tid] = l;
   }
-  red[threadIdx.x] = l;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
+  if (tid == 0) {
+    double s = 0.0;
+    for (int i = 0; i < ROWS; ++i) s += red[i];
+    lpart[blockIdx.x] = s;
   }
-  if (threadIdx.x == 0 && lpart) lpart[blockIdx.x] = red[0];
+  auto back = [&](auto layer, float* __restrict__ out) {   // through layer l to the activations below it
+    constexpr int l = decltype(layer)::value, O = (int)mlp_out(l);
+    const int col = 16 * wave + xc;   // i
+    const float* W = theta + layer_off(l) + (long)col * O;
+    f4 acc[RT] = {};
+    mlp_strip<RT, O, false>(act[(3 - l) & 1], acc, [&](int k0, float (&b)[4]) {
+      if constexpr (O % 16 == 0) {
+        const f4u w = *(const f4u*)(W + k0);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) b[m] = w[m];
+      } else {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) b[m] = k0 + m < O ? W[k0 + m < O ? k0 + m : 0] : 0.f;
+      }
+    });
+    float* y = act[(4 - l) & 1];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const long row = r0 + 16 * i + 4 * kr + r;
+        float v = 0.f;
+        if (row < nrows) {
+          const double h = H[((long)(l - 1) * nrows + row) * kNhid + col];
+          v = (float)((double)acc[i][r] * (1.0 - h * h));
+          if (out) out[row * kNhid + col] = v;
+        }
+        if (l > 1) y[(16 * i + 4 * kr + r) * kActLd + col] = v;
+      }
+    if (l > 1) __syncthreads();
+  };
+  back(std::integral_constant<int, 3>(), dA2);
+  back(std::integral_constant<int, 2>(), dA1);
+  back(std::integral_constant<int, 1>(), dA0);
 }
 
-__global__ __launch_bounds__(256) void k_sum_parts(int n, const double* __restrict__ parts, double scale,
-                                                   double* __restrict__ out) {
+// Weight gradients of every layer, dW_aug[i][o] = sum_row x_aug[row][i]
+// dY[row][o], split over the rows: workgroup (s, l) sums the rows
+// [s chunk, (s+1) chunk) of layer l into part[s], eight waves of TM x TN
+// fragments (WN waves along o) whose operands come straight from memory: a
+// fragment is 16 consecutive floats of four rows, and the fragments of a wave
+// feed TM TN MFMAs per four rows, so nothing is staged.  The bias row is the
+// sum of the dY fragments, in FP64, by the waves of the first strip of i.
+struct WgradArgs {
+  int nrows, chunk;
+  const float *X, *H, *dZ, *dA[3];
+  double* part;   // [splits][n_params], or null: one split, straight into grad
+  float* grad;
+  int first;      // blockIdx.y + first: 0, 1, 2, 3 for layers 1, 2, 3, 0
+};
+template <int L, int TM, int TN, int WN>
+__device__ __forceinline__ void wgrad_layer(const WgradArgs& a) {
+  constexpr int I = (int)mlp_in(L), O = (int)mlp_out(L);
+  const float* x = L == 0 ? a.X : a.H + (long)(L - 1) * a.nrows * kNhid;
+  const float* dy = L == 3 ? a.dZ : a.dA[L];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kr = lane >> 4, xc = lane & 15;
+  const int i0 = (wave / WN) * TM * 16, o0 = (wave % WN) * TN * 16;
+  const int k0 = blockIdx.x * a.chunk, k1 = min(a.nrows, k0 + a.chunk);
+  f4 s[TM][TN] = {};
+  d4 v[TM][TN] = {};
+  double bias[TN] = {};
+  int ic[TM], oc[TN];   // fragment columns, clamped: those past the end are never stored
+#pragma unroll
+  for (int i = 0; i < TM; ++i) ic[i] = min(i0 + 16 * i + xc, I - 1);
+#pragma unroll
+  for (int j = 0; j < TN; ++j) oc[j] = min(o0 + 16 * j + xc, O - 1);
+  // sixteen rows a step, the next step's loads in flight during this one's
+  // MFMAs; rows past the end read the last one and count as zero
+  float av[4][TM], bv[4][TN], an[4][TM], bn[4][TN];
+  auto fetch = [&](int k, float (&x4)[4][TM], float (&y4)[4][TN]) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const long rc = min(k + 4 * m + kr, k1 - 1);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) x4[m][i] = x[rc * I + ic[i]];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) y4[m][j] = dy[rc * O + oc[j]];
+    }
+  };
+  auto step = [&](int k, float (&x4)[4][TM], float (&y4)[4][TN]) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const bool ok = k + 4 * m + kr < k1;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) x4[m][i] = ok ? x4[m][i] : 0.f;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        y4[m][j] = ok ? y4[m][j] : 0.f;
+        if (i0 == 0) bias[j] += (double)y4[m][j];
+      }
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          s[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x4[m][i], y4[m][j], s[i][j], 0, 0, 0);
+    }
+    if (((k - k0) & 127) == 112 || k + 16 >= k1) {   // 128 rows, or the last of them
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[i][j][r] += (double)s[i][j][r];
+          s[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+  };
+  fetch(k0, av, bv);
+  for (int k = k0; k < k1; k += 32) {
+    fetch(min(k + 16, k1 - 1), an, bn);
+    step(k, av, bv);
+    if (k + 16 >= k1) break;
+    fetch(min(k + 32, k1 - 1), av, bv);
+    step(k + 16, an, bn);
+  }
+  double* out = a.part ? a.part + (long)blockIdx.x * layer_off(4) + layer_off(L) : nullptr;
+  auto put = [&](int i, int o, double g) {
+    if (out) out[(long)i * O + o] = g;
+    else a.grad[layer_off(L) + (long)i * O + o] = (float)g;
+  };
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int ii = i0 + 16 * i + 4 * kr + r, oo = o0 + 16 * j + xc;
+        if (ii < I && oo < O) put(ii, oo, v[i][j][r]);
+      }
+  if (i0 == 0) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {   // the four rows of each step sit in the four lane groups
+      double b = bias[j];
+      b += __shfl_xor(b, 16, 64);
+      b += __shfl_xor(b, 32, 64);
+      if (kr == 0 && o0 + 16 * j + xc < O) put(I, o0 + 16 * j + xc, b);
+    }
+  }
+}
+__global__ __launch_bounds__(kMlpThreads) void k_mlp_wgrad(WgradArgs a) {
+  switch (a.first + (int)blockIdx.y) {   // layer 0 last, on its own where the arena is capped
+    case 0: wgrad_layer<1, 2, 4, 2>(a); break;
+    case 1: wgrad_layer<2, 2, 4, 2>(a); break;
+    case 2: wgrad_layer<3, 1, 1, 1>(a); break;
+    default: wgrad_layer<0, 3, 1, 8>(a); break;
+  }
+}
+
+// grad[i] = sum over the splits, in a fixed order (four strided quarters, then
+// their sum); the last workgroup adds up the loss partials.
+__global__ __launch_bounds__(256) void k_mlp_reduce(int n, int splits, const double* __restrict__ part,
+                                                    float* __restrict__ grad, int nl,
+                                                    const double* __restrict__ lpart, double scale,
+                                                    double* __restrict__ loss) {
   __shared__ double red[256];
+  const int tid = threadIdx.x;
+  if (blockIdx.x + 1 < gridDim.x) {
+    const int i = blockIdx.x * 64 + (tid & 63);
+    double s = 0.0;
+    if (i < n) {
+#pragma unroll 8
+      for (int k = tid >> 6; k < splits; k += 4) s += part[(long)k * n + i];
+    }
+    red[tid] = s;
+    __syncthreads();
+    if (tid < 64 && i < n) grad[i] = (float)((red[tid] + red[tid + 64]) + (red[tid + 128] + red[tid + 192]));
+    return;
+  }
   double s = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) s += parts[i];
-  red[threadIdx.x] = s;
+  for (int i = tid; i < nl; i += 256) s += lpart[i];
+  red[tid] = s;
   __syncthreads();
   for (int k = 128; k > 0; k >>= 1) {
-    if (threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
+    if (tid < k) red[tid] += red[tid + k];
     __syncthreads();
   }
-  if (threadIdx.x == 0) *out = red[0] * scale;
+  if (tid == 0) *loss = red[0] * scale;
 }
 
 // Adam with bias correction (step counts from 1)
@@ -660,73 +902,79 @@ rif_status op_on_warmstart(rif_ctx* c, int n, const OnProblem* probs, const floa
   return check_launch(c, "on_warm");
 }
 
-static const long kLayerIn[4] = {kNin, kNhid, kNhid, kNhid};
-static const long kLayerOut[4] = {kNhid, kNhid, kNhid, kNout};
-static long layer_off(int l) {
-  long o = 0;
-  for (int i = 0; i < l; ++i) o += (kLayerIn[i] + 1) * kLayerOut[i];
-  return o;
-}
 long mlp_n_params() { return layer_off(4); }
+
+// Rows per workgroup of the fused passes: 32 halve the weight reads, 16 fill the
+// chip sooner and halve a workgroup's chain.  Forward + backward, 16 against 32
+// rows: 70.4 / 72.9 us at 8,208 rows, 78.7 / 84.5 at 12,000, 102 / 93 at 16,000
+// (119 both ways at 19,553); the line lies between, at 3.5 16-row workgroups per CU.
+static bool mlp_wide(int nrows) { return nrows > 256 * 56; }
 
 rif_status op_mlp_forward(rif_ctx* c, int nrows, const float* X, const float* M, const float* theta, float* H,
                           float* Z, float* Pn) {
-  const float* in = X;
-  for (int l = 0; l < 4; ++l) {
-    const int I = (int)kLayerIn[l], O = (int)kLayerOut[l];
-    float* out = l < 3 ? H + (long)l * nrows * kNhid : Z;
-    ProfScope ps(c, "mlp_fwd");
-    hipLaunchKernelGGL(k_mlp_fwd, dim3(cdiv_i(nrows, MCfg::BM), cdiv_i(O, MCfg::BN)), dim3(MCfg::NT), 0, c->stream,
-                       nrows, I, O, in, theta + layer_off(l), out, l < 3 ? 1 : 0);
-    rif_status st = check_launch(c, "mlp_fwd");
-    if (st) return st;
-    in = out;
-  }
-  hipLaunchKernelGGL(k_mlp_softmax_loss, dim3(cdiv_i(nrows, 256)), dim3(256), 0, c->stream, nrows, Z, nullptr, M,
-                     Pn, nullptr, nullptr);
-  return check_launch(c, "mlp_softmax");
+  ProfScope ps(c, "mlp_fwd");
+  if (mlp_wide(nrows))
+    hipLaunchKernelGGL(k_mlp_fwd<2>, dim3(cdiv_i(nrows, 32)), dim3(kMlpThreads), 0, c->stream, nrows, X, M, theta, H,
+                       Z, Pn);
+  else
+    hipLaunchKernelGGL(k_mlp_fwd<1>, dim3(cdiv_i(nrows, 16)), dim3(kMlpThreads), 0, c->stream, nrows, X, M, theta, H,
+                       Z, Pn);
+  return check_launch(c, "mlp_fwd");
 }
 
 rif_status op_mlp_backward(rif_ctx* c, int nrows, const float* X, const float* M, const float* T,
                            const float* theta, const float* H, const float* Z, float* dA, float* grad,
                            double* loss) {
-  const int nb = cdiv_i(nrows, 256);
+  const bool wide = mlp_wide(nrows);
+  const int nl = cdiv_i(nrows, wide ? 32 : 16), n = (int)mlp_n_params();
+  // splits of the weight gradients: about 100 workgroups for each wide layer
+  // (two of them fill the chip), at least one 128-row FP32 chunk each
+  int chunk = std::max(128, 4 * cdiv_i(nrows, 4 * 100)), splits = cdiv_i(nrows, chunk);
   Carve cv;
-  const size_t o_lp = cv.take<double>((size_t)nb);
+  const size_t o_lp = cv.take<double>((size_t)nl);
   const size_t o_dz = cv.take<float>((size_t)nrows * kNout);
-  rif_status st = ws_reserve(c, cv.off);
+  // the rest only if the arena may hold it (rif_set_workspace_limit): without
+  // it each gradient is one split, stored straight into grad, and the third
+  // dA shares dA's first buffer in a second backward pass
+  Carve full = cv;
+  const size_t o_part = full.take<double>((size_t)splits * n);
+  const size_t o_da = full.take<float>((size_t)nrows * kNhid);
+  const bool lean = !ws_fits(c, full.off);
+  rif_status st = ws_reserve(c, lean ? cv.off : full.off);
   if (st) return st;
-  double* lp = (double*)((char*)c->ws + o_lp);
-  float* dZ = (float*)((char*)c->ws + o_dz);
-  {
-    ProfScope ps(c, "mlp_loss");
-    hipLaunchKernelGGL(k_mlp_softmax_loss, dim3(nb), dim3(256), 0, c->stream, nrows, Z, T, M, (float*)nullptr, dZ,
-                       lp);
-    hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, c->stream, nb, lp, 1.0 / nrows, loss);
+  char* ws = (char*)c->ws;
+  double* lp = (double*)(ws + o_lp);
+  float* dZ = (float*)(ws + o_dz);
+  float *d2 = dA, *d1 = dA + (long)nrows * kNhid, *d0 = lean ? dA : (float*)(ws + o_da);
+  auto back = [&](float* p2, float* p1, float* p0) {
+    ProfScope ps(c, "mlp_dgrad");
+    if (wide)
+      hipLaunchKernelGGL(k_mlp_bwd<2>, dim3(nl), dim3(kMlpThreads), 0, c->stream, nrows, T, M, theta, H, Z, dZ, p2, p1,
+                         p0, lp);
+    else
+      hipLaunchKernelGGL(k_mlp_bwd<1>, dim3(nl), dim3(kMlpThreads), 0, c->stream, nrows, T, M, theta, H, Z, dZ, p2, p1,
+                         p0, lp);
+    return check_launch(c, "mlp_dgrad");
+  };
+  if (lean) { chunk = nrows; splits = 1; }
+  WgradArgs a{nrows, chunk, X, H, dZ, {d0, d1, d2}, splits > 1 ? (double*)(ws + o_part) : nullptr, grad, 0};
+  auto weights_of = [&](int first, int count) {
+    a.first = first;
+    ProfScope ps(c, "mlp_wgrad");
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3((unsigned)splits, (unsigned)count), dim3(kMlpThreads), 0, c->stream, a);
+    return check_launch(c, "mlp_wgrad");
+  };
+  if (lean) {
+    if ((st = back(d2, d1, nullptr)) || (st = weights_of(0, 3)) || (st = back(nullptr, nullptr, d0)) ||
+        (st = weights_of(3, 1)))
+      return st;
+  } else if ((st = back(d2, d1, d0)) || (st = weights_of(0, 4))) {
+    return st;
   }
-  if ((st = check_launch(c, "mlp_loss"))) return st;
-  // dA holds two [nrows][128] ping-pong buffers
-  const float* dcur = dZ;
-  for (int l = 3; l >= 0; --l) {
-    const int I = (int)kLayerIn[l], O = (int)kLayerOut[l];
-    const float* xin = l == 0 ? X : H + (long)(l - 1) * nrows * kNhid;
-    {
-      ProfScope ps(c, "mlp_wgrad");
-      hipLaunchKernelGGL(k_mlp_wgrad, dim3(cdiv_i(I + 1, MCfg::BM), cdiv_i(O, MCfg::BN)), dim3(MCfg::NT), 0,
-                         c->stream, nrows, I, O, xin, dcur, grad + layer_off(l));
-    }
-    if ((st = check_launch(c, "mlp_wgrad"))) return st;
-    if (l == 0) break;
-    float* dnext = dA + (long)(l % 2) * nrows * kNhid;
-    {
-      ProfScope ps(c, "mlp_dgrad");
-      hipLaunchKernelGGL(k_mlp_dgrad, dim3(cdiv_i(nrows, MCfg::BM), cdiv_i(I, MCfg::BN)), dim3(MCfg::NT), 0,
-                         c->stream, nrows, I, O, dcur, theta + layer_off(l), xin, dnext);
-    }
-    if ((st = check_launch(c, "mlp_dgrad"))) return st;
-    dcur = dnext;
-  }
-  return RIF_OK;
+  ProfScope ps(c, "mlp_reduce");
+  hipLaunchKernelGGL(k_mlp_reduce, dim3((unsigned)((splits > 1 ? cdiv_i(n, 64) : 0) + 1)), dim3(256), 0, c->stream, n,
+                     splits, a.part, grad, nl, lp, 1.0 / nrows, loss);
+  return check_launch(c, "mlp_reduce");
 }
 
 rif_status op_adam(rif_ctx* c, int n, float* theta, const float* grad, float* m, float* v, int step, float lr,

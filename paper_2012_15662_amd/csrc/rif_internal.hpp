@@ -59,6 +59,10 @@ enum : int { kBadOcc = 1, kBadSum = 2, kBadMap = 4, kBadCount = 8, kNonFinite = 
 rif_status fail(rif_ctx* c, rif_status s, const std::string& msg);
 // Ensures the arena holds at least `bytes`; returns RIF_OK or RIF_ENOMEM/RIF_EHIP.
 rif_status ws_reserve(rif_ctx* c, size_t bytes);
+// Whether the arena may hold `bytes` (rif_set_workspace_limit).
+inline bool ws_fits(const rif_ctx* c, size_t bytes) {
+  return bytes <= c->ws_bytes || !c->ws_limit || bytes <= c->ws_limit;
+}
 
 // Carves aligned sub-buffers from the arena.
 struct Carve {
