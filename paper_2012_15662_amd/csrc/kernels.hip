@@ -14,6 +14,7 @@
 // and reduced in a fixed order, so every result is deterministic.
 #include <math.h>
 
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -1161,6 +1162,12 @@ __global__ __launch_bounds__(256) void k_bsplitj(BSplitJArgs a) {
 
 // MO J/K partial sums over a contiguous range of l (fixed split), then a
 // fixed-order reduction over the splits.  FP64 arithmetic in every mode.
+// Splits: enough for about 1024 workgroups, at least eight l each (one batch
+// of loads in flight; shorter ranges cost as much and leave more to add up).
+static int jk_splits(int na, int nw) {
+  const long nx = cdiv((long)nw * nw, 256);
+  return (int)std::max(1L, std::min((long)cdiv(na, 8), (1024L + nx - 1) / nx));
+}
 template <int P, class Cfg>
 __host__ __device__ inline long jkp_tiles(const JkArgs& a) { return (long)cdiv((long)a.nw * a.nw, 256) * a.nsplit; }
 template <int P, class Cfg>
@@ -1185,20 +1192,44 @@ __device__ void jkp_tile(const JkArgs& a, long t, char*) {
   a.part[(2L * s + 1) * w2 + pq] = sk;
 }
 
+// A tile's 256 threads are 256 / SL elements times SL strided shares of the
+// splits, added in a fixed order through LDS.  A small n_omega has few
+// elements and many splits, and one thread per element walked them as a chain
+// of dependent loads (50 us at n_omega 10 and 192 splits, 68 us at 48 and 114,
+// the longest kernel of those builds; now 5 us); from few splits on the shares
+// would idle.
+__host__ __device__ inline int jkr_share(int nsplit) { return nsplit >= 32 ? 16 : nsplit >= 8 ? 4 : 1; }
 template <int P, class Cfg>
-__host__ __device__ inline long jkr_tiles(const JkArgs& a) { return cdiv((long)a.nw * a.nw, 256); }
+__host__ __device__ inline long jkr_tiles(const JkArgs& a) {
+  return cdiv((long)a.nw * a.nw, 256 / jkr_share(a.nsplit));
+}
 template <int P, class Cfg>
-__device__ void jkr_tile(const JkArgs& a, long t, char*) {
+__device__ void jkr_tile(const JkArgs& a, long t, char* smem) {
+  double* red = (double*)smem;   // [2][256]
   const long w2 = (long)a.nw * a.nw;
-  const long pq = t * 256 + threadIdx.x;
-  if (pq >= w2) return;
+  const int SL = jkr_share(a.nsplit), NE = 256 / SL, tid = threadIdx.x;
+  const int e = tid % NE, sh = tid / NE;
+  const long pq = t * NE + e;
   double sj = 0.0, sk = 0.0;
-  for (int s = 0; s < a.nsplit; ++s) {
-    sj += a.part[(2L * s) * w2 + pq];
-    sk += a.part[(2L * s + 1) * w2 + pq];
+  if (pq < w2) {
+#pragma unroll 4
+    for (int s = sh; s < a.nsplit; s += SL) {
+      sj += a.part[(2L * s) * w2 + pq];
+      sk += a.part[(2L * s + 1) * w2 + pq];
+    }
   }
-  a.J[pq] = sj;
-  a.K[pq] = sk;
+  red[tid] = sj;
+  red[256 + tid] = sk;
+  __syncthreads();
+  if (sh == 0 && pq < w2) {
+    for (int i = 1; i < SL; ++i) {
+      sj += red[i * NE + e];
+      sk += red[256 + i * NE + e];
+    }
+    a.J[pq] = sj;
+    a.K[pq] = sk;
+  }
+  __syncthreads();   // a grouped workgroup's next tile writes red again
 }
 
 // Pair index of orbital p of Omega (explicit map or the default one).
@@ -1424,7 +1455,7 @@ RIF_STEP_KERNELS(fock, FockArgs, GEMM_SMEM, Cfg::NT, false, GEMM_WPE, GEMM_WPE, 
 RIF_STEP_KERNELS(yd, YdArgs, GEMM_SMEM, Cfg::NT, false, GEMM_WPE, 1, yd_tile)
 RIF_STEP_KERNELS(ydz, YdzArgs, kYdzLds * 8, 256, false, 1, 1, ydz_tile)
 RIF_STEP_KERNELS(jkp, JkArgs, 16, 256, false, 1, 1, jkp_tile)
-RIF_STEP_KERNELS(jkr, JkArgs, 16, 256, false, 1, 1, jkr_tile)
+RIF_STEP_KERNELS(jkr, JkArgs, 2 * 256 * 8, 256, false, 1, 1, jkr_tile)
 RIF_STEP_KERNELS(coef, CoefArgs, 256 * 8, 256, false, 1, 1, coef_tile)
 RIF_STEP_KERNELS(energy, EnergyArgs, kEnergySmem, kEnergyThreads, false, 1, 1, energy_tile)
 RIF_STEP_KERNELS(fred, FockRedArgs, 16, 256, false, 1, 1, fred_tile)
@@ -1701,7 +1732,7 @@ struct Plan {
     nw = npairs * (1 + ncwo);
     const long w2 = (long)nw * nw;
     const long nx = cdiv(w2, 256);
-    jk_nsplit = (int)std::max(1L, std::min((long)na, (1024L + nx - 1) / nx));
+    jk_nsplit = jk_splits(na, nw);
     // fock split-K over the stacked slabs' slices, sized so the 128x128-tile
     // launch fills the 512 slots of two workgroups per CU in one round (the
     // 64x64 one then fills four per CU in about two); at most one split per
@@ -1880,8 +1911,7 @@ rif_status op_half_slabs_f64(rif_ctx* c, int nb, long nslab, int nw, int nmo, co
 rif_status op_jk_mo(rif_ctx* c, int prec, int na, int nw, const void* bmo, const double* d, double* J, double* K) {
   if (!prec_ok(prec)) return fail(c, RIF_ENOTSUP, "precision mode not available");
   const long w2 = (long)nw * nw;
-  const long nx = cdiv(w2, 256);
-  const int nsplit = (int)std::max(1L, std::min((long)na, (1024L + nx - 1) / nx));
+  const int nsplit = jk_splits(na, nw);
   Carve cv;
   const size_t o_part = cv.take<double>(2L * nsplit * w2);
   rif_status st = ws_reserve(c, cv.off);
@@ -1918,8 +1948,7 @@ rif_status op_jk_mo_noalloc(rif_ctx* c, int prec, int na, int nw, const void* bm
   if (!prec_ok(prec)) return fail(c, RIF_ENOTSUP, "precision mode not available");
   if (!c->scratch) return fail(c, RIF_EHIP, "rif_jk_mo_noalloc: the static scratch could not be resolved");
   const long w2 = (long)nw * nw;
-  const long nx = cdiv(w2, 256);
-  const int nsplit = (int)std::max(1L, std::min((long)na, (1024L + nx - 1) / nx));
+  const int nsplit = jk_splits(na, nw);
   const size_t need = sizeof(double) * 2 * (size_t)nsplit * (size_t)w2;
   if (need > c->scratch_bytes)
     return fail(c, RIF_ENOMEM, "rif_jk_mo_noalloc: needs " + std::to_string(need) + " bytes of scratch, more than its " +
