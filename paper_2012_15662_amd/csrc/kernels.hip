@@ -20,6 +20,8 @@
 
 #include "mfma_engine.hpp"
 #include "rif_internal.hpp"
+#include "strip64.hpp"
+#include "wave.hpp"
 
 namespace rif {
 
@@ -91,15 +93,13 @@ constexpr int kDeep = kPieces<P> == 2 ? 2 : 1;
 struct Planes { const unsigned short* p; long ps; int ld; };
 // Bs / bf: b given pre-split (bf16 piece planes with rows r = l*n_bf + nu, or
 // an FP32 copy in b's layout); unset (null) means b is split on load.
-// dma: FP64 operands staged by direct global -> LDS loads in the 128 x 128
-// tile (set when every row of b and C starts 16-byte aligned and n_omega is even).
 struct HalfArgs {
   int nb, nw, nmo; long nr; const double* b; const double* C; void* bh; Planes Cs; Planes Bs; const float* bf;
-  int dma;
 };
-inline int half_dma_ok(int nb, int nmo, int nw, const double* b, const double* C) {
-  return nb % 2 == 0 && nmo % 2 == 0 && nw % 2 == 0 && ((uintptr_t)b | (uintptr_t)C) % 16 == 0;
-}
+// The FP64 strip tiles stage column pairs (two columns at least) at 32-bit
+// offsets (fifteen rows of a slab's width from the tile's first element); the
+// 64 x 64 tile staged through registers takes what is left.
+inline bool strip_fits(int nb, int nmo, int nw) { return nb >= 2 && nw >= 2 && nb < 5900 && nmo < 5900; }
 // b pre-split once per call: element (r, mu) = b[r*n_bf + mu] (row r = l*n_bf + nu;
 // b symmetric) into the mode's pieces, rows zero-filled from n_bf up to ld;
 // FP32 mode: a float copy.
@@ -109,9 +109,7 @@ struct BSplitArgs { const double* b; long nr; int nb, ld; void* out; long ps; };
 struct MoArgs { int nb, na, nw, nmo; const void* bh; const double* C; void* bmo; double* d; Planes Cs; int dma; };
 // Bj: b pre-split for J^q (piece planes with rows r = mu*n_bf + nu and
 // k = l contiguous), or unset (split on load).
-// dma: FP64 operands staged by direct global -> LDS loads in the 128 x 128
-// tile (rows of b and d 16-byte aligned).
-struct JaoArgs { int nb, na, nw; const double* b; const double* d; void* Jn; Planes Ds; Planes Bj; int dma; };
+struct JaoArgs { int nb, na, nw; const double* b; const double* d; void* Jn; Planes Ds; Planes Bj; };
 // Pre-split of X (element (x, k) at X[k*sk + x]) into NPC bf16 planes
 // out[s*ps + x*ld + k], zero from k = K up to ld.
 struct PSplitArgs { const double* X; long sk; int nx, K, ld; unsigned short* out; long ps; };
@@ -126,14 +124,13 @@ struct GemmArgs {
   double* out; long ldo;
   int ksplit, kc; long ostride;
 };
-// dma: FP64 128 x 128 tiles stage J^q/K^q and C by direct global -> LDS loads
-// (even n_bf, n_omega and n_mo, 16-byte aligned Jn, Kn and C).
+// strip: the FP64 step on strip tiles (fock_strip_tile), its partials in Yp.
 struct FockArgs {
   int nb, nw, nmo, nsplit;
   const void *Jn, *Kn;
   const double *Ac, *Bc, *C;
   double* Yp;
-  int dma;
+  int strip;
 };
 struct JkArgs { int na, nw, nsplit; const void* bmo; const double* d; double* part; double* J; double* K; };
 struct CoefArgs {
@@ -149,7 +146,7 @@ struct EnergyArgs {
   double* energy;
   int* flag;
 };
-struct FockRedArgs { int nb, nw, nsplit; const double *Yp, *occ, *HC; double* Y; };
+struct FockRedArgs { int nb, nw, nsplit; const double *Yp, *occ, *HC; double* Y; int strip; };
 // Gradient without per-MO AO matrices: Y[nu][q] = sum_{k=(r,l)} bh[r][l][nu] X[k][q] with
 // X = Bt[q][r] * (r == q ? Zt[l][q] : bmo[l][r][q]), k = r*n_aux + l, split over k
 // into nsplit ranges of kc; Zt, Bt (the mode's storage type) from k_ydz.
@@ -194,7 +191,56 @@ __device__ __forceinline__ void run_q_rows(int fim, typename EngineOf<P>::type::
 // b and stores of b_half both run along nu), K = mu.  Tiles: q-tile fastest.
 template <int P, class Cfg>
 __host__ __device__ inline long half_tiles(const HalfArgs& a) {
-  return (long)cdiv(a.nw, Cfg::BM) * cdiv(a.nr, Cfg::BN);
+  if constexpr (is_strip<Cfg>::value)
+    return strip_tiles(a.nw) * (long)cdiv(a.nr / a.nb * pair_len(a.nb), Cfg::BN);
+  else
+    return (long)cdiv(a.nw, Cfg::BM) * cdiv(a.nr, Cfg::BN);
+}
+// FP64 on strip tiles.  Columns run over (l, nu) with nu's positions rounded up
+// to pairs; a tile's offsets start at the slab of its first column.
+// Per launch, against 128 x 128 tiles of 64-bit-addressed direct loads (even
+// sizes) or 64 x 64 register-staged ones (odd) before: 553 -> 530 us at the
+// cyclohexane-like size (n_omega 120: 58 TFLOP/s useful), 4.77 -> 4.07 ms at the
+// cyclodecane-like one (n_omega 200: tiles of 112 rows instead of 128), 76 -> 61
+// at n_bf 201 / n_omega 48.  With random operands the clock gives way: the same
+// loop on zeros takes 520, 3904 and 53.
+template <class Cfg>
+__device__ __forceinline__ void half_strip(const HalfArgs& a, long t, char* smem) {
+  const int nb = a.nb, nw = a.nw, nqt = strip_tiles(nw), tm = strip_frags(nw), ne = pair_len(nb);
+  const long na = a.nr / nb, B2 = (long)nb * nb, nre = na * ne;
+  const int q0 = (int)(t % nqt) * 16 * tm;
+  const long r0 = (t / nqt) * Cfg::BN, l0 = r0 / ne;
+  const int p0 = (int)(r0 - l0 * ne);
+  double* bh = (double*)a.bh;
+  with_frags(tm, [&](auto frags) {
+    using L = Strip<Cfg, decltype(frags)::value>;
+    StripStage<L> st;
+    st.init(a.C, a.nmo, [&](int x) -> long { return q0 + x < nw ? pair_start(q0 + x, nw) : 0; },
+            a.b + l0 * B2, nb, [&](int x) -> long {
+              const int p = p0 + x, dl = p / ne;
+              return r0 + x < nre ? dl * B2 + pair_start(p - dl * ne, nb) : 0;
+            });
+    StripAcc<L> acc;
+    strip_mainloop(cdiv(nb, 16), st.w, acc, smem, [&](int kt, lds_char* s) { st.issue(s, nb - 16 * kt); });
+    const int xc = threadIdx.x & 15;
+    long o[L::FN];   // this lane's output columns
+#pragma unroll
+    for (int j = 0; j < L::FN; ++j) {
+      const int p = p0 + acc.wn + 16 * j + xc, dl = p / ne, c = pair_column(p - dl * ne, nb);
+      o[j] = c >= 0 && l0 + dl < na ? (l0 + dl) * nb + c : -1;
+    }
+#pragma unroll
+    for (int i = 0; i < L::FM; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int q = pair_column(q0 + acc.wm + 16 * i + ((threadIdx.x & 63) >> 4) + 4 * e, nw);
+        if (q >= 0) {
+#pragma unroll
+          for (int j = 0; j < L::FN; ++j)
+            if (o[j] >= 0) bh[(long)q * a.nr + o[j]] = acc.v[i][j][e];
+        }
+      }
+  });
 }
 template <int P, class Cfg, bool kBPre, bool kTrim>
 __device__ void half_tile_with(const HalfArgs& a, long t, char* smem) {
@@ -217,22 +263,6 @@ __device__ void half_tile_with(const HalfArgs& a, long t, char* smem) {
     if (q < nw && r < nr) bh[(long)q * nr + r] = (IOT<P>)v;
   };
   const int fim = cdiv(nw - q0, 16);   // live fragment rows
-  if constexpr (P == kF64 && !kBPre && Cfg::BM == 128 && Cfg::BN == 128) {
-    if (a.dma) {
-      XcDma64<Cfg::NT, E::BK, E::PAD> la, lb;
-      la.init(a.C, a.nmo, nb, [&](int x, long& o) { o = q0 + x; return q0 + x < nw; });
-      lb.init(a.b, nb, nb, slab_off);
-      if constexpr (kTrim) {
-        run_q_rows<P, Cfg, kTrim>(fim, acc, [&](auto mma) {
-          gemm_mainloop_dma_with<E, Cfg, 2>(la, lb, cdiv(nb, E::BK), acc, smem, false, mma);
-        }, store);
-      } else {
-        gemm_mainloop_dma<E, Cfg, 2>(la, lb, cdiv(nb, E::BK), acc, smem);
-        acc.for_each(store);
-      }
-      return;
-    }
-  }
   if constexpr (kBPre && kPieces<P> > 0) {
     // A: C_Omega^T (x = q, k = mu) from its per-call piece planes; B: column
     // r = l*n_bf + nu, piece-plane row r of the pre-split b (k = mu
@@ -271,7 +301,10 @@ __device__ void half_tile_with(const HalfArgs& a, long t, char* smem) {
 // Separate kernels for b split on load (half) and pre-split (halfp), so each
 // keeps its own register budget.
 template <int P, class Cfg>
-__device__ void half_tile(const HalfArgs& a, long t, char* smem) { half_tile_with<P, Cfg, false, false>(a, t, smem); }
+__device__ __forceinline__ void half_tile(const HalfArgs& a, long t, char* smem) {
+  if constexpr (is_strip<Cfg>::value) half_strip<Cfg>(a, t, smem);
+  else half_tile_with<P, Cfg, false, false>(a, t, smem);
+}
 // The single-molecule pre-split half transform in the split modes runs
 // persistent workgroups (one per resident slot, tiles strided by the grid),
 // whose direct loads run ahead into the next tile while a tile's epilogue
@@ -313,7 +346,10 @@ __device__ void halfp_tile(const HalfArgs& a, long t, char* smem) {
     half_tile_with<P, Cfg, true, false>(a, t, smem);
 }
 template <int P, class Cfg>
-__device__ void half_g_tile(const HalfArgs& a, long t, char* smem) { half_tile_with<P, Cfg, false, true>(a, t, smem); }
+__device__ __forceinline__ void half_g_tile(const HalfArgs& a, long t, char* smem) {
+  if constexpr (is_strip<Cfg>::value) half_strip<Cfg>(a, t, smem);
+  else half_tile_with<P, Cfg, false, true>(a, t, smem);
+}
 template <int P, class Cfg>
 __device__ void halfp_g_tile(const HalfArgs& a, long t, char* smem) { half_tile_with<P, Cfg, true, true>(a, t, smem); }
 template <int P, class Cfg>
@@ -455,10 +491,82 @@ __host__ __device__ inline long jao_active(int nb, int tmu, int tnu) {  // block
 // mirrored, so every element of the full matrix is written exactly once.
 template <int P, class Cfg>
 __host__ __device__ inline long jao_tiles(const JaoArgs& a) {
-  return jao_active(a.nb, Cfg::BN / kJaoTNU, kJaoTNU) * cdiv(a.nw, Cfg::BM);
+  return jao_active(a.nb, Cfg::BN / kJaoTNU, kJaoTNU) * cdiv(a.nw, Cfg::BM);   // (128-row strips: as many tiles)
 }
-template <int P, class Cfg, bool kTrim = false>
-__device__ void jao_tile(const JaoArgs& a, long t, char* smem) {
+// Tile r of the list of live blocks: its first row and column; false past the list.
+__device__ __forceinline__ bool up_block(long r, int nb, int tmu, int& mu0, int& nu0) {
+  const int nbj = cdiv(nb, kJaoTNU), nbi = cdiv(nb, tmu);
+  int bi = 0;
+  for (; bi < nbi; ++bi) {
+    const int n = nbj - jao_first_col(bi, tmu, kJaoTNU);
+    if (r < n) break;
+    r -= n;
+  }
+  if (bi >= nbi) return false;
+  mu0 = bi * tmu;
+  nu0 = (jao_first_col(bi, tmu, kJaoTNU) + (int)r) * kJaoTNU;
+  return true;
+}
+// Offset of the pair at (even) tile column x from the operand's start: row
+// mu0 + x / 16, position nu0 + x % 16 (odd n_bf: the last pair one early).
+__device__ __forceinline__ long up_offset(int x, int mu0, int nu0, int nb) {
+  const int mu = mu0 + x / kJaoTNU, p = nu0 + x % kJaoTNU;
+  return mu < nb && p < nb ? (long)mu * nb + pair_start(p, nb) : 0;
+}
+// FP64 J^q on strip tiles.  The mirrored half goes through LDS (a row's TMU
+// elements of one nu side by side) so that a store instruction writes whole
+// 64-byte pieces: written straight from the accumulators, one 8-byte element
+// per row, it took 36 us of a 298 us launch at the cyclohexane-like size.
+// Per launch 312 -> 294 us there, 2.70 -> 2.22 ms at the cyclodecane-like size.
+template <class Cfg>
+__device__ __forceinline__ void jao_strip(const JaoArgs& a, long t, char* smem) {
+  constexpr int TMU = Cfg::BN / kJaoTNU;
+  const int nb = a.nb, na = a.na, nw = a.nw, nqt = strip_tiles(nw), tm = strip_frags(nw);
+  int mu0, nu0;
+  if (!up_block(t / nqt, nb, TMU, mu0, nu0)) return;
+  const int q0 = (int)(t % nqt) * 16 * tm;
+  const long B2 = (long)nb * nb;
+  double* Jn = (double*)a.Jn;
+  with_frags(tm, [&](auto frags) {
+    using L = Strip<Cfg, decltype(frags)::value>;
+    StripStage<L> st;
+    st.init(a.d, nw, [&](int x) -> long { return q0 + x < nw ? pair_start(q0 + x, nw) : 0; },
+            a.b, B2, [&](int x) -> long { return up_offset(x, mu0, nu0, nb); });
+    StripAcc<L> acc;
+    strip_mainloop(cdiv(na, 16), st.w, acc, smem, [&](int kt, lds_char* s) { st.issue(s, na - 16 * kt); });
+    const int kr = (threadIdx.x & 63) >> 4, xc = threadIdx.x & 15, nu = pair_column(nu0 + xc, nb);
+    // T[buffer][row of the pass][nu][mu], rows of TMU + 1
+    constexpr int R = 16 * L::WVM, TS = R * 16 * (TMU + 1);
+    static_assert(2 * TS * 8 <= strip_smem<Cfg>(), "two passes in LDS");
+    lds_f64* T = (lds_f64*)(lds_char*)smem;
+#pragma unroll
+    for (int i = 0; i < L::FM; ++i) {
+      lds_f64* Ti = T + (i & 1) * TS;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int m = acc.wm + 16 * i + kr + 4 * e, q = pair_column(q0 + m, nw);
+        const int row = acc.wm / (16 * L::FM) * 16 + kr + 4 * e;
+#pragma unroll
+        for (int j = 0; j < L::FN; ++j) {
+          const int ml = acc.wn / 16 + j, mu = mu0 + ml;
+          if (q >= 0 && nu >= 0 && mu <= nu) Jn[(long)q * B2 + (long)mu * nb + nu] = acc.v[i][j][e];
+          Ti[(row * 16 + xc) * (TMU + 1) + ml] = acc.v[i][j][e];
+        }
+      }
+      __syncthreads();   // (the other buffer's readers are a barrier behind)
+#pragma unroll
+      for (int k = 0; k < R * 16 * TMU / Cfg::NT; ++k) {
+        const int y = (int)threadIdx.x + k * Cfg::NT, ml = y % TMU, nl = y / TMU % 16, row = y / (16 * TMU);
+        const int q = pair_column(q0 + row / 16 * (16 * L::FM) + 16 * i + row % 16, nw);
+        const int mu = mu0 + ml, nuc = pair_column(nu0 + nl, nb);
+        if (q >= 0 && nuc >= 0 && mu < nuc) Jn[(long)q * B2 + (long)nuc * nb + mu] = Ti[(row * 16 + nl) * (TMU + 1) + ml];
+      }
+    }
+    __syncthreads();   // a grouped workgroup's next tile stages into this LDS
+  });
+}
+template <int P, class Cfg, bool kTrim>
+__device__ void jao_tile_with(const JaoArgs& a, long t, char* smem) {
   using E = typename EngineOf<P>::type;
   constexpr int TNU = kJaoTNU, TMU = Cfg::BN / TNU;
   const int nb = a.nb, na = a.na, nw = a.nw;
@@ -493,24 +601,7 @@ __device__ void jao_tile(const JaoArgs& a, long t, char* smem) {
     }
   };
   const int fim = cdiv(nw - q0, 16);   // live fragment rows
-  bool staged = false;
-  if constexpr (P == kF64 && Cfg::BM == 128 && Cfg::BN == 128) {
-    if (a.dma) {   // both operands by direct global -> LDS loads
-      XcDma64<Cfg::NT, E::BK, E::PAD> la, lb;
-      la.init(a.d, nw, na, [&](int x, long& o) { o = q0 + x; return q0 + x < nw; });
-      lb.init(a.b, B2, na, b_off);
-      if constexpr (kTrim) {
-        run_q_rows<P, Cfg, kTrim>(fim, acc, [&](auto mma) {
-          gemm_mainloop_dma_with<E, Cfg, 2>(la, lb, cdiv(na, E::BK), acc, smem, false, mma);
-        }, store);
-        return;
-      } else {
-        gemm_mainloop_dma<E, Cfg, 2>(la, lb, cdiv(na, E::BK), acc, smem);
-        staged = true;
-      }
-    }
-  }
-  if (!staged) {
+  {
     // A: d^T (x = q, k = l), from piece planes in the split modes
     typename std::conditional<kPlanesHalfJao<P>, PCS<P, Cfg::BM, Cfg::NT>, XCS<P, double, Cfg::BM, Cfg::NT>>::type la;
     if constexpr (kPlanesHalfJao<P>)
@@ -532,7 +623,15 @@ __device__ void jao_tile(const JaoArgs& a, long t, char* smem) {
 }
 
 template <int P, class Cfg>
-__device__ void jao_g_tile(const JaoArgs& a, long t, char* smem) { jao_tile<P, Cfg, true>(a, t, smem); }
+__device__ __forceinline__ void jao_tile(const JaoArgs& a, long t, char* smem) {
+  if constexpr (is_strip<Cfg>::value) jao_strip<Cfg>(a, t, smem);
+  else jao_tile_with<P, Cfg, false>(a, t, smem);
+}
+template <int P, class Cfg>
+__device__ __forceinline__ void jao_g_tile(const JaoArgs& a, long t, char* smem) {
+  if constexpr (is_strip<Cfg>::value) jao_strip<Cfg>(a, t, smem);
+  else jao_tile_with<P, Cfg, true>(a, t, smem);
+}
 
 // The same J^q tile with b read as pre-split piece planes (split modes):
 // B element (x = (mu, nu) of the block, k = l) at plane row mu*n_bf + nu, and
@@ -864,40 +963,102 @@ struct FockB {  // element (q, nu) of slab t: coef_t[q] * C[nu][q]; r[R] holds c
   __device__ double val(const double (&r)[RR], int p, int i) const { return r[R] * r[p * KV + i]; }
 };
 
-// FP64 Fock operands by direct global -> LDS loads (128 x 128 tiles, one
-// 128-column k-row per wave load into the engine's padded [k][x] layout).
-// Slice g of the stacked slabs holds rows nu0 .. nu0+15 of slab t = g / nchunk
-// (nu0 = 16 (g mod nchunk)); rows at or past n_bf read zeros.  A: element
-// (mu, nu) of slab t read as row nu of X_t (J^t or K^t, symmetric); B: row nu
-// of C (x = q), scaled by the slab's coefficient at MFMA time.
-template <int NT>
-struct FockDma {
-  static constexpr int NW = NT / 64, BK = 16, UPW = BK / NW, STRIDE = (128 + EngF64::PAD) * 8;
-  static_assert(BK % NW == 0, "k rows per wave");
-  const double *J, *K, *C;   // A: J, K (slabs of B2); B: C (J == nullptr)
-  long B2, ld;
-  int nb, nw, g0, nchunk, col;
-  __device__ int count() const { return UPW; }
-  __device__ void issue(int kt, lds_char* S) const {
-    const int w = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
-    const int g = g0 + kt, t = g / nchunk, nu0 = (g - t * nchunk) * BK;
-    const double* base = J ? (t < nw ? J + (long)t * B2 : K + (long)(t - nw) * B2) : C;
+// FP64 Fock step on strip tiles, from the other side: F^(q) = sum_t A_qt J^t +
+// B_qt K^t on the upper triangle (a J^q-shaped product: M = q, N = a live block
+// of (mu, nu), K = the 2 n_omega slabs), and at once Y[mu][q] += F_mu,nu C[nu][q]
+// and Y[nu][q] += F_mu,nu C[mu][q] in the epilogue.  The slabs are symmetric, so
+// this takes half the products of X_t C summed over t, and reads half of Jn and
+// Kn.  Partials per tile, summed over tiles in a fixed order by the Fock
+// reduction: TMU rows (over the block's 16 nu), then 16 columns (over its mu):
+//   Yp[tile][TMU][n_omega], then Yp'[tile][16][n_omega], tile = block of (mu, nu).
+// 162 -> 84 us at the cyclohexane-like size, 1366 -> 664 at the cyclodecane-like.
+constexpr int kFockTMU = 8;
+__host__ __device__ inline long fock_strip_doubles(int nb, int nw) {
+  return jao_active(nb, kFockTMU, kJaoTNU) * (kFockTMU + 16) * nw;
+}
+template <class Cfg>
+__device__ __forceinline__ void fock_strip(const FockArgs& a, long t, char* smem) {
+  constexpr int TMU = kFockTMU;
+  static_assert(Cfg::BN == TMU * kJaoTNU, "block of (mu, nu)");
+  const int nb = a.nb, nw = a.nw, nqt = strip_tiles(nw), tm = strip_frags(nw), nks = cdiv(nw, 16);
+  int mu0, nu0;
+  const long blk = t / nqt;
+  if (!up_block(blk, nb, TMU, mu0, nu0)) return;
+  const int q0 = (int)(t % nqt) * 16 * tm;
+  const long B2 = (long)nb * nb;
+  double* Pr = a.Yp + blk * TMU * nw;
+  double* Pc = a.Yp + jao_active(nb, TMU, kJaoTNU) * TMU * nw + blk * 16 * nw;
+  with_frags(tm, [&](auto frags) {
+    using L = Strip<Cfg, decltype(frags)::value>;
+    StripStage<L> st;
+    // A and B are symmetric: row t of either holds the coefficients of slab t along q
+    st.init(a.Ac, nw, [&](int x) -> long { return q0 + x < nw ? pair_start(q0 + x, nw) : 0; },
+            (const double*)a.Jn, B2, [&](int x) -> long { return up_offset(x, mu0, nu0, nb); });
+    StripAcc<L> acc;
+    strip_mainloop(2 * nks, st.w, acc, smem, [&](int kt, lds_char* s) {
+      if (kt == nks) st.rebase(a.Bc, (const double*)a.Kn);
+      st.issue(s, nw - 16 * (kt < nks ? kt : kt - nks));
+    });
+    const int lane = threadIdx.x & 63, kr = lane >> 4, xc = lane & 15, nu = pair_column(nu0 + xc, nb);
+    // column sums CS[nu][q], row sums RS[mu][q] of the tile
+    constexpr int LD = L::BM + 1;
+    static_assert((16 + TMU) * LD * 8 <= strip_smem<Cfg>(), "sums in LDS");
+    lds_f64* CS = (lds_f64*)(lds_char*)smem;
+    lds_f64* RS = CS + 16 * LD;
+    double cs[L::FM][4];
 #pragma unroll
-    for (int j = 0; j < UPW; ++j) {
-      const int r = w + j * NW, nu = nu0 + r;
-      const double* src = nu < nb ? base + (long)nu * ld + col : kDmaZeros + 2 * lane;
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                       (__attribute__((address_space(3))) void*)(S + r * STRIDE), 16, 0, 0);
+    for (int i = 0; i < L::FM; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int m = acc.wm + 16 * i + kr + 4 * e, q = pair_column(q0 + m, nw);
+        const bool ok = q >= 0 && nu >= 0;
+        const double cn = ok ? a.C[(long)nu * a.nmo + q] : 0.0;
+        double c = 0.0;
+#pragma unroll
+        for (int j = 0; j < L::FN; ++j) {
+          const int ml = acc.wn / 16 + j, mu = mu0 + ml;
+          const double F = acc.v[i][j][e];
+          if (ok && mu < nu) c = fma(F, a.C[(long)mu * a.nmo + q], c);
+          // over the block's nu: the sixteen lanes of a row, the same bits in each
+          double r = ok && mu <= nu ? F * cn : 0.0;
+          r += dpp_move<0xB1>(r);
+          r += dpp_move<0x4E>(r);
+          r += dpp_move<0x124>(r);
+          r += dpp_move<0x128>(r);
+          if (xc == 0) RS[ml * LD + m] = r;
+        }
+        cs[i][e] = c;
+      }
+    // the waves along N hold other mu of the same (nu, q): one after the other
+    const int wn = acc.wn / (16 * L::FN);
+#pragma unroll
+    for (int k = 0; k < L::WVN; ++k) {
+      if (wn == k) {
+#pragma unroll
+        for (int i = 0; i < L::FM; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            lds_f64* p = CS + xc * LD + acc.wm + 16 * i + kr + 4 * e;
+            *p = k == 0 ? cs[i][e] : *p + cs[i][e];
+          }
+      }
+      __syncthreads();
     }
-  }
-};
+    for (int y = threadIdx.x; y < (16 + TMU) * L::BM; y += Cfg::NT) {
+      const int m = y % L::BM, r = y / L::BM, q = pair_column(q0 + m, nw);
+      if (q >= 0) (r < 16 ? Pc + (long)r * nw : Pr + (long)(r - 16) * nw)[q] = CS[r * LD + m];
+    }
+    __syncthreads();   // a grouped workgroup's next tile stages into this LDS
+  });
+}
 
 template <int P, class Cfg>
 __host__ __device__ inline long fock_tiles(const FockArgs& a) {
-  return (long)cdiv(a.nb, Cfg::BM) * cdiv(a.nw, Cfg::BN) * a.nsplit;
+  if constexpr (is_strip<Cfg>::value) return jao_active(a.nb, kFockTMU, kJaoTNU) * strip_tiles(a.nw);
+  else return (long)cdiv(a.nb, Cfg::BM) * cdiv(a.nw, Cfg::BN) * a.nsplit;
 }
 template <int P, class Cfg>
-__device__ void fock_tile(const FockArgs& a, long t, char* smem) {
+__device__ void fock_tile_with(const FockArgs& a, long t, char* smem) {
   using E = typename EngineOf<P>::type;
   const int nb = a.nb, nw = a.nw;
   const int nmt = cdiv(nb, Cfg::BM), nnt = cdiv(nw, Cfg::BN);
@@ -906,54 +1067,6 @@ __device__ void fock_tile(const FockArgs& a, long t, char* smem) {
   const int s = (int)(t / ((long)nmt * nnt));
   const long S = 2L * nw * cdiv(nb, E::BK);   // slices over all slabs
   const int g0 = (int)(S * s / a.nsplit), g1 = (int)(S * (s + 1) / a.nsplit);
-  if constexpr (P == kF64 && Cfg::BM == 128 && Cfg::BN == 128) {
-    if (a.dma) {
-      const int lane = (int)(threadIdx.x & 63), nchunk = cdiv(nb, E::BK);
-      FockDma<Cfg::NT> la{(const double*)a.Jn, (const double*)a.Kn, nullptr, (long)nb * nb, nb,
-                          nb, nw, g0, nchunk, mu0 + 2 * lane < nb ? mu0 + 2 * lane : 0};
-      FockDma<Cfg::NT> lb{nullptr, nullptr, a.C, 0, a.nmo, nb, nw, g0, nchunk, q0 + 2 * lane < nw ? q0 + 2 * lane : 0};
-      typename E::template Acc<Cfg> acc;
-      int kt = 0, tc = -1;
-      double cq[Cfg::TN];
-      int wm0, wn0;
-      wave_origin(Cfg::WAVES_N, Cfg::WM, Cfg::WN, wm0, wn0);
-      const int kr = lane >> 4, xc = lane & 15;
-      // B element (q, nu) = coef_t[q] * C[nu][q], the product the register
-      // path stages; the coefficients change once per slab
-      gemm_mainloop_dma_with<E, Cfg, 2>(la, lb, g1 - g0, acc, smem, false,
-                                        [&](const lds_char* SA, const lds_char* SB, typename E::template Acc<Cfg>& c) {
-        const int t = (g0 + kt++) / nchunk;
-        if (t != tc) {
-          tc = t;
-#pragma unroll
-          for (int j = 0; j < Cfg::TN; ++j) {
-            const int q = q0 + wn0 + j * 16 + xc;
-            cq[j] = q < nw ? (t < nw ? a.Ac[(long)q * nw + t] : a.Bc[(long)q * nw + (t - nw)]) : 0.0;
-          }
-        }
-        const lds_f64* As = (const lds_f64*)SA;
-        const lds_f64* Bs = (const lds_f64*)SB;
-#pragma unroll
-        for (int kk = 0; kk < E::BK; kk += 4) {
-          double av[Cfg::TM], bv[Cfg::TN];
-#pragma unroll
-          for (int i = 0; i < Cfg::TM; ++i) av[i] = As[(kk + kr) * (Cfg::BM + E::PAD) + wm0 + i * 16 + xc];
-#pragma unroll
-          for (int j = 0; j < Cfg::TN; ++j) bv[j] = cq[j] * Bs[(kk + kr) * (Cfg::BN + E::PAD) + wn0 + j * 16 + xc];
-#pragma unroll
-          for (int i = 0; i < Cfg::TM; ++i)
-#pragma unroll
-            for (int j = 0; j < Cfg::TN; ++j)
-              c.v[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i], bv[j], c.v[i][j], 0, 0, 0);
-        }
-      });
-      double* Y = a.Yp + (long)s * nb * nw;
-      acc.for_each([&](int m, int n, double v) {
-        if (mu0 + m < nb && q0 + n < nw) Y[(long)(mu0 + m) * nw + q0 + n] = v;
-      });
-      return;
-    }
-  }
   FockA<P, Cfg> la;
   la.init((const IOT<P>*)a.Jn, (const IOT<P>*)a.Kn, nb, nw, g0, mu0);
   FockB<P, Cfg> lb;
@@ -964,6 +1077,12 @@ __device__ void fock_tile(const FockArgs& a, long t, char* smem) {
   acc.for_each([&](int m, int n, double v) {
     if (mu0 + m < nb && q0 + n < nw) Y[(long)(mu0 + m) * nw + q0 + n] = v;
   });
+}
+
+template <int P, class Cfg>
+__device__ __forceinline__ void fock_tile(const FockArgs& a, long t, char* smem) {
+  if constexpr (is_strip<Cfg>::value) fock_strip<Cfg>(a, t, smem);
+  else fock_tile_with<P, Cfg>(a, t, smem);
 }
 
 // ---- gradient without per-MO AO matrices ---------------------------------------
@@ -1363,8 +1482,34 @@ __device__ void fred_tile(const FockRedArgs& a, long t, char*) {
   if (i >= n) return;
   const int q = (int)(i % a.nw);
   double y = a.occ[q] * a.HC[i];
+  if (a.strip) {   // the blocks of row mu, then those whose columns hold mu
+    constexpr int TMU = kFockTMU;
+    const int mu = (int)(i / a.nw), nbj = cdiv(a.nb, kJaoTNU), bi = mu / TMU;
+    // position of column mu in its row of pairs
+    const int p = (a.nb & 1) && mu == a.nb - 1 ? a.nb : mu, bj = p / kJaoTNU;
+    long at = 0, all = 0;   // blocks before row bi, and all
+    for (int k = 0; k < cdiv(a.nb, TMU); ++k) {
+      const int c = nbj - jao_first_col(k, TMU, kJaoTNU);
+      if (k < bi) at += c;
+      all += c;
+    }
+    const double* Pr = a.Yp + (at * TMU + mu % TMU) * a.nw + q;
+    const int cr = nbj - jao_first_col(bi, TMU, kJaoTNU);
 #pragma unroll 8
-  for (int s = 0; s < a.nsplit; ++s) y += a.Yp[(long)s * n + i];
+    for (int k = 0; k < cr; ++k) y += Pr[(long)k * TMU * a.nw];
+    const double* Pc = a.Yp + (all * TMU + p % kJaoTNU) * a.nw + q;
+    // rows k with a block at column bj: k TMU <= 16 bj + 15
+    const int last = min(cdiv(a.nb, TMU), (kJaoTNU * bj + kJaoTNU - 1) / TMU + 1);
+    at = 0;
+    for (int k = 0; k < last; ++k) {
+      const int f = jao_first_col(k, TMU, kJaoTNU);
+      y += Pc[(at + bj - f) * 16 * a.nw];
+      at += nbj - f;
+    }
+  } else {
+#pragma unroll 8
+    for (int s = 0; s < a.nsplit; ++s) y += a.Yp[(long)s * n + i];
+  }
   a.Y[i] = y;
 }
 
@@ -1435,11 +1580,17 @@ __device__ __forceinline__ int find_owner(const long* __restrict__ off, int n, l
 // direct-staged path would.
 template <int P, class Cfg>
 constexpr int gemm_wpe() {
+  if (is_strip<Cfg>::value) return Cfg::NT == 512 ? 4 : 3;   // two, or three, workgroups per CU
   return Cfg::NT == 1024 ? 4 : Cfg::NT == 512 ? (P == kF64 ? 4 : 2) : 1;
 }
-#define GEMM_SMEM smem_bytes<typename EngineOf<P>::type, Cfg>()
+template <int P, class Cfg>
+constexpr int gemm_smem() {
+  if constexpr (is_strip<Cfg>::value) return strip_smem<Cfg>();
+  else return smem_bytes<typename EngineOf<P>::type, Cfg>();
+}
+#define GEMM_SMEM gemm_smem<P, Cfg>()
 #define GEMM_WPE (gemm_wpe<P, Cfg>())
-RIF_STEP_KERNELS(half, HalfArgs, GEMM_SMEM, Cfg::NT, false, GEMM_WPE, GEMM_WPE, half_g_tile)
+RIF_STEP_KERNELS(half, HalfArgs, GEMM_SMEM, Cfg::NT, is_strip<Cfg>::value, GEMM_WPE, GEMM_WPE, half_g_tile)
 // the pre-split half transform and J^q stage piece planes directly (split modes)
 #define GEMM_SMEM_DMA \
   (kPieces<P> > 0 ? smem_bytes_dma<typename EngineOf<P>::type, Cfg>() : smem_bytes<typename EngineOf<P>::type, Cfg>())
@@ -1451,7 +1602,7 @@ RIF_STEP_KERNELS(jaop, JaoArgs, GEMM_SMEM_DMA, Cfg::NT, false, GEMM_WPE, 1, jaop
 #define KAO_SMEM (P == kF64 && Cfg::BM == 64 ? 3 * 2 * EngF64T<16, 0>::template stage_bytes<64>() : GEMM_SMEM)
 RIF_STEP_KERNELS(kao, KaoArgs, KAO_SMEM, Cfg::NT, true, GEMM_WPE, 1, kao_tile)
 RIF_STEP_KERNELS(gemm, GemmArgs, GEMM_SMEM, Cfg::NT, false, GEMM_WPE, 1, gemm_tile)
-RIF_STEP_KERNELS(fock, FockArgs, GEMM_SMEM, Cfg::NT, false, GEMM_WPE, GEMM_WPE, fock_tile)
+RIF_STEP_KERNELS(fock, FockArgs, GEMM_SMEM, Cfg::NT, is_strip<Cfg>::value, GEMM_WPE, GEMM_WPE, fock_tile)
 RIF_STEP_KERNELS(yd, YdArgs, GEMM_SMEM, Cfg::NT, false, GEMM_WPE, 1, yd_tile)
 RIF_STEP_KERNELS(ydz, YdzArgs, kYdzLds * 8, 256, false, 1, 1, ydz_tile)
 RIF_STEP_KERNELS(jkp, JkArgs, 16, 256, false, 1, 1, jkp_tile)
@@ -1489,6 +1640,45 @@ template <> struct Vars<32> {
 struct Cfg256 { static constexpr int NT = 256; };  // element-wise steps
 struct CfgEnergy { static constexpr int NT = kEnergyThreads; };
 
+// The FP64 half transform, J^q and Fock step: strip tiles of 128 (variant 0) or
+// 64 columns (1; J^q and the half transform only), and the 64 x 64 tile staged
+// through registers for the operands that strips do not take (strip_fits).
+using Strip128 = StripCfg<128, 8>;
+using Strip64 = StripCfg<64, 4>;
+using Reg64 = Vars<16>::V1;
+template <class F>
+static decltype(auto) dispatch_strip(int v, F&& f) {
+  switch (v) {
+    case 0: return f(Strip128());
+    case 1: return f(Strip64());
+    default: return f(Reg64());
+  }
+}
+template <int P, class F>
+static decltype(auto) dispatch(int v, F&& f);
+// variants of a step and their tiles: dispatch_<step><P>(v, f), kVariants_<step>
+template <int P, class F>
+static decltype(auto) dispatch_half(int v, F&& f) {
+  if constexpr (P == kF64) return dispatch_strip(v, f);
+  else return dispatch<P>(v, f);
+}
+template <int P, class F>
+static decltype(auto) dispatch_jao(int v, F&& f) { return dispatch_half<P>(v, f); }
+template <int P, class F>
+static decltype(auto) dispatch_fock(int v, F&& f) {
+  if constexpr (P == kF64) {
+    if (v == 0) return f(Strip128());
+    return f(Reg64());
+  } else {
+    return dispatch<P>(v, f);
+  }
+}
+template <int P, class F>
+static decltype(auto) dispatch_halfp(int v, F&& f) { return dispatch<P>(v, f); }
+template <int P, class F>
+static decltype(auto) dispatch_mo(int v, F&& f) { return dispatch<P>(v, f); }
+template <int P, class F>
+static decltype(auto) dispatch_kao(int v, F&& f) { return dispatch<P>(v, f); }
 template <int P, class F>
 static decltype(auto) dispatch(int v, F&& f) {
   using VS = Vars<EngineOf<P>::type::BK>;
@@ -1510,10 +1700,13 @@ static double est_cost(long nwg, int wg_per_cu, long tile_mn, double useful) {
 }
 template <int P, class Cfg>
 static int wg_per_cu() {
+  if constexpr (is_strip<Cfg>::value) return 163840 / strip_smem<Cfg>();
+  else {
   using E = typename EngineOf<P>::type;
   const int lds = 163840 / smem_bytes<E, Cfg>();
   const int waves = 32 / Cfg::NWAVES;  // at most 8 waves per SIMD
   return std::max(1, std::min(std::min(lds, waves), 4));
+  }
 }
 template <class F>
 static int best_of(int nvar, F&& cost) {
@@ -1611,24 +1804,93 @@ static long jaop_grid(const JaoArgs& a) {
 
 RIF_GEMM_STEP(half, HalfArgs, "half_transform", 4, a.nb, a.nr, a.nw, a.nmo)
 RIF_GEMM_STEP(halfp, HalfArgs, "half_transform_presplit", 4, a.nb, a.nr, a.nw, a.nmo)
+// FP64 strips by default: the tile width whose fullest CU has the fewer columns
+// to do, 64-wide tiles counted 8% dearer (they read as many rows of the other
+// operand for half the columns).  128 against 64, J^q: 47.7 / 48.4 us at n_bf
+// 201 (182 tiles of 128), 202.6 / 169.8 at 288 (342), 52.7 / 38.4 at 160 (110);
+// half transform: 53.1 / 49.4 at 160 (600 tiles), 276 / 280 at 288 (1944), 13.9 /
+// 15.4 at 100 (235).
+static int strip_default(long tiles128, long tiles64) {
+  return cdiv(tiles128, 256) * 128.0 <= cdiv(tiles64, 256) * 64.0 * 1.08 ? 0 : 1;
+}
+static rif_status step_half64(rif_ctx* c, const HalfArgs& a) {
+  auto run = [&](int v) {
+    return dispatch_strip(v, [&](auto cfg) {
+      using Cfg = decltype(cfg);
+      hipLaunchKernelGGL((k_half<kF64, Cfg>), dim3((unsigned)half_tiles<kF64, Cfg>(a)), dim3(Cfg::NT), 0, c->stream, a);
+      return check_launch(c, "half_transform");
+    });
+  };
+  int v = 2;
+  if (strip_fits(a.nb, a.nmo, a.nw)) {
+    v = pick_variant(c, "half_transform", {kF64, a.nb, a.nr, a.nw, a.nmo}, 2,
+                     strip_default(half_tiles<kF64, Strip128>(a), half_tiles<kF64, Strip64>(a)), run);
+    if (v < 0) return RIF_EHIP;
+  }
+  ProfScope ps(c, "half_transform");
+  return run(v);
+}
 template <int P>
 static rif_status step_half_any(rif_ctx* c, const HalfArgs& a) {
-  if constexpr (P != kF64)
+  if constexpr (P == kF64) {
+    return step_half64(c, a);
+  } else {
     if (b_presplit<P>(a)) return step_halfp<P>(c, a);
-  return step_half<P>(c, a);
+    return step_half<P>(c, a);
+  }
 }
 RIF_GEMM_STEP(mo, MoArgs, "mo_transform", 4, a.nb, a.na, a.nw, a.nmo)
 RIF_GEMM_STEP(jao, JaoArgs, "jao", 4, a.nb, a.na, a.nw)
 RIF_GEMM_STEP(jaop, JaoArgs, "jao_presplit", 4, a.nb, a.na, a.nw)
+static rif_status step_jao64(rif_ctx* c, const JaoArgs& a) {
+  auto run = [&](int v) {
+    return dispatch_strip(v, [&](auto cfg) {
+      using Cfg = decltype(cfg);
+      hipLaunchKernelGGL((k_jao<kF64, Cfg>), dim3((unsigned)jao_tiles<kF64, Cfg>(a)), dim3(Cfg::NT), 0, c->stream, a);
+      return check_launch(c, "jao");
+    });
+  };
+  int v = 2;
+  if (strip_fits(a.nb, a.nw, a.nw)) {
+    v = pick_variant(c, "jao", {kF64, a.nb, a.na, a.nw}, 2,
+                     strip_default(jao_tiles<kF64, Strip128>(a), jao_tiles<kF64, Strip64>(a)), run);
+    if (v < 0) return RIF_EHIP;
+  }
+  ProfScope ps(c, "jao");
+  return run(v);
+}
 // J^q from the pre-split b where the build has it (split modes), else split on load.
 template <int P>
 static rif_status step_jao_any(rif_ctx* c, const JaoArgs& a) {
-  if constexpr (kPieces<P> > 0)
-    if (a.Bj.p) return step_jaop<P>(c, a);
-  return step_jao<P>(c, a);
+  if constexpr (P == kF64) {
+    return step_jao64(c, a);
+  } else {
+    if constexpr (kPieces<P> > 0)
+      if (a.Bj.p) return step_jaop<P>(c, a);
+    return step_jao<P>(c, a);
+  }
 }
 RIF_GEMM_STEP(kao, KaoArgs, "kao", 2, a.nb, a.na, a.nw)
 RIF_GEMM_STEP(fock, FockArgs, "fock", 4, a.nb, a.nw, a.nmo, a.nsplit)
+template <int P>
+static rif_status step_fock_any(rif_ctx* c, const FockArgs& a) {
+  if constexpr (P == kF64) {
+    // one strip shape: its partials' layout is part of the plan
+    auto run = [&](int v) {
+      return dispatch_fock<kF64>(v, [&](auto cfg) {
+        using Cfg = decltype(cfg);
+        hipLaunchKernelGGL((k_fock<kF64, Cfg>), dim3((unsigned)fock_tiles<kF64, Cfg>(a)), dim3(Cfg::NT), 0, c->stream, a);
+        return check_launch(c, "fock");
+      });
+    };
+    const int v = a.strip ? pick_variant(c, "fock", {kF64, a.nb, a.nw, a.nmo}, 1, 0, run) : 1;
+    if (v < 0) return RIF_EHIP;
+    ProfScope ps(c, "fock");
+    return run(v);
+  } else {
+    return step_fock<P>(c, a);
+  }
+}
 // The direct contraction has few q (n_omega) and many nu (n_bf) columns: its
 // first variant for the FP64/FP32 engines is a 256x128 16-wave tile, so one
 // tile spans all q of a split (b_half read once) and the b_mo coefficients are
@@ -1727,7 +1989,9 @@ struct Plan {
   long yd_kc;
   size_t o_part, o_hc, o_a, o_b, o_yp, o_y, o_ep, o_lp, o_cs, o_ds, bytes;
   size_t o_ydp, o_zt, o_bt, bytes_direct;   // the gradient without per-MO AO matrices
-  Plan(int nb_, int na_, int npairs_, int ncwo_, int nmo_) {
+  int fock_strip;   // the FP64 Fock step on strip tiles
+  // strip: whether the workspace may hold that step's partials
+  Plan(int nb_, int na_, int npairs_, int ncwo_, int nmo_, bool strip = true) {
     nb = nb_; na = na_; npairs = npairs_; ncwo = ncwo_; nmo = nmo_;
     nw = npairs * (1 + ncwo);
     const long w2 = (long)nw * nw;
@@ -1757,7 +2021,8 @@ struct Plan {
     o_hc = cv.take<double>((size_t)nb * nw);
     o_a = cv.take<double>((size_t)w2);
     o_b = cv.take<double>((size_t)w2);
-    o_yp = cv.take<double>((size_t)fock_nsplit * nb * nw);
+    fock_strip = strip && strip_fits(nb, nmo, nw);
+    o_yp = cv.take<double>(std::max((size_t)fock_nsplit * nb * nw, fock_strip ? (size_t)fock_strip_doubles(nb, nw) : 0));
     o_y = cv.take<double>((size_t)nb * nw);
     o_ep = cv.take<double>((size_t)nparts);
     o_lp = cv.take<double>((size_t)lam_split * nmo * nw);
@@ -1807,8 +2072,7 @@ static BuildArgs make_build_args(const Plan& pl, const rif_instance& in, int pre
   A.psc = PSplitArgs{in.C, (long)nmo, nw, nb, lc, Cs, (long)nw * lc};
   A.psd = PSplitArgs{in.d, (long)nw, nw, na, ldd, Ds, (long)nw * ldd};
   const Planes cs{Cs, (long)nw * lc, lc}, ds{Ds, (long)nw * ldd, ldd};
-  A.half = HalfArgs{nb, nw, nmo, (long)na * nb, in.b, in.C, in.b_half, cs, Planes{nullptr, 0, 0}, nullptr,
-                    half_dma_ok(nb, nmo, nw, in.b, in.C)};
+  A.half = HalfArgs{nb, nw, nmo, (long)na * nb, in.b, in.C, in.b_half, cs, Planes{nullptr, 0, 0}, nullptr};
   if (in.b_split && (prec == RIF_BF16X3 || prec == RIF_BF16X6 || prec == RIF_FP16X3)) {
     const int lb = round32(nb);
     A.half.Bs = Planes{(const unsigned short*)in.b_split, (long)na * nb * lb, lb};
@@ -1818,8 +2082,7 @@ static BuildArgs make_build_args(const Plan& pl, const rif_instance& in, int pre
   A.mo = MoArgs{nb, na, nw, nmo, in.b_half, in.C, in.b_mo, in.d, cs,
                 nb % 2 == 0 && nmo % 2 == 0 && ((uintptr_t)in.b_half | (uintptr_t)in.C) % 16 == 0};
   A.jk = JkArgs{na, nw, pl.jk_nsplit, in.b_mo, in.d, part, in.J, in.K};
-  A.jao = JaoArgs{nb, na, nw, in.b, in.d, in.Jn, ds, Planes{nullptr, 0, 0},
-                  nb % 2 == 0 && nw % 2 == 0 && ((uintptr_t)in.b | (uintptr_t)in.d) % 16 == 0};
+  A.jao = JaoArgs{nb, na, nw, in.b, in.d, in.Jn, ds, Planes{nullptr, 0, 0}};
   if (in.b_split && (prec == RIF_BF16X3 || prec == RIF_BF16X6 || prec == RIF_FP16X3)) {
     const long npc = prec == RIF_BF16X6 ? 3 : 2;
     const int lj = round32(na);
@@ -1831,10 +2094,8 @@ static BuildArgs make_build_args(const Plan& pl, const rif_instance& in, int pre
   A.coef = CoefArgs{functional, nw, pl.npairs, pl.ncwo, in.pair_of, in.occ, in.J, in.K, Ac, Bc, Ep};
   A.energy = EnergyArgs{nw, pl.npairs, pl.ncwo, nb, nmo, pl.nparts, in.pair_of, in.occ, in.C, HC, Ep, in.energy,
                         flag};
-  A.fock = FockArgs{nb, nw, nmo, pl.fock_nsplit, in.Jn, in.Kn, Ac, Bc, in.C, Yp,
-                    nb % 2 == 0 && nw % 2 == 0 && nmo % 2 == 0 &&
-                        ((uintptr_t)in.Jn | (uintptr_t)in.Kn | (uintptr_t)in.C) % 16 == 0};
-  A.fred = FockRedArgs{nb, nw, pl.fock_nsplit, Yp, in.occ, HC, Y};
+  A.fock = FockArgs{nb, nw, nmo, pl.fock_nsplit, in.Jn, in.Kn, Ac, Bc, in.C, Yp, prec == RIF_FP64 && pl.fock_strip};
+  A.fred = FockRedArgs{nb, nw, pl.fock_nsplit, Yp, in.occ, HC, Y, A.fock.strip};
   A.lam = GemmArgs{nmo, nw, nb, in.C, (long)nmo, Y, (long)nw, Lp, (long)nw, pl.lam_split, pl.small_kc,
                    (long)nmo * nw};
   A.grad = GradArgs{nmo, nw, pl.lam_split, Lp, in.lambda, in.grad, flag};
@@ -1843,7 +2104,7 @@ static BuildArgs make_build_args(const Plan& pl, const rif_instance& in, int pre
   double* Ydp = (double*)(ws + pl.o_ydp);
   A.ydz = YdzArgs{na, nw, Ac, Bc, in.d, Zt, Bt};
   A.yd = YdArgs{nb, na, nw, pl.yd_nsplit, pl.yd_kc, in.b_half, in.b_mo, Zt, Bt, Ydp};
-  A.ydred = FockRedArgs{nb, nw, pl.yd_nsplit, Ydp, in.occ, HC, Y};
+  A.ydred = FockRedArgs{nb, nw, pl.yd_nsplit, Ydp, in.occ, HC, Y, 0};
   return A;
 }
 
@@ -1856,7 +2117,7 @@ static rif_status run_transform(rif_ctx* c, const PSplitArgs& ps, const HalfArgs
 template <int P>
 static rif_status run_jk_ao(rif_ctx* c, const PSplitArgs& ps, const JaoArgs& j, const KaoArgs& k) {
   rif_status st = kPlanesHalfJao<P> ? step_psplit<P>(c, ps) : RIF_OK;
-  if (st || (st = step_jao<P>(c, j))) return st;
+  if (st || (st = step_jao_any<P>(c, j))) return st;
   return step_kao<P>(c, k);
 }
 template <int P>
@@ -1865,7 +2126,7 @@ static rif_status run_energy_grad(rif_ctx* c, const BuildArgs& A) {
   if ((st = step1_gemm(c, A.hc))) return st;
   if ((st = step1_coef(c, A.coef))) return st;
   if ((st = step1_energy(c, A.energy))) return st;
-  if ((st = step_fock<P>(c, A.fock))) return st;
+  if ((st = step_fock_any<P>(c, A.fock))) return st;
   if ((st = step1_fred(c, A.fred))) return st;
   if ((st = step1_gemm(c, A.lam))) return st;
   return step1_grad(c, A.grad);
@@ -1895,7 +2156,7 @@ rif_status op_transform(rif_ctx* c, int prec, int nb, int na, int nw, int nmo, c
   unsigned short* Cs = (unsigned short*)((char*)c->ws + o_cs);
   const Planes cs{Cs, (long)nw * lc, lc};
   const PSplitArgs ps{C, (long)nmo, nw, nb, lc, Cs, (long)nw * lc};
-  const HalfArgs h{nb, nw, nmo, (long)na * nb, b, C, bh, cs, Planes{}, nullptr, half_dma_ok(nb, nmo, nw, b, C)};
+  const HalfArgs h{nb, nw, nmo, (long)na * nb, b, C, bh, cs, Planes{}, nullptr};
   const MoArgs m{nb, na, nw, nmo, bh, C, bmo, d, cs,
                  nb % 2 == 0 && nmo % 2 == 0 && ((uintptr_t)bh | (uintptr_t)C) % 16 == 0};
   RIF_PREC_SWITCH(prec, run_transform<P>(c, ps, h, m))
@@ -1903,9 +2164,8 @@ rif_status op_transform(rif_ctx* c, int prec, int nb, int na, int nw, int nmo, c
 
 rif_status op_half_slabs_f64(rif_ctx* c, int nb, long nslab, int nw, int nmo, const double* slabs, const double* C,
                              double* out) {
-  const HalfArgs h{nb, nw, nmo, nslab * nb, slabs, C, out, Planes{}, Planes{}, nullptr,
-                   half_dma_ok(nb, nmo, nw, slabs, C)};
-  return step_half<kF64>(c, h);
+  const HalfArgs h{nb, nw, nmo, nslab * nb, slabs, C, out, Planes{}, Planes{}, nullptr};
+  return step_half64(c, h);
 }
 
 rif_status op_jk_mo(rif_ctx* c, int prec, int na, int nw, const void* bmo, const double* d, double* J, double* K) {
@@ -1980,8 +2240,7 @@ rif_status op_jk_ao(rif_ctx* c, int prec, int nb, int na, int nw, const double* 
   if (st) return st;
   unsigned short* Ds = (unsigned short*)((char*)c->ws + o_ds);
   const PSplitArgs ps{d, (long)nw, nw, na, ldd, Ds, (long)nw * ldd};
-  const JaoArgs j{nb, na, nw, b, d, Jn, Planes{Ds, (long)nw * ldd, ldd}, Planes{nullptr, 0, 0},
-                  nb % 2 == 0 && nw % 2 == 0 && ((uintptr_t)b | (uintptr_t)d) % 16 == 0};
+  const JaoArgs j{nb, na, nw, b, d, Jn, Planes{Ds, (long)nw * ldd, ldd}, Planes{nullptr, 0, 0}};
   const KaoArgs k{nb, na, nw, bh, Kn, nb % 2 == 0 && (uintptr_t)bh % 16 == 0};
   RIF_PREC_SWITCH(prec, run_jk_ao<P>(c, ps, j, k))
 }
@@ -1991,7 +2250,8 @@ rif_status op_energy_grad(rif_ctx* c, int prec, int functional, int nb, int nmo,
                           const double* J, const double* K, const void* Jn, const void* Kn, double* energy,
                           double* lambda, double* grad) {
   if (!prec_ok(prec)) return fail(c, RIF_ENOTSUP, "precision mode not available");
-  const Plan pl(nb, 1, npairs, ncwo, nmo);
+  Plan pl(nb, 1, npairs, ncwo, nmo);
+  if (!ws_fits(c, pl.bytes)) pl = Plan(nb, 1, npairs, ncwo, nmo, false);
   rif_status st = ws_reserve(c, pl.bytes);
   if (st) return st;
   rif_instance in{};
@@ -2047,7 +2307,7 @@ static rif_status run_build(rif_ctx* c, const BuildArgs& A) {
         (st = hip(hipEventRecord(e_energy, side))))
       return st;
   }
-  if ((st = step_fock<P>(c, A.fock)) || (st = step1_fred(c, A.fred)) || (st = step1_gemm(c, A.lam)) ||
+  if ((st = step_fock_any<P>(c, A.fock)) || (st = step1_fred(c, A.fred)) || (st = step1_gemm(c, A.lam)) ||
       (st = step1_grad(c, A.grad)))
     return st;
   return hip(hipStreamWaitEvent(main, e_energy, 0));
@@ -2105,7 +2365,8 @@ rif_status op_build(rif_ctx* c, int prec, int functional, const rif_instance& in
   if (!prec_ok(prec)) return fail(c, RIF_ENOTSUP, "precision mode not available");
   rif_status st = ensure_side(c);
   if (st) return st;
-  const Plan pl(in.n_bf, in.n_aux, in.n_pairs, in.n_cwo, in.n_mo);
+  Plan pl(in.n_bf, in.n_aux, in.n_pairs, in.n_cwo, in.n_mo);
+  if (!ws_fits(c, pl.bytes)) pl = Plan(in.n_bf, in.n_aux, in.n_pairs, in.n_cwo, in.n_mo, false);
   if ((st = ws_reserve(c, pl.bytes))) return st;
   const BuildArgs A = make_build_args(pl, in, prec, functional, (char*)c->ws, c->dflag);
   RIF_PREC_SWITCH(prec, run_build<P>(c, A))
@@ -2165,7 +2426,7 @@ rif_status op_build_direct(rif_ctx* c, int prec, int functional, const rif_insta
   if (!prec_ok(prec)) return fail(c, RIF_ENOTSUP, "precision mode not available");
   rif_status st = ensure_side(c);
   if (st) return st;
-  const Plan pl(in.n_bf, in.n_aux, in.n_pairs, in.n_cwo, in.n_mo);
+  const Plan pl(in.n_bf, in.n_aux, in.n_pairs, in.n_cwo, in.n_mo, false);   // (no Fock step)
   if ((st = ws_reserve(c, pl.bytes_direct))) return st;
   const BuildArgs A = make_build_args(pl, in, prec, functional, (char*)c->ws, c->dflag);
   RIF_PREC_SWITCH(prec, run_build_direct<P>(c, A))
@@ -2206,9 +2467,10 @@ static void group_offsets(const std::vector<Args>& a, TilesFn tiles, std::vector
   for (size_t i = 0; i < a.size(); ++i) off[i + 1] = off[i] + tiles(a[i]);
 }
 
-#define RIF_GROUP_SETUP(NAME, ARGS, LABEL, NVAR)                                                           \
+#define RIF_GROUP_SETUP(NAME, ARGS, LABEL, NV64, NVO)                                                      \
   template <int P>                                                                                         \
   static rif_status setup_##NAME(BatchImpl* B, const std::vector<ARGS>& a) {                              \
+    constexpr int NVAR = P == kF64 ? NV64 : NVO;                                                           \
     GroupStep& g = B->NAME;                                                                                \
     g.name = LABEL;                                                                                        \
     g.nvar = NVAR;                                                                                         \
@@ -2217,7 +2479,7 @@ static void group_offsets(const std::vector<Args>& a, TilesFn tiles, std::vector
     g.total.assign(NVAR, 0);                                                                               \
     g.grid.assign(NVAR, 0);                                                                                \
     for (int v = 0; v < NVAR; ++v) {                                                                       \
-      dispatch<P>(v, [&](auto cfg) {                                                                       \
+      dispatch_##NAME<P>(v, [&](auto cfg) {                                                                       \
         using Cfg = decltype(cfg);                                                                         \
         long acc = 0;                                                                                      \
         for (int i = 0; i < n; ++i) {                                                                      \
@@ -2242,9 +2504,10 @@ static void group_offsets(const std::vector<Args>& a, TilesFn tiles, std::vector
   }                                                                                                        \
   template <int P>                                                                                         \
   static rif_status launch_##NAME(BatchImpl* B, int v) {                                                   \
+    constexpr int NVAR = P == kF64 ? NV64 : NVO;                                                           \
     GroupStep& g = B->NAME;                                                                                \
     const int n = B->n;                                                                                    \
-    return dispatch<P>(v, [&](auto cfg) {                                                                  \
+    return dispatch_##NAME<P>(v, [&](auto cfg) {                                                                  \
       using Cfg = decltype(cfg);                                                                           \
       if constexpr (NVAR == 2 && Cfg::BM != Cfg::BN) {                                                     \
         return fail(B->c, RIF_ENOTSUP, LABEL ": non-square tile variant");                                 \
@@ -2286,12 +2549,12 @@ static void group_offsets(const std::vector<Args>& a, TilesFn tiles, std::vector
     return check_launch(B->c, LABEL);                                                                      \
   }
 
-RIF_GROUP_SETUP(half, HalfArgs, "g_half_transform", 4)
-RIF_GROUP_SETUP(halfp, HalfArgs, "g_half_transform_presplit", 4)
-RIF_GROUP_SETUP(mo, MoArgs, "g_mo_transform", 4)
-RIF_GROUP_SETUP(jao, JaoArgs, "g_jao", 4)
-RIF_GROUP_SETUP(kao, KaoArgs, "g_kao", 2)
-RIF_GROUP_SETUP(fock, FockArgs, "g_fock", 4)
+RIF_GROUP_SETUP(half, HalfArgs, "g_half_transform", 3, 4)
+RIF_GROUP_SETUP(halfp, HalfArgs, "g_half_transform_presplit", 4, 4)
+RIF_GROUP_SETUP(mo, MoArgs, "g_mo_transform", 4, 4)
+RIF_GROUP_SETUP(jao, JaoArgs, "g_jao", 3, 4)
+RIF_GROUP_SETUP(kao, KaoArgs, "g_kao", 2, 2)
+RIF_GROUP_SETUP(fock, FockArgs, "g_fock", 2, 4)
 #define RIF_GROUP_FIXED_P(NAME, ARGS, LABEL)                                                               \
   template <int P>                                                                                         \
   static rif_status setup_##NAME(BatchImpl* B, const std::vector<ARGS>& a) {                              \
@@ -2396,9 +2659,13 @@ static rif_status batch_setup(BatchImpl* B, const std::vector<BuildArgs>& A) {
     return st;
   // tile variants for the grouped GEMM steps: measured if autotuning, else the
   // variant with the fewest tile-area rounds
-  auto choose = [&](GroupStep& g, const std::function<rif_status(int)>& run) {
+  auto pick = [&](GroupStep& g, int nvar, int hv, const std::function<rif_status(int)>& run) {
     long key = 0;
-    for (long t : g.total) key = key * 1000003 + t;
+    for (int v = 0; v < nvar; ++v) key = key * 1000003 + g.total[v];
+    g.variant = pick_variant(B->c, g.name.c_str(), {P, B->n, key}, nvar, hv, run);
+    return g.variant < 0 ? RIF_EHIP : RIF_OK;
+  };
+  auto choose = [&](GroupStep& g, const std::function<rif_status(int)>& run) {
     int hv = 0;
     double best = 1e300;
     for (int v = 0; v < g.nvar; ++v) {
@@ -2409,17 +2676,31 @@ static rif_status batch_setup(BatchImpl* B, const std::vector<BuildArgs>& A) {
       });
       if (e < best) { best = e; hv = v; }
     }
-    g.variant = pick_variant(B->c, g.name.c_str(), {P, B->n, key}, g.nvar, hv, run);
-    return g.variant < 0 ? RIF_EHIP : RIF_OK;
+    return pick(g, g.nvar, hv, run);
+  };
+  // FP64: strips for the whole batch, or the register-staged tile if one
+  // molecule does not take them
+  bool strips = P == kF64;
+  for (auto& h : half) strips = strips && strip_fits(h.nb, h.nmo, h.nw);
+  auto choose_strip = [&](GroupStep& g, const std::function<rif_status(int)>& run) -> rif_status {
+    if (strips) return pick(g, 2, strip_default(g.total[0], g.total[1]), run);
+    g.variant = 2;
+    return RIF_OK;
   };
   if constexpr (P != kF64) {
     if (B->bpre && (st = choose(B->halfp, [&](int v) { return launch_halfp<P>(B, v); }))) return st;
   }
-  if (!B->bpre && (st = choose(B->half, [&](int v) { return launch_half<P>(B, v); }))) return st;
+  if constexpr (P == kF64) {
+    if ((st = choose_strip(B->half, [&](int v) { return launch_half<P>(B, v); }))) return st;
+    if ((st = choose_strip(B->jao, [&](int v) { return launch_jao<P>(B, v); }))) return st;
+    B->fock.variant = fock[0].strip ? 0 : 1;
+  } else {
+    if (!B->bpre && (st = choose(B->half, [&](int v) { return launch_half<P>(B, v); }))) return st;
+    if ((st = choose(B->jao, [&](int v) { return launch_jao<P>(B, v); }))) return st;
+    if ((st = choose(B->fock, [&](int v) { return launch_fock<P>(B, v); }))) return st;
+  }
   if ((st = choose(B->mo, [&](int v) { return launch_mo<P>(B, v); }))) return st;
-  if ((st = choose(B->jao, [&](int v) { return launch_jao<P>(B, v); }))) return st;
   if ((st = choose(B->kao, [&](int v) { return launch_kao<P>(B, v); }))) return st;
-  if ((st = choose(B->fock, [&](int v) { return launch_fock<P>(B, v); }))) return st;
   return RIF_OK;
 }
 
@@ -2468,9 +2749,11 @@ rif_status op_batch_create(rif_ctx* c, int prec, int functional, int n, const ri
   std::vector<Plan> plans;
   std::vector<size_t> base;
   size_t total = 0;
+  bool strips = true;   // one Fock kernel for the whole batch
+  for (int k = 0; k < n; ++k) strips = strips && strip_fits(inst[k].n_bf, inst[k].n_mo, inst[k].n_pairs * (1 + inst[k].n_cwo));
   for (int k = 0; k < n; ++k) {
     const rif_instance& in = inst[B->order[k]];
-    plans.emplace_back(in.n_bf, in.n_aux, in.n_pairs, in.n_cwo, in.n_mo);
+    plans.emplace_back(in.n_bf, in.n_aux, in.n_pairs, in.n_cwo, in.n_mo, strips);
     base.push_back(total);
     total += (plans.back().bytes + 255) & ~size_t(255);
   }
