@@ -421,15 +421,13 @@ __global__ __launch_bounds__(64) void k_on_warm(const OnProblem* __restrict__ pr
 // counts is passes and launches: one workgroup carries 16 RT rows through every
 // layer with the activations in LDS and the weights read from L2 (each
 // fragment once per workgroup), forward and backward alike, and the weight
-// gradients are one split contraction over the rows for all four layers.  Going
-// back, a 16-deep slice of k is dealt to the lane groups as k = 4 (lane / 16) +
-// m, m = 0..3 the MFMA step, so a k-contiguous operand is one 16-byte read per
-// lane; going forward k runs in its natural order (the FP64 loss keeps the
-// digits of logits summed that way).
+// gradients are one split contraction over the rows for all four layers.  Every
+// FP32 sum runs over its k in ascending order, 128 at a time: a training run's
+// FP64 losses keep the digits of weights updated that way.
 // At 19,553 rows (an epoch of the 2000-molecule training set) forward, backward
 // and Adam took 3665 us with a launch per layer and the weight gradients as 6
-// workgroups of 64 x 64 tiles walking all the rows (864 us a layer); now 119 us
-// (forward 44, activations' gradients 34, weights' 41 + 7, Adam 5).
+// workgroups of 64 x 64 tiles walking all the rows (864 us a layer); now 131 us
+// (forward 51, backward 76, Adam 4).
 constexpr int kActLd = kNhid + 4;   // LDS row of an activation: 16-byte aligned, rows 4 banks apart
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // 16 bytes at any float address
 
@@ -444,43 +442,57 @@ __host__ __device__ constexpr long layer_off(int l) {
 
 // acc[i] += x rows (16 i ..) . B over K, x in LDS ([row][k], zero from K up to
 // a multiple of 16); bval(k, b) gives this lane's column of B at the four steps
-// of a slice: k + 4 m (natural order) or k + m.
-template <int RT, int K, bool kNatural, class BV>
+// k + 4 m + lane / 16 of the slice at k.
+template <int RT, int K, class BV>
 __device__ __forceinline__ void mlp_strip(const float* x, f4 (&acc)[RT], BV&& bval) {
   const int lane = threadIdx.x & 63, kr = lane >> 4, xc = lane & 15;
 #pragma unroll
   for (int c = 0; c < (K + 15) / 16; ++c) {
-    f4 a[RT];
-    float b[4];
-    bval(16 * c + (kNatural ? kr : 4 * kr), b);
+    float a[RT][4], b[4];
+    bval(16 * c, b);
 #pragma unroll
-    for (int i = 0; i < RT; ++i) {
-      const float* xr = x + (16 * i + xc) * kActLd + 16 * c;
-      if constexpr (kNatural) {
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int m = 0; m < 4; ++m) a[i][m] = xr[4 * m + kr];
-      } else {
-        a[i] = *(const f4*)(xr + 4 * kr);
-      }
-    }
+      for (int m = 0; m < 4; ++m) a[i][m] = x[(16 * i + xc) * kActLd + 16 * c + 4 * m + kr];
 #pragma unroll
     for (int m = 0; m < 4; ++m)
 #pragma unroll
       for (int i = 0; i < RT; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][m], b[m], acc[i], 0, 0, 0);
   }
 }
+// b[m] of lane group g holds element 4 g + m on entry, 4 m + g on return.
+__device__ __forceinline__ void transpose_groups(float (&b)[4]) {
+  auto swap32 = [](float& x, float& y) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    x = __uint_as_float(r[0]);
+    y = __uint_as_float(r[1]);
+  };
+  auto swap16 = [](float& x, float& y) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    x = __uint_as_float(r[0]);
+    y = __uint_as_float(r[1]);
+  };
+  swap32(b[0], b[2]);
+  swap32(b[1], b[3]);
+  swap16(b[0], b[1]);
+  swap16(b[2], b[3]);
+}
 
 // tanh |x| = E / (E + 2), E = exp(2|x|) - 1 = 2^n expm1(r) + (2^n - 1) with 2|x| =
-// n ln 2 + r, |r| <= ln 2 / 2, expm1 from its Taylor series to r^11 (the next
-// term is 2e-13 of it) and the quotient from the reciprocal with two Newton
-// steps: good to 1e-12 relative down to x = 0, so its FP32 rounding is the
-// library tanh's, at about a third of the FP64 instructions.  1 from |x| = 20 on.
+// n ln 2 + r, |r| <= ln 2 / 2, expm1 from its Taylor series to r^14 (the next
+// term is below 2^-54 of it) and the quotient from the reciprocal with two Newton
+// steps: a few FP64 roundings from the true value down to x = 0, so its FP32
+// rounding is the library tanh's, at about a third of the FP64 instructions.  1
+// from |x| = 20 on.
 __device__ __forceinline__ double tanh_for_f32(double x) {
   double y = 2.0 * fabs(x);
   y = y > 40.0 ? 40.0 : y;   // (a NaN stays)
   const double n = rint(y * 1.4426950408889634);
   const double r = fma(n, -1.9082149292705877e-10, fma(n, -0.69314718036912381, y));   // ln 2 in two parts
-  double q = 1.0 / 39916800.0;
+  double q = 1.0 / 87178291200.0;   // 1/14!, down to 1/1!
+  q = fma(q, r, 1.0 / 6227020800.0);
+  q = fma(q, r, 1.0 / 479001600.0);
+  q = fma(q, r, 1.0 / 39916800.0);
   q = fma(q, r, 1.0 / 3628800.0);
   q = fma(q, r, 1.0 / 362880.0);
   q = fma(q, r, 1.0 / 40320.0);
@@ -496,7 +508,8 @@ __device__ __forceinline__ double tanh_for_f32(double x) {
   double c = __builtin_amdgcn_rcp(d);
   c = fma(fma(-d, c, 1.0), c, c);
   c = fma(fma(-d, c, 1.0), c, c);
-  return copysign(E * c, x);
+  const double t = E * c;
+  return copysign(fma(fma(-d, t, E), c, t), x);
 }
 
 // masked softmax of one row of logits
@@ -537,10 +550,10 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_fwd(int nrows, const float*
     f4 acc[RT] = {};
     // layer 0's 40 rows of W_aug are one sum; with 128 inputs the bias joins in FP64
     constexpr int K = I % 16 == 0 ? I : I + 1;
-    mlp_strip<RT, K, true>(act[l & 1], acc, [&](int k0, float (&b)[4]) {
+    mlp_strip<RT, K>(act[l & 1], acc, [&](int k0, float (&b)[4]) {
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
-        const int k = k0 + 4 * m;
+        const int k = k0 + 4 * m + kr;
         b[m] = K % 16 == 0 || k < K ? W[(long)(K % 16 == 0 || k < K ? k : 0) * kNhid] : 0.f;
       }
     });
@@ -563,9 +576,9 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_fwd(int nrows, const float*
   if (wave < RT) {   // logits: one wave per 16 rows, columns past the last unused
     const float* W = theta + layer_off(3) + (xc < kNout ? xc : 0);
     f4 acc[1] = {};
-    mlp_strip<1, kNhid, true>(act[1] + 16 * wave * kActLd, acc, [&](int k0, float (&b)[4]) {
+    mlp_strip<1, kNhid>(act[1] + 16 * wave * kActLd, acc, [&](int k0, float (&b)[4]) {
 #pragma unroll
-      for (int m = 0; m < 4; ++m) b[m] = W[(long)(k0 + 4 * m) * kNout];
+      for (int m = 0; m < 4; ++m) b[m] = W[(long)(k0 + 4 * m + kr) * kNout];
     });
     const double bias = W[(long)kNhid * kNout];
 #pragma unroll
@@ -637,14 +650,15 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_bwd(int nrows, const float*
     const int col = 16 * wave + xc;   // i
     const float* W = theta + layer_off(l) + (long)col * O;
     f4 acc[RT] = {};
-    mlp_strip<RT, O, false>(act[(3 - l) & 1], acc, [&](int k0, float (&b)[4]) {
+    mlp_strip<RT, O>(act[(3 - l) & 1], acc, [&](int k0, float (&b)[4]) {
       if constexpr (O % 16 == 0) {
-        const f4u w = *(const f4u*)(W + k0);
+        const f4u w = *(const f4u*)(W + k0 + 4 * kr);
 #pragma unroll
         for (int m = 0; m < 4; ++m) b[m] = w[m];
+        transpose_groups(b);
       } else {
 #pragma unroll
-        for (int m = 0; m < 4; ++m) b[m] = k0 + m < O ? W[k0 + m < O ? k0 + m : 0] : 0.f;
+        for (int m = 0; m < 4; ++m) b[m] = k0 + 4 * m + kr < O ? W[k0 + 4 * m + kr] : 0.f;
       }
     });
     float* y = act[(4 - l) & 1];
@@ -673,8 +687,9 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_bwd(int nrows, const float*
 // [s chunk, (s+1) chunk) of layer l into part[s], eight waves of TM x TN
 // fragments (WN waves along o) whose operands come straight from memory: a
 // fragment is 16 consecutive floats of four rows, and the fragments of a wave
-// feed TM TN MFMAs per four rows, so nothing is staged.  The bias row is the
-// sum of the dY fragments, in FP64, by the waves of the first strip of i.
+// feed TM TN MFMAs per four rows, so nothing is staged.  The bias row is a row
+// of ones among x's: row 39 of layer 0's last fragment, else a fragment of its
+// own, one column fragment of it to each strip of i.
 struct WgradArgs {
   int nrows, chunk;
   const float *X, *H, *dZ, *dA[3];
@@ -692,7 +707,10 @@ __device__ __forceinline__ void wgrad_layer(const WgradArgs& a) {
   const int k0 = blockIdx.x * a.chunk, k1 = min(a.nrows, k0 + a.chunk);
   f4 s[TM][TN] = {};
   d4 v[TM][TN] = {};
-  double bias[TN] = {};
+  f4 sb = {};   // bias, column fragment (strip of i) of this wave
+  d4 vb = {};
+  constexpr bool kOwnBias = I % 16 == 0;
+  const int jb = wave / WN;
   int ic[TM], oc[TN];   // fragment columns, clamped: those past the end are never stored
 #pragma unroll
   for (int i = 0; i < TM; ++i) ic[i] = min(i0 + 16 * i + xc, I - 1);
@@ -716,11 +734,12 @@ __device__ __forceinline__ void wgrad_layer(const WgradArgs& a) {
     for (int m = 0; m < 4; ++m) {
       const bool ok = k + 4 * m + kr < k1;
 #pragma unroll
-      for (int i = 0; i < TM; ++i) x4[m][i] = ok ? x4[m][i] : 0.f;
+      for (int i = 0; i < TM; ++i)
+        x4[m][i] = !ok ? 0.f : !kOwnBias && i0 + 16 * i + xc == I ? 1.f : x4[m][i];
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         y4[m][j] = ok ? y4[m][j] : 0.f;
-        if (i0 == 0) bias[j] += (double)y4[m][j];
+        if (kOwnBias && j == jb) sb = __builtin_amdgcn_mfma_f32_16x16x4f32(1.f, y4[m][j], sb, 0, 0, 0);
       }
 #pragma unroll
       for (int i = 0; i < TM; ++i)
@@ -737,6 +756,9 @@ __device__ __forceinline__ void wgrad_layer(const WgradArgs& a) {
           for (int r = 0; r < 4; ++r) v[i][j][r] += (double)s[i][j][r];
           s[i][j] = f4{0.f, 0.f, 0.f, 0.f};
         }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) vb[r] += (double)sb[r];
+      sb = f4{0.f, 0.f, 0.f, 0.f};
     }
   };
   fetch(k0, av, bv);
@@ -759,17 +781,9 @@ __device__ __forceinline__ void wgrad_layer(const WgradArgs& a) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int ii = i0 + 16 * i + 4 * kr + r, oo = o0 + 16 * j + xc;
-        if (ii < I && oo < O) put(ii, oo, v[i][j][r]);
+        if (ii < I + (kOwnBias ? 0 : 1) && oo < O) put(ii, oo, v[i][j][r]);
       }
-  if (i0 == 0) {
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {   // the four rows of each step sit in the four lane groups
-      double b = bias[j];
-      b += __shfl_xor(b, 16, 64);
-      b += __shfl_xor(b, 32, 64);
-      if (kr == 0 && o0 + 16 * j + xc < O) put(I, o0 + 16 * j + xc, b);
-    }
-  }
+  if (kOwnBias && jb < TN && kr == 0 && o0 + 16 * jb + xc < O) put(I, o0 + 16 * jb + xc, vb[0]);   // every row alike
 }
 __global__ __launch_bounds__(kMlpThreads) void k_mlp_wgrad(WgradArgs a) {
   switch (a.first + (int)blockIdx.y) {   // layer 0 last, on its own where the arena is capped
@@ -906,9 +920,9 @@ long mlp_n_params() { return layer_off(4); }
 
 // Rows per workgroup of the fused passes: 32 halve the weight reads, 16 fill the
 // chip sooner and halve a workgroup's chain.  Forward + backward, 16 against 32
-// rows: 70.4 / 72.9 us at 8,208 rows, 78.7 / 84.5 at 12,000, 102 / 93 at 16,000
-// (119 both ways at 19,553); the line lies between, at 3.5 16-row workgroups per CU.
-static bool mlp_wide(int nrows) { return nrows > 256 * 56; }
+// rows: 50.8 / 60.8 us at 4,096 rows, 83.4 / 89.1 at 12,000, 105 / 93.6 at 14,336,
+// 130 / 127 at 19,553; the line lies at three 16-row workgroups per CU.
+static bool mlp_wide(int nrows) { return nrows > 256 * 48; }
 
 rif_status op_mlp_forward(rif_ctx* c, int nrows, const float* X, const float* M, const float* theta, float* H,
                           float* Z, float* Pn) {
@@ -927,9 +941,9 @@ rif_status op_mlp_backward(rif_ctx* c, int nrows, const float* X, const float* M
                            double* loss) {
   const bool wide = mlp_wide(nrows);
   const int nl = cdiv_i(nrows, wide ? 32 : 16), n = (int)mlp_n_params();
-  // splits of the weight gradients: about 100 workgroups for each wide layer
-  // (two of them fill the chip), at least one 128-row FP32 chunk each
-  int chunk = std::max(128, 4 * cdiv_i(nrows, 4 * 100)), splits = cdiv_i(nrows, chunk);
+  // splits of the weight gradients: whole 128-row FP32 sums, at most about 160
+  // workgroups for each wide layer (two of them fill the chip)
+  int chunk = 128 * cdiv_i(nrows, 128 * 160), splits = cdiv_i(nrows, chunk);
   Carve cv;
   const size_t o_lp = cv.take<double>((size_t)nl);
   const size_t o_dz = cv.take<float>((size_t)nrows * kNout);

@@ -15,7 +15,7 @@ from oracle import mlp as omlp
 
 pytestmark = pytest.mark.gpu
 LAYER = 129 * 2.0 ** -24
-SWITCH = 256 * 56   # rows from which a workgroup takes 32
+SWITCH = 256 * 48   # rows from which a workgroup takes 32
 
 
 @pytest.mark.parametrize("rows,limit", [(1, 0), (15, 0), (16, 0), (17, 0), (127, 0), (129, 0), (260, 0), (SWITCH, 0), (SWITCH + 1, 0),
