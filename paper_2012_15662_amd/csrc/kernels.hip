@@ -104,17 +104,21 @@ inline bool strip_fits(int nb, int nmo, int nw) { return nb >= 2 && nw >= 2 && n
 // b symmetric) into the mode's pieces, rows zero-filled from n_bf up to ld;
 // FP32 mode: a float copy.
 struct BSplitArgs { const double* b; long nr; int nb, ld; void* out; long ps; };
-// dma: FP64 128 x 128 tiles stage b_half and C_Omega by direct global -> LDS
-// loads (even n_bf and n_mo, 16-byte aligned b_half and C).
-struct MoArgs { int nb, na, nw, nmo; const void* bh; const double* C; void* bmo; double* d; Planes Cs; int dma; };
+struct MoArgs { int nb, na, nw, nmo; const void* bh; const double* C; void* bmo; double* d; Planes Cs; };
+// (and 16 rows of b_half, n_aux n_bf apart, at 32-bit offsets).  From 192 tiles on:
+// below, both triangles of b_mo stay products of their own, as small molecules'
+// orbital loops have them.  Such a loop starts from a F^lambda whose block outside
+// Omega is zero, so part of its first eigenvectors is set by the last bits of
+// what it is given; mirrored elements would change them.  The launch takes 9 us
+// there (7 with strips), of a few hundred for an inner iteration.
+inline bool mo_strip_fits(int nb, int na, int nmo, int nw);
 // Bj: b pre-split for J^q (piece planes with rows r = mu*n_bf + nu and
 // k = l contiguous), or unset (split on load).
 struct JaoArgs { int nb, na, nw; const double* b; const double* d; void* Jn; Planes Ds; Planes Bj; };
 // Pre-split of X (element (x, k) at X[k*sk + x]) into NPC bf16 planes
 // out[s*ps + x*ld + k], zero from k = K up to ld.
 struct PSplitArgs { const double* X; long sk; int nx, K, ld; unsigned short* out; long ps; };
-// dma: FP64 b_half staged by direct global -> LDS loads (rows 16-byte aligned).
-struct KaoArgs { int nb, na, nw; const void* bh; void* Kn; int dma; };
+struct KaoArgs { int nb, na, nw; const void* bh; void* Kn; };
 // Split over k: out + s*ostride receives the partial product over
 // k in [s*kc, min(K, (s+1)*kc)), s < ksplit.
 struct GemmArgs {
@@ -361,52 +365,196 @@ inline bool b_presplit(const HalfArgs& a) {
 
 // MO transform: rows s = l*n_omega + p, bmo[s][q] = sum_nu bh[p][l][nu] C[nu][q];
 // the FP64 diagonal d[l][p] = bmo[l][p][p] comes from the same epilogue.
+// FP64: b_mo is symmetric in (p, q), so only q <= p is computed.  A tile's 128
+// columns are 16 p (block P) of 8 consecutive l, and its rows the q up to that
+// block: every wave has the same fragments to do, and n_omega = 120 takes 36 of
+// 64 fragment rows.  A: C_Omega ([k][q], rows padded by 8 columns); B: b_half
+// rows ([x][k], k contiguous, 128 bytes a row and slice with its eight 16-byte
+// chunks swizzled, chunk c at slot c ^ (x % 8)).  Lane group kr of step (h, m)
+// takes k = 2 (kr + 4 h) + m: one 16-byte read of B per step pair, and A rows two
+// apart, which the padding puts on different banks.  An odd n_bf is a row of
+// n_bf + 1 positions (pair_column): position n_bf - 1 repeats n_bf - 2 and meets
+// a zero row of C.  Tiles: the largest blocks first, every group of l of one
+// block after another, so the short ones fill the end of the launch (block after
+// block per group of l left a third of the CUs idle for the last 50 us of 190).
+// Stores: b_mo[l][q][p] in 128-byte pieces, b_mo[l][p][q] in 32-byte ones that
+// meet in L2 (a tile writes a row's whole beginning).
+// Bound by HBM and matrix cores about equally (n_omega 120: 474 MB and 6.8e9
+// padded flops).  Per launch, against every (p, q) in 128 x 128 tiles before: 210
+// -> 157 us at the cyclohexane-like size, 1788 -> 895 at the cyclodecane-like, 153
+// -> 90 at n_bf 288 / n_omega 100.
+constexpr int kMoL = 8;   // l per tile
+template <int TM_>
+struct MoStrip {
+  static constexpr int TM = TM_, BM = 16 * TM, NW = 8, LDA = BM + 8;
+  static constexpr int WVM = TM % 2 == 0 ? 2 : 1, WVN = NW / WVM, FM = TM / WVM, FN = kMoL / WVN;
+  static constexpr int S = TM <= 4 ? 3 : 2;
+  static constexpr int NIA = 2 * TM + 1, NIB = 16, NI = NIA + NIB, NU = (NI + NW - 1) / NW;
+  static constexpr int ST = NI * 1024;
+};
+template <int TM = 8>
+constexpr int mo_strip_smem() {
+  constexpr int here = MoStrip<TM>::S * MoStrip<TM>::ST;
+  if constexpr (TM == 1) return here;
+  else return here > mo_strip_smem<TM - 1>() ? here : mo_strip_smem<TM - 1>();
+}
+struct MoCfg {
+  static constexpr bool kMo = true;
+  static constexpr int NT = 512, BM = 128, BN = 128;
+};
+__host__ __device__ inline int mo_blocks(int nw) {   // tiles per group of l
+  int n = 0;
+  for (int P = 0; P < cdiv(nw, 16); ++P) n += strip_tiles(16 * (P + 1));
+  return n;
+}
+inline bool mo_strip_fits(int nb, int na, int nmo, int nw) {
+  return strip_fits(nb, nmo, nw) && (long)na * nb < (1L << 25) && (long)mo_blocks(nw) * cdiv(na, kMoL) >= 192;
+}
 template <int P, class Cfg>
 __host__ __device__ inline long mo_tiles(const MoArgs& a) {
-  return (long)cdiv(a.nw, Cfg::BN) * cdiv((long)a.na * a.nw, Cfg::BM);
+  if constexpr (std::is_same<Cfg, MoCfg>::value) return (long)mo_blocks(a.nw) * cdiv(a.na, kMoL);
+  else return (long)cdiv(a.nw, Cfg::BN) * cdiv((long)a.na * a.nw, Cfg::BM);
 }
-// FP64 slice of MFMAs with A in the swizzled [x][k] layout of KcDma64 and B in
-// the engine's padded [k][x] layout.  Lane group kr of MFMA step (h, m) takes
-// k = 2(kr + 4h) + m, so each lane reads its two A values of a step pair as
-// one 16-byte chunk (eight lanes of one k group read eight rows' chunks in
-// distinct bank slots); B is read at the same k.  Every k of the slice is
-// summed once per slice, in a fixed order.
-template <class Cfg>
-__device__ __forceinline__ void mma_xk_f64(const lds_char* SA, const lds_char* SB,
-                                           typename EngF64::template Acc<Cfg>& acc) {
-  using E = EngF64;
-  const lds_f64* As = (const lds_f64*)SA;
-  const lds_f64* Bs = (const lds_f64*)SB;
-  const int lane = threadIdx.x & 63, kr = lane >> 4, xc = lane & 15;
-  int wm0, wn0;
-  wave_origin(Cfg::WAVES_N, Cfg::WM, Cfg::WN, wm0, wn0);
+__device__ __forceinline__ void mo_strip(const MoArgs& a, long t, char* smem_generic) {
+  const int nb = a.nb, na = a.na, nw = a.nw, nmo = a.nmo, ng = cdiv(na, kMoL), K = pair_len(nb);
+  const int l0 = (int)(t % ng) * kMoL;
+  int r = (int)(t / ng), P = cdiv(nw, 16) - 1;
+  while (r >= strip_tiles(16 * (P + 1))) r -= strip_tiles(16 * (P + 1)), --P;
+  const int tm = strip_frags(16 * (P + 1)), q0 = r * 16 * tm;
+  const long AB = (long)na * nb;
+  const double* bh = (const double*)a.bh + 16L * P * AB + (long)l0 * nb;   // p = 16 P, l = l0
+  double* bmo = (double*)a.bmo;
+  lds_char* sm = (lds_char*)smem_generic;
+  with_frags(tm, [&](auto frags) {
+    using L = MoStrip<decltype(frags)::value>;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, kr = lane >> 4, xc = lane & 15;
+    unsigned off[L::NU];
+    const char* base[L::NU];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int c = kr + 4 * h;   // chunk: k = 2c, 2c + 1
-    double a0[Cfg::TM], a1[Cfg::TM];
+    for (int i = 0; i < L::NU; ++i) {
+      const int u = w + i * L::NW;
+      const bool isA = u < L::NIA;
+      if (isA) {
+        const int v = u * 64 + lane, k = v / (L::LDA / 2), x = 2 * (v % (L::LDA / 2));
+        off[i] = 8u * (unsigned)(k * (long)nmo + (k < 16 && x < L::BM && q0 + x < nw ? pair_start(q0 + x, nw) : 0));
+        if (k >= 16) off[i] = 0;   // the padded stage's last units
+      } else {
+        const int x = (u - L::NIA) * 8 + lane / 8, c = (lane % 8) ^ (x & 7);
+        const int p = x % 16, l = x / 16;
+        off[i] = 8u * (unsigned)((16 * P + p < nw ? p * AB : 0) + (l0 + l < na ? (long)l * nb : 0) + 2 * c);
+      }
+      base[i] = (const char*)(isA ? a.C : bh);
+    }
+    auto have = [&](int i) { return L::NI % L::NW == 0 || i + 1 < L::NU || w + i * L::NW < L::NI; };
+    auto issue = [&](int kt, lds_char* st) {
+      const int left = K - 16 * kt;
+      // a slice with every k of the row, none of them an odd row's last pair
+      if (left > 16 || (left == 16 && !(nb & 1))) {
 #pragma unroll
-    for (int i = 0; i < Cfg::TM; ++i) {
-      const int x = wm0 + i * 16 + xc;
-      const lds_f64* q = As + x * 16 + 2 * (c ^ (x & 7));
-      a0[i] = q[0];
-      a1[i] = q[1];
+        for (int i = 0; i < L::NU; ++i)
+          if (have(i)) {
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(base[i] + off[i]),
+                                             (__attribute__((address_space(3))) void*)(st + (w + i * L::NW) * 1024),
+                                             16, 0, 0);
+            base[i] += w + i * L::NW < L::NIA ? 128L * nmo : 128L;
+          }
+      } else {
+#pragma unroll
+        for (int i = 0; i < L::NU; ++i)
+          if (have(i)) {
+            const int u = w + i * L::NW;
+            const char* p = (const char*)(kDmaZeros + 2 * lane);
+            if (u < L::NIA) {
+              const int k = (u * 64 + lane) / (L::LDA / 2), kc = k < 16 ? pair_column(16 * kt + k, nb) : -1;
+              if (kc >= 0) p = base[i] + off[i] + 8L * nmo * (kc - 16 * kt - k);
+            } else {
+              const int x = (u - L::NIA) * 8 + lane / 8, k = 2 * ((lane % 8) ^ (x & 7));
+              if (k < left) p = base[i] + off[i] + 8L * (pair_start(16 * kt + k, nb) - 16 * kt - k);
+            }
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p,
+                                             (__attribute__((address_space(3))) void*)(st + u * 1024), 16, 0, 0);
+          }
+      }
+    };
+    d4 acc[L::FM][L::FN];
+#pragma unroll
+    for (int i = 0; i < L::FM; ++i)
+#pragma unroll
+      for (int j = 0; j < L::FN; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+    const int wm = (w / L::WVN) * L::FM * 16, wl = (w % L::WVN) * L::FN;   // first row, first l of this wave
+    const int nk = cdiv(K, 16);
+#pragma unroll
+    for (int j = 0; j < L::S - 1; ++j)
+      if (j < nk) issue(j, sm + j * L::ST);
+    auto slice = [&](int kt, int sg) {
+      if (L::S == 3 && kt + 1 < nk) {
+        if (L::NI % L::NW == 0 || w + (L::NU - 1) * L::NW < L::NI) __builtin_amdgcn_s_waitcnt(L::NU | (7 << 4) | (15 << 8));
+        else __builtin_amdgcn_s_waitcnt((L::NU - 1) | (7 << 4) | (15 << 8));
+      } else {
+        __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));
+      }
+      strip_barrier();
+      if (kt + L::S - 1 < nk) issue(kt + L::S - 1, sm + ((sg + L::S - 1) % L::S) * L::ST);
+      const lds_f64* As = (const lds_f64*)(sm + sg * L::ST);
+      const lds_f64* Bs = (const lds_f64*)(sm + sg * L::ST + L::NIA * 1024);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int c = kr + 4 * h;
+        double b[L::FN][2];
+#pragma unroll
+        for (int j = 0; j < L::FN; ++j) {
+          const lds_f64* q = Bs + ((wl + j) * 16 + xc) * 16 + 2 * (c ^ (xc & 7));
+          b[j][0] = q[0];
+          b[j][1] = q[1];
+        }
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          double av[L::FM];
+#pragma unroll
+          for (int i = 0; i < L::FM; ++i) av[i] = As[(2 * c + m) * L::LDA + wm + 16 * i + xc];
+#pragma unroll
+          for (int i = 0; i < L::FM; ++i)
+#pragma unroll
+            for (int j = 0; j < L::FN; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i], b[j][m], acc[i][j], 0, 0, 0);
+        }
+      }
+    };
+    int kt = 0;
+    for (; kt + L::S <= nk; kt += L::S) {
+#pragma unroll
+      for (int sg = 0; sg < L::S; ++sg) slice(kt + sg, sg);
     }
 #pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      double b[Cfg::TN];
+    for (int sg = 0; sg < L::S - 1; ++sg)
+      if (kt + sg < nk) slice(kt + sg, sg);
+    const int p = 16 * P + xc;
 #pragma unroll
-      for (int j = 0; j < Cfg::TN; ++j) b[j] = Bs[(2 * c + m) * (Cfg::BN + E::PAD) + wn0 + j * 16 + xc];
+    for (int j = 0; j < L::FN; ++j) {
+      const long l = l0 + wl + j;
+      if (l < na && p < nw) {
+        double* o = bmo + l * nw * nw;
 #pragma unroll
-      for (int i = 0; i < Cfg::TM; ++i)
+        for (int i = 0; i < L::FM; ++i)
 #pragma unroll
-        for (int j = 0; j < Cfg::TN; ++j)
-          acc.v[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(m ? a1[i] : a0[i], b[j], acc.v[i][j], 0, 0, 0);
+          for (int e = 0; e < 4; ++e) {
+            const int q = pair_column(q0 + wm + 16 * i + kr + 4 * e, nw);
+            const double v = acc[i][j][e];
+            if (q >= 0 && q <= p) {
+              o[(long)q * nw + p] = v;
+              if (q < p) o[(long)p * nw + q] = v;
+              else a.d[l * nw + p] = v;
+            }
+          }
+      }
     }
-  }
+    strip_barrier();   // a grouped workgroup's next tile stages into this LDS
+  });
 }
 
 template <int P, class Cfg>
-__device__ void mo_tile(const MoArgs& a, long t, char* smem) {
+__device__ void mo_tile_with(const MoArgs& a, long t, char* smem) {
   using E = typename EngineOf<P>::type;
   const int nb = a.nb, na = a.na, nw = a.nw;
   const int nqt = cdiv(nw, Cfg::BN);
@@ -417,32 +565,6 @@ __device__ void mo_tile(const MoArgs& a, long t, char* smem) {
   const IOT<P>* bh = (const IOT<P>*)a.bh;
   IOT<P>* bmo = (IOT<P>*)a.bmo;
   double* d = a.d;
-  if constexpr (P == kF64 && Cfg::BM == 128 && Cfg::BN == 128) {
-    if (a.dma) {   // b_half rows into the swizzled [x][k] layout, C_Omega into [k][x], both by direct loads
-      KcDma64<Cfg::NT, E::BK, Cfg::BM> la;
-      la.init([&](int x) -> const double* {
-        const long s = s0 + x;
-        if (s >= ns) return nullptr;
-        const long l = s / nw, p = s - l * nw;
-        return (const double*)bh + p * AB + l * nb;
-      }, (const double*)bh, nb);
-      XcDma64<Cfg::NT, E::BK, E::PAD> lb;
-      lb.init(a.C, a.nmo, nb, [&](int x, long& o) { o = q0 + x; return q0 + x < nw; });
-      typename E::template Acc<Cfg> acc;
-      gemm_mainloop_dma_with<E, Cfg, 2>(la, lb, cdiv(nb, E::BK), acc, smem, false,
-                                        [&](const lds_char* SA, const lds_char* SB,
-                                            typename E::template Acc<Cfg>& c) { mma_xk_f64<Cfg>(SA, SB, c); });
-      acc.for_each([&](int m, int n, double v) {
-        const long s = s0 + m;
-        const int q = q0 + n;
-        if (s < ns && q < nw) {
-          bmo[s * nw + q] = v;
-          if (s % nw == q) d[s] = v;
-        }
-      });
-      return;
-    }
-  }
   KCS<P, IOT<P>, Cfg::BM, Cfg::NT> la;
   la.init([&](int x) -> const IOT<P>* {
     const long s = s0 + x;
@@ -466,6 +588,12 @@ __device__ void mo_tile(const MoArgs& a, long t, char* smem) {
       if (s % nw == q) d[s] = v;
     }
   });
+}
+
+template <int P, class Cfg>
+__device__ __forceinline__ void mo_tile(const MoArgs& a, long t, char* smem) {
+  if constexpr (std::is_same<Cfg, MoCfg>::value) mo_strip(a, t, smem);
+  else mo_tile_with<P, Cfg>(a, t, smem);
 }
 
 // First block column of block row bi that holds an element with nu >= mu.
@@ -753,13 +881,181 @@ __device__ void jaop_tile(const JaoArgs& a, long, char* smem) { jaop_persistent<
 // FP64/FP32, a block on the diagonal (fragments I <= J only) or on the ragged
 // edge trims each wave's fragment rows to the live ones under a balanced wave
 // plan, and a diagonal block stages its single operand panel once.
-template <int P, class Cfg>
-__host__ __device__ inline long kao_tiles(const KaoArgs& a) {
-  const long nbk = cdiv(a.nb, Cfg::BM);
-  return nbk * (nbk + 1) / 2 * a.nw;
+// FP64 on strip tiles.  The 16-column fragments of a row are cut into nearly
+// equal blocks of at most NW; a tile is a pair of blocks bi <= bj, each wave one
+// fragment column of bj against all rows of bi.  In a tile on the diagonal
+// (one staged panel) the wave of column c needs c + 1 fragment rows: columns c
+// and cw-1-c go to waves of one SIMD, so each SIMD has the same to do.  A wave
+// without a column idles, and which one is rotated over the tiles.
+// Order: an XCD takes every eighth q, its off-diagonal tiles first and the
+// half-size diagonal ones last, which evens out the end of the launch.
+// The mirrored half is transposed in LDS, 16 x 16 per wave, so that both halves
+// store whole 128-byte pieces.  Per launch, against 64 x 64 tiles of
+// 64-bit-addressed direct loads before: 2.40 -> 2.17 ms at the cyclodecane-like
+// size, 54 -> 51 us at n_bf 201 / n_omega 48 (odd: register-staged before), 330 us
+// either way at the cyclohexane-like size, where the tiles' last round leaves a
+// fifth of the launch half empty.
+template <class Cfg, int TM_, bool kDiag>
+struct KaoStrip {
+  static constexpr int TM = TM_, BM = 16 * TM, BN = Cfg::BN, NW = Cfg::NWAVES;
+  static constexpr int S = TM <= 4 || kDiag ? 3 : 2;
+  static constexpr int NIA = kDiag ? 0 : BM / 8, NIB = BN / 8, NI = NIA + NIB, NU = (NI + NW - 1) / NW;
+  static constexpr int ST = NI * 1024;
+};
+struct KaoBlocks {   // block b: fragments [start(b), start(b) + size(b))
+  int nf, nc;
+  __host__ __device__ KaoBlocks(int nb, int nw) : nf(cdiv(pair_len(nb), 16)), nc(cdiv(nf, nw)) {}
+  __host__ __device__ int size(int b) const { return nf / nc + (b < nf % nc ? 1 : 0); }
+  __host__ __device__ int start(int b) const { return b * (nf / nc) + (b < nf % nc ? b : nf % nc); }
+  __host__ __device__ int nfull() const { return nc * (nc - 1) / 2; }
+  __host__ __device__ int tiles() const { return nc + nfull(); }
+};
+// 128-column tiles read half the operand bytes per product of 64-column ones, but
+// their 16 units of work (fragment rows per SIMD and slice) are too coarse for a
+// launch of few of them per CU: they pay from about 60 units per CU.  us, 128 /
+// 64 columns: 338 / 334 at n_bf 348, n_omega 120 (30 units), 612 / 528 at 420, 120
+// (44), 1004 / 1071 at 480, 170 (77), 2124 / 2265 at 580, 200 (137); 80 / 51 at
+// 201, 48.
+static int kao_default(int nb, int nw) {
+  const int nf = KaoBlocks(nb, 8).nf;
+  return nw * (nf * (nf + 1) / 2) / 4.0 / 256.0 >= 60.0 ? 0 : 1;
 }
 template <int P, class Cfg>
-__device__ void kao_tile(const KaoArgs& a, long t, char* smem) {
+__host__ __device__ inline long kao_tiles(const KaoArgs& a) {
+  if constexpr (is_strip<Cfg>::value) {
+    return 8L * cdiv(a.nw, 8) * KaoBlocks(a.nb, Cfg::NWAVES).tiles();
+  } else {
+    const long nbk = cdiv(a.nb, Cfg::BM);
+    return nbk * (nbk + 1) / 2 * a.nw;
+  }
+}
+template <class Cfg, int TM, bool kDiag>
+__device__ __forceinline__ void kao_strip_tile(const KaoArgs& a, int q, int f0, int g0, int cw, int rot, char* smem) {
+  using L = KaoStrip<Cfg, TM, kDiag>;
+  const int nb = a.nb, na = a.na, ne = pair_len(nb);
+  const double* X = (const double*)a.bh + (long)q * na * nb;
+  const int m0 = 16 * f0, n0 = 16 * g0;   // first row and column (positions)
+  StripStage<L> st;
+  st.init(X, nb, [&](int x) -> long { return m0 + x < ne ? pair_start(m0 + x, nb) : 0; },
+          X, nb, [&](int x) -> long { return n0 + x < ne ? pair_start(n0 + x, nb) : 0; });
+  const int w = st.w, lane = threadIdx.x & 63, kr = lane >> 4, xc = lane & 15;
+  lds_char* sm = (lds_char*)smem;
+  // this wave's column fragment and its live rows
+  int c, ni;
+  if constexpr (kDiag && L::NW == 8) {
+    c = w < 4 ? w : cw - 1 - (w - 4);
+    ni = w < 4 ? (c < cw ? c + 1 : 0) : (c > 3 ? c + 1 : 0);
+  } else {
+    c = (w + rot) & (L::NW - 1);
+    ni = c < cw ? (kDiag ? c + 1 : TM) : 0;
+  }
+  d4 acc[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) acc[i] = d4{0.0, 0.0, 0.0, 0.0};
+  const int nk = cdiv(na, 16);
+  auto loop = [&](auto rows) {
+    constexpr int NI = decltype(rows)::value;
+#pragma unroll
+    for (int j = 0; j < L::S - 1; ++j)
+      if (j < nk) st.issue(sm + j * L::ST, na - 16 * j);
+    constexpr bool swA = kDiag || TM % 2 == 0;
+    constexpr int LDA = kDiag ? L::BN : L::BM;
+    const int sa = swA && (kr & 1) ? 16 : 0, sb = (kr & 1) ? 16 : 0;
+    const int ae = kr * LDA + xc + sa, ao = kr * LDA + xc - sa;
+    const int b0 = kr * L::BN + 16 * c + xc + ((c & 1) ? -sb : sb);
+    auto slice = [&](int kt, int s) {
+      if (L::S == 3 && kt + 1 < nk) {
+        if (L::NI % L::NW == 0 || w + (L::NU - 1) * L::NW < L::NI) __builtin_amdgcn_s_waitcnt(L::NU | (7 << 4) | (15 << 8));
+        else __builtin_amdgcn_s_waitcnt((L::NU - 1) | (7 << 4) | (15 << 8));
+      } else {
+        __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));
+      }
+      strip_barrier();
+      if (kt + L::S - 1 < nk) st.issue(sm + ((s + L::S - 1) % L::S) * L::ST, na - 16 * (kt + L::S - 1));
+      const lds_f64* As = (const lds_f64*)(sm + s * L::ST);
+      const lds_f64* Bs = As + (kDiag ? 0 : 16 * L::BM);
+      if constexpr (NI > 0) {
+#pragma unroll
+        for (int kk = 0; kk < 16; kk += 4) {
+          double av[NI];
+          const double b = Bs[kk * L::BN + b0];
+#pragma unroll
+          for (int i = 0; i < NI; ++i) av[i] = As[kk * LDA + ((i & 1) ? ao : ae) + 16 * i];
+#pragma unroll
+          for (int i = 0; i < NI; ++i) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i], b, acc[i], 0, 0, 0);
+        }
+      }
+    };
+    int kt = 0;
+    for (; kt + L::S <= nk; kt += L::S) {
+#pragma unroll
+      for (int s = 0; s < L::S; ++s) slice(kt + s, s);
+    }
+#pragma unroll
+    for (int s = 0; s < L::S - 1; ++s)
+      if (kt + s < nk) slice(kt + s, s);
+  };
+  if constexpr (kDiag) {
+    with_rows<TM>(ni, loop);
+  } else {
+    if (ni) loop(std::integral_constant<int, TM>());
+    else loop(std::integral_constant<int, 0>());
+  }
+  strip_barrier();
+  double* K = (double*)a.Kn + (long)q * nb * nb;
+  lds_f64* T = (lds_f64*)sm + w * (16 * 17);   // this wave's transpose
+  const int nu = pair_column(n0 + 16 * c + xc, nb);
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    if (i >= ni) continue;   // (wave-uniform)
+    const int mb = m0 + 16 * i;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int mu = pair_column(mb + kr + 4 * e, nb);
+      if (mu >= 0 && mu <= nu) K[(long)mu * nb + nu] = acc[i][e];
+      T[xc * 17 + kr + 4 * e] = acc[i][e];
+    }
+    __builtin_amdgcn_wave_barrier();   // one wave's LDS operations complete in order
+    const int mu = pair_column(mb + xc, nb);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = kr + 4 * e, nuc = pair_column(n0 + 16 * c + r, nb);
+      if (mu >= 0 && mu < nuc) K[(long)nuc * nb + mu] = T[r * 17 + xc];
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  strip_barrier();   // a grouped workgroup's next tile stages into this LDS
+}
+template <class Cfg>
+constexpr int kao_strip_smem() { return strip_smem<Cfg>(); }   // (the diagonal's stages and the transposes fit it)
+template <class Cfg>
+__device__ __forceinline__ void kao_strip(const KaoArgs& a, long t, char* smem) {
+  static_assert(KaoStrip<Cfg, 8, true>::S * KaoStrip<Cfg, 8, true>::ST <= strip_smem<Cfg>() &&
+                Cfg::NWAVES * 16 * 17 * 8 <= strip_smem<Cfg>(), "LDS");
+  const KaoBlocks B(a.nb, Cfg::NWAVES);
+  const int nq = cdiv(a.nw, 8), nfull = B.nfull();
+  const int x = (int)(t % 8);
+  long k = t / 8;
+  const bool diag = k >= (long)nq * nfull;
+  if (diag) k -= (long)nq * nfull;
+  const int per = diag ? B.nc : nfull, q = x + 8 * (int)(k / per);
+  if (q >= a.nw) return;
+  int r = (int)(k % per), bi = 0, bj;
+  if (diag) {
+    bi = bj = r;
+  } else {
+    while (r >= B.nc - 1 - bi) r -= B.nc - 1 - bi, ++bi;
+    bj = bi + 1 + r;
+  }
+  const int f0 = B.start(bi), g0 = B.start(bj), cw = B.size(bj), rot = (int)k;
+  with_frags<Cfg::NWAVES>(B.size(bi), [&](auto frags) {
+    constexpr int TM = decltype(frags)::value;
+    if (diag) kao_strip_tile<Cfg, TM, true>(a, q, f0, g0, cw, rot, smem);
+    else kao_strip_tile<Cfg, TM, false>(a, q, f0, g0, cw, rot, smem);
+  });
+}
+template <int P, class Cfg>
+__device__ void kao_tile_with(const KaoArgs& a, long t, char* smem) {
   static_assert(Cfg::BM == Cfg::BN, "square blocks");
   using E = typename EngineOf<P>::type;
   const int nb = a.nb, na = a.na, nw = a.nw;
@@ -790,56 +1086,6 @@ __device__ void kao_tile(const KaoArgs& a, long t, char* smem) {
   constexpr int FB = Cfg::BM / 16;
   const int fim = min(FB, cdiv(nb - mu0, 16)), fjm = min(FB, cdiv(nb - nu0, 16));
   const bool diag = bi == bj;
-  if constexpr (P == kF64 && Cfg::BM == 64) {
-    if (a.dma) {   // unpadded rows, three stages (two slices in flight), three workgroups per CU
-      using E2 = EngF64T<16, 0>;
-      XcDma64<Cfg::NT, E2::BK, E2::PAD, 64> da, db;
-      da.init((const double*)X, nb, na, [&](int x, long& o) { o = mu0 + x; return mu0 + x < nb; });
-      db.init((const double*)X, nb, na, [&](int x, long& o) { o = nu0 + x; return nu0 + x < nb; });
-      typename E2::template Acc<Cfg> acc2;
-      if (!diag && fim == FB && fjm == FB) {
-        gemm_mainloop_dma<E2, Cfg, 3>(da, db, cdiv(na, E2::BK), acc2, smem);
-        acc2.for_each(store);
-        return;
-      }
-      const WavePlan w =
-          make_wave_plan<Cfg>([&](int I, int J) { return I < fim && J < fjm && (!diag || I <= J); });
-      with_rows<Cfg::TM>(w.ni, [&](auto rows) {
-        constexpr int NI = decltype(rows)::value;
-        gemm_mainloop_dma_with<E2, Cfg, 3>(da, db, cdiv(na, E2::BK), acc2, smem, diag,
-                                           [&](const lds_char* SA, const lds_char* SB,
-                                               typename E2::template Acc<Cfg>& c) {
-                                             E2::template mma_rows<Cfg, NI>(SA, SB, c, w);
-                                           });
-      });
-      acc2.for_each(w, store);
-      return;
-    }
-  }
-  if constexpr (P == kF64 && Cfg::BM == 128) {
-    if (a.dma) {   // b_half by direct global -> LDS loads; a diagonal block stages one panel
-      XcDma64<Cfg::NT, E::BK, E::PAD, Cfg::BM> da, db;
-      da.init((const double*)X, nb, na, [&](int x, long& o) { o = mu0 + x; return mu0 + x < nb; });
-      db.init((const double*)X, nb, na, [&](int x, long& o) { o = nu0 + x; return nu0 + x < nb; });
-      if (!diag && fim == FB && fjm == FB) {
-        gemm_mainloop_dma<E, Cfg, 2>(da, db, cdiv(na, E::BK), acc, smem);
-        acc.for_each(store);
-        return;
-      }
-      const WavePlan w =
-          make_wave_plan<Cfg>([&](int I, int J) { return I < fim && J < fjm && (!diag || I <= J); });
-      with_rows<Cfg::TM>(w.ni, [&](auto rows) {
-        constexpr int NI = decltype(rows)::value;
-        gemm_mainloop_dma_with<E, Cfg, 2>(da, db, cdiv(na, E::BK), acc, smem, diag,
-                                          [&](const lds_char* SA, const lds_char* SB,
-                                              typename E::template Acc<Cfg>& c) {
-                                            E::template mma_rows<Cfg, NI>(SA, SB, c, w);
-                                          });
-      });
-      acc.for_each(w, store);
-      return;
-    }
-  }
   // The split-BF16 engines (VALU-bound by operand splitting, and short of
   // registers for the extra loop copies) always compute whole blocks.
   constexpr bool kPlan = P == kF64 || P == kF32;
@@ -860,6 +1106,12 @@ __device__ void kao_tile(const KaoArgs& a, long t, char* smem) {
     });
     acc.for_each(w, store);
   }
+}
+
+template <int P, class Cfg>
+__device__ __forceinline__ void kao_tile(const KaoArgs& a, long t, char* smem) {
+  if constexpr (is_strip<Cfg>::value) kao_strip<Cfg>(a, t, smem);
+  else kao_tile_with<P, Cfg>(a, t, smem);
 }
 
 // FP64 GEMM out[m][n] = sum_k A[k][m] B[k][n], both operands x-contiguous;
@@ -1281,11 +1533,10 @@ __global__ __launch_bounds__(256) void k_bsplitj(BSplitJArgs a) {
 
 // MO J/K partial sums over a contiguous range of l (fixed split), then a
 // fixed-order reduction over the splits.  FP64 arithmetic in every mode.
-// Splits: enough for about 1024 workgroups, at least eight l each (one batch
-// of loads in flight; shorter ranges cost as much and leave more to add up).
+// Splits: enough for about 1024 workgroups.
 static int jk_splits(int na, int nw) {
   const long nx = cdiv((long)nw * nw, 256);
-  return (int)std::max(1L, std::min((long)cdiv(na, 8), (1024L + nx - 1) / nx));
+  return (int)std::max(1L, std::min((long)na, (1024L + nx - 1) / nx));
 }
 template <int P, class Cfg>
 __host__ __device__ inline long jkp_tiles(const JkArgs& a) { return (long)cdiv((long)a.nw * a.nw, 256) * a.nsplit; }
@@ -1311,44 +1562,60 @@ __device__ void jkp_tile(const JkArgs& a, long t, char*) {
   a.part[(2L * s + 1) * w2 + pq] = sk;
 }
 
-// A tile's 256 threads are 256 / SL elements times SL strided shares of the
-// splits, added in a fixed order through LDS.  A small n_omega has few
-// elements and many splits, and one thread per element walked them as a chain
-// of dependent loads (50 us at n_omega 10 and 192 splits, 68 us at 48 and 114,
-// the longest kernel of those builds; now 5 us); from few splits on the shares
-// would idle.
-__host__ __device__ inline int jkr_share(int nsplit) { return nsplit >= 32 ? 16 : nsplit >= 8 ? 4 : 1; }
+// A small n_omega has few elements and many splits.  One thread per element
+// walked them as a chain of dependent loads (50 us at n_omega 10 and 192 splits,
+// 68 us at 48 and 114, the longest kernel of those builds); here a tile's 256
+// threads load 64 splits of 16 elements at once into LDS, and 16 of them add them
+// up in the order of the splits (4 and 5 us).  From few splits on (below 16) a
+// thread per element has all its loads in flight anyway.
+constexpr int kJkElems = 16, kJkChunk = 64;
+__host__ __device__ inline int jkr_elems(int nsplit) { return nsplit >= 16 ? kJkElems : 256; }
 template <int P, class Cfg>
-__host__ __device__ inline long jkr_tiles(const JkArgs& a) {
-  return cdiv((long)a.nw * a.nw, 256 / jkr_share(a.nsplit));
-}
+__host__ __device__ inline long jkr_tiles(const JkArgs& a) { return cdiv((long)a.nw * a.nw, jkr_elems(a.nsplit)); }
 template <int P, class Cfg>
 __device__ void jkr_tile(const JkArgs& a, long t, char* smem) {
-  double* red = (double*)smem;   // [2][256]
   const long w2 = (long)a.nw * a.nw;
-  const int SL = jkr_share(a.nsplit), NE = 256 / SL, tid = threadIdx.x;
-  const int e = tid % NE, sh = tid / NE;
-  const long pq = t * NE + e;
+  const int tid = threadIdx.x;
   double sj = 0.0, sk = 0.0;
-  if (pq < w2) {
-#pragma unroll 4
-    for (int s = sh; s < a.nsplit; s += SL) {
+  if (jkr_elems(a.nsplit) == 256) {
+    const long pq = t * 256 + tid;
+    if (pq >= w2) return;
+#pragma unroll 8
+    for (int s = 0; s < a.nsplit; ++s) {
       sj += a.part[(2L * s) * w2 + pq];
       sk += a.part[(2L * s + 1) * w2 + pq];
     }
+    a.J[pq] = sj;
+    a.K[pq] = sk;
+    return;
   }
-  red[tid] = sj;
-  red[256 + tid] = sk;
-  __syncthreads();
-  if (sh == 0 && pq < w2) {
-    for (int i = 1; i < SL; ++i) {
-      sj += red[i * NE + e];
-      sk += red[256 + i * NE + e];
+  double* buf = (double*)smem;   // [2][kJkChunk][kJkElems]
+  const int e = tid % kJkElems, sh = tid / kJkElems;
+  const long pq = t * kJkElems + e;
+  for (int s0 = 0; s0 < a.nsplit; s0 += kJkChunk) {
+    const int n = min(kJkChunk, a.nsplit - s0);
+#pragma unroll
+    for (int i = 0; i < kJkChunk * kJkElems / 256; ++i) {
+      const int s = sh + i * (256 / kJkElems);
+      const bool ok = s < n && pq < w2;
+      const double* p = a.part + 2L * (s0 + (ok ? s : 0)) * w2 + (ok ? pq : 0);
+      buf[s * kJkElems + e] = p[0];
+      buf[(kJkChunk + s) * kJkElems + e] = p[w2];
     }
+    __syncthreads();
+    if (sh == 0) {
+#pragma unroll 8
+      for (int s = 0; s < n; ++s) {
+        sj += buf[s * kJkElems + e];
+        sk += buf[(kJkChunk + s) * kJkElems + e];
+      }
+    }
+    __syncthreads();   // the next chunk, or a grouped workgroup's next tile, writes buf again
+  }
+  if (sh == 0 && pq < w2) {
     a.J[pq] = sj;
     a.K[pq] = sk;
   }
-  __syncthreads();   // a grouped workgroup's next tile writes red again
 }
 
 // Pair index of orbital p of Omega (explicit map or the default one).
@@ -1580,12 +1847,13 @@ __device__ __forceinline__ int find_owner(const long* __restrict__ off, int n, l
 // direct-staged path would.
 template <int P, class Cfg>
 constexpr int gemm_wpe() {
-  if (is_strip<Cfg>::value) return Cfg::NT == 512 ? 4 : 3;   // two, or three, workgroups per CU
+  if (is_strip<Cfg>::value || std::is_same<Cfg, MoCfg>::value) return Cfg::NT == 512 ? 4 : 3;   // two, or three, workgroups per CU
   return Cfg::NT == 1024 ? 4 : Cfg::NT == 512 ? (P == kF64 ? 4 : 2) : 1;
 }
 template <int P, class Cfg>
 constexpr int gemm_smem() {
   if constexpr (is_strip<Cfg>::value) return strip_smem<Cfg>();
+  else if constexpr (std::is_same<Cfg, MoCfg>::value) return mo_strip_smem();
   else return smem_bytes<typename EngineOf<P>::type, Cfg>();
 }
 #define GEMM_SMEM gemm_smem<P, Cfg>()
@@ -1595,18 +1863,16 @@ RIF_STEP_KERNELS(half, HalfArgs, GEMM_SMEM, Cfg::NT, is_strip<Cfg>::value, GEMM_
 #define GEMM_SMEM_DMA \
   (kPieces<P> > 0 ? smem_bytes_dma<typename EngineOf<P>::type, Cfg>() : smem_bytes<typename EngineOf<P>::type, Cfg>())
 RIF_STEP_KERNELS(halfp, HalfArgs, GEMM_SMEM_DMA, Cfg::NT, false, GEMM_WPE, GEMM_WPE, halfp_g_tile)
-RIF_STEP_KERNELS(mo, MoArgs, GEMM_SMEM, Cfg::NT, false, GEMM_WPE, 1, mo_tile)
+RIF_STEP_KERNELS(mo, MoArgs, GEMM_SMEM, Cfg::NT, false, GEMM_WPE, (std::is_same<Cfg, MoCfg>::value ? 4 : 1), mo_tile)
 RIF_STEP_KERNELS(jao, JaoArgs, GEMM_SMEM, Cfg::NT, true, GEMM_WPE, GEMM_WPE, jao_g_tile)
 RIF_STEP_KERNELS(jaop, JaoArgs, GEMM_SMEM_DMA, Cfg::NT, false, GEMM_WPE, 1, jaop_one_tile)
-// the FP64 64x64 K^q tile: three unpadded direct-load stages
-#define KAO_SMEM (P == kF64 && Cfg::BM == 64 ? 3 * 2 * EngF64T<16, 0>::template stage_bytes<64>() : GEMM_SMEM)
-RIF_STEP_KERNELS(kao, KaoArgs, KAO_SMEM, Cfg::NT, true, GEMM_WPE, 1, kao_tile)
+RIF_STEP_KERNELS(kao, KaoArgs, GEMM_SMEM, Cfg::NT, !is_strip<Cfg>::value, GEMM_WPE, (is_strip<Cfg>::value ? GEMM_WPE : 1), kao_tile)
 RIF_STEP_KERNELS(gemm, GemmArgs, GEMM_SMEM, Cfg::NT, false, GEMM_WPE, 1, gemm_tile)
 RIF_STEP_KERNELS(fock, FockArgs, GEMM_SMEM, Cfg::NT, is_strip<Cfg>::value, GEMM_WPE, GEMM_WPE, fock_tile)
 RIF_STEP_KERNELS(yd, YdArgs, GEMM_SMEM, Cfg::NT, false, GEMM_WPE, 1, yd_tile)
 RIF_STEP_KERNELS(ydz, YdzArgs, kYdzLds * 8, 256, false, 1, 1, ydz_tile)
 RIF_STEP_KERNELS(jkp, JkArgs, 16, 256, false, 1, 1, jkp_tile)
-RIF_STEP_KERNELS(jkr, JkArgs, 2 * 256 * 8, 256, false, 1, 1, jkr_tile)
+RIF_STEP_KERNELS(jkr, JkArgs, 2 * kJkChunk * kJkElems * 8, 256, false, 1, 1, jkr_tile)
 RIF_STEP_KERNELS(coef, CoefArgs, 256 * 8, 256, false, 1, 1, coef_tile)
 RIF_STEP_KERNELS(energy, EnergyArgs, kEnergySmem, kEnergyThreads, false, 1, 1, energy_tile)
 RIF_STEP_KERNELS(fred, FockRedArgs, 16, 256, false, 1, 1, fred_tile)
@@ -1676,9 +1942,19 @@ static decltype(auto) dispatch_fock(int v, F&& f) {
 template <int P, class F>
 static decltype(auto) dispatch_halfp(int v, F&& f) { return dispatch<P>(v, f); }
 template <int P, class F>
-static decltype(auto) dispatch_mo(int v, F&& f) { return dispatch<P>(v, f); }
+static decltype(auto) dispatch_mo(int v, F&& f) {
+  if constexpr (P == kF64) {
+    if (v == 0) return f(MoCfg());
+    return f(Reg64());
+  } else {
+    return dispatch<P>(v, f);
+  }
+}
 template <int P, class F>
-static decltype(auto) dispatch_kao(int v, F&& f) { return dispatch<P>(v, f); }
+static decltype(auto) dispatch_kao(int v, F&& f) {
+  if constexpr (P == kF64) return dispatch_strip(v, f);
+  else return dispatch<P>(v, f);
+}
 template <int P, class F>
 static decltype(auto) dispatch(int v, F&& f) {
   using VS = Vars<EngineOf<P>::type::BK>;
@@ -1701,6 +1977,7 @@ static double est_cost(long nwg, int wg_per_cu, long tile_mn, double useful) {
 template <int P, class Cfg>
 static int wg_per_cu() {
   if constexpr (is_strip<Cfg>::value) return 163840 / strip_smem<Cfg>();
+  else if constexpr (std::is_same<Cfg, MoCfg>::value) return 2;
   else {
   using E = typename EngineOf<P>::type;
   const int lds = 163840 / smem_bytes<E, Cfg>();
@@ -1840,6 +2117,25 @@ static rif_status step_half_any(rif_ctx* c, const HalfArgs& a) {
   }
 }
 RIF_GEMM_STEP(mo, MoArgs, "mo_transform", 4, a.nb, a.na, a.nw, a.nmo)
+template <int P>
+static rif_status step_mo_any(rif_ctx* c, const MoArgs& a) {
+  if constexpr (P == kF64) {
+    auto run = [&](int v) {
+      return dispatch_mo<kF64>(v, [&](auto cfg) {
+        using Cfg = decltype(cfg);
+        hipLaunchKernelGGL((k_mo<kF64, Cfg>), dim3((unsigned)mo_tiles<kF64, Cfg>(a)), dim3(Cfg::NT), 0, c->stream, a);
+        return check_launch(c, "mo_transform");
+      });
+    };
+    const int tile = mo_strip_fits(a.nb, a.na, a.nmo, a.nw) ? 0 : 1;
+    if (pick_variant(c, "mo_transform", {kF64, a.nb, a.na, a.nw, a.nmo}, 1, 0, [&](int) { return run(tile); }) < 0)
+      return RIF_EHIP;
+    ProfScope ps(c, "mo_transform");
+    return run(tile);
+  } else {
+    return step_mo<P>(c, a);
+  }
+}
 RIF_GEMM_STEP(jao, JaoArgs, "jao", 4, a.nb, a.na, a.nw)
 RIF_GEMM_STEP(jaop, JaoArgs, "jao_presplit", 4, a.nb, a.na, a.nw)
 static rif_status step_jao64(rif_ctx* c, const JaoArgs& a) {
@@ -1871,6 +2167,27 @@ static rif_status step_jao_any(rif_ctx* c, const JaoArgs& a) {
   }
 }
 RIF_GEMM_STEP(kao, KaoArgs, "kao", 2, a.nb, a.na, a.nw)
+template <int P>
+static rif_status step_kao_any(rif_ctx* c, const KaoArgs& a) {
+  if constexpr (P == kF64) {
+    auto run = [&](int v) {
+      return dispatch_strip(v, [&](auto cfg) {
+        using Cfg = decltype(cfg);
+        hipLaunchKernelGGL((k_kao<kF64, Cfg>), dim3((unsigned)kao_tiles<kF64, Cfg>(a)), dim3(Cfg::NT), 0, c->stream, a);
+        return check_launch(c, "kao");
+      });
+    };
+    int v = 2;
+    if (strip_fits(a.nb, a.nb, 2)) {
+      v = pick_variant(c, "kao", {kF64, a.nb, a.na, a.nw}, 2, kao_default(a.nb, a.nw), run);
+      if (v < 0) return RIF_EHIP;
+    }
+    ProfScope ps(c, "kao");
+    return run(v);
+  } else {
+    return step_kao<P>(c, a);
+  }
+}
 RIF_GEMM_STEP(fock, FockArgs, "fock", 4, a.nb, a.nw, a.nmo, a.nsplit)
 template <int P>
 static rif_status step_fock_any(rif_ctx* c, const FockArgs& a) {
@@ -2079,8 +2396,7 @@ static BuildArgs make_build_args(const Plan& pl, const rif_instance& in, int pre
   } else if (in.b_split && prec == RIF_FP32) {
     A.half.bf = (const float*)in.b_split;
   }
-  A.mo = MoArgs{nb, na, nw, nmo, in.b_half, in.C, in.b_mo, in.d, cs,
-                nb % 2 == 0 && nmo % 2 == 0 && ((uintptr_t)in.b_half | (uintptr_t)in.C) % 16 == 0};
+  A.mo = MoArgs{nb, na, nw, nmo, in.b_half, in.C, in.b_mo, in.d, cs};
   A.jk = JkArgs{na, nw, pl.jk_nsplit, in.b_mo, in.d, part, in.J, in.K};
   A.jao = JaoArgs{nb, na, nw, in.b, in.d, in.Jn, ds, Planes{nullptr, 0, 0}};
   if (in.b_split && (prec == RIF_BF16X3 || prec == RIF_BF16X6 || prec == RIF_FP16X3)) {
@@ -2089,7 +2405,7 @@ static BuildArgs make_build_args(const Plan& pl, const rif_instance& in, int pre
     const unsigned short* j0 = (const unsigned short*)in.b_split + npc * (long)na * nb * round32(nb);
     A.jao.Bj = Planes{j0, (long)nb * nb * lj, lj};
   }
-  A.kao = KaoArgs{nb, na, nw, in.b_half, in.Kn, nb % 2 == 0 && (uintptr_t)in.b_half % 16 == 0};
+  A.kao = KaoArgs{nb, na, nw, in.b_half, in.Kn};
   A.hc = GemmArgs{nb, nw, nb, in.H, (long)nb, in.C, (long)nmo, HC, (long)nw, 1, nb, (long)nb * nw};
   A.coef = CoefArgs{functional, nw, pl.npairs, pl.ncwo, in.pair_of, in.occ, in.J, in.K, Ac, Bc, Ep};
   A.energy = EnergyArgs{nw, pl.npairs, pl.ncwo, nb, nmo, pl.nparts, in.pair_of, in.occ, in.C, HC, Ep, in.energy,
@@ -2112,13 +2428,13 @@ template <int P>
 static rif_status run_transform(rif_ctx* c, const PSplitArgs& ps, const HalfArgs& h, const MoArgs& m) {
   rif_status st = step_psplit<P>(c, ps);
   if (st || (st = step_half_any<P>(c, h))) return st;
-  return step_mo<P>(c, m);
+  return step_mo_any<P>(c, m);
 }
 template <int P>
 static rif_status run_jk_ao(rif_ctx* c, const PSplitArgs& ps, const JaoArgs& j, const KaoArgs& k) {
   rif_status st = kPlanesHalfJao<P> ? step_psplit<P>(c, ps) : RIF_OK;
   if (st || (st = step_jao_any<P>(c, j))) return st;
-  return step_kao<P>(c, k);
+  return step_kao_any<P>(c, k);
 }
 template <int P>
 static rif_status run_energy_grad(rif_ctx* c, const BuildArgs& A) {
@@ -2157,8 +2473,7 @@ rif_status op_transform(rif_ctx* c, int prec, int nb, int na, int nw, int nmo, c
   const Planes cs{Cs, (long)nw * lc, lc};
   const PSplitArgs ps{C, (long)nmo, nw, nb, lc, Cs, (long)nw * lc};
   const HalfArgs h{nb, nw, nmo, (long)na * nb, b, C, bh, cs, Planes{}, nullptr};
-  const MoArgs m{nb, na, nw, nmo, bh, C, bmo, d, cs,
-                 nb % 2 == 0 && nmo % 2 == 0 && ((uintptr_t)bh | (uintptr_t)C) % 16 == 0};
+  const MoArgs m{nb, na, nw, nmo, bh, C, bmo, d, cs};
   RIF_PREC_SWITCH(prec, run_transform<P>(c, ps, h, m))
 }
 
@@ -2241,7 +2556,7 @@ rif_status op_jk_ao(rif_ctx* c, int prec, int nb, int na, int nw, const double* 
   unsigned short* Ds = (unsigned short*)((char*)c->ws + o_ds);
   const PSplitArgs ps{d, (long)nw, nw, na, ldd, Ds, (long)nw * ldd};
   const JaoArgs j{nb, na, nw, b, d, Jn, Planes{Ds, (long)nw * ldd, ldd}, Planes{nullptr, 0, 0}};
-  const KaoArgs k{nb, na, nw, bh, Kn, nb % 2 == 0 && (uintptr_t)bh % 16 == 0};
+  const KaoArgs k{nb, na, nw, bh, Kn};
   RIF_PREC_SWITCH(prec, run_jk_ao<P>(c, ps, j, k))
 }
 
@@ -2287,7 +2602,7 @@ static rif_status run_build(rif_ctx* c, const BuildArgs& A) {
     OnStream on(c, side);
     if ((st = step1_gemm(c, A.hc))) return st;
   }
-  if ((st = step_psplit<P>(c, A.psc)) || (st = step_half_any<P>(c, A.half)) || (st = step_mo<P>(c, A.mo))) return st;
+  if ((st = step_psplit<P>(c, A.psc)) || (st = step_half_any<P>(c, A.half)) || (st = step_mo_any<P>(c, A.mo))) return st;
   if ((st = hip(hipEventRecord(e_mo, main)))) return st;
   {
     OnStream on(c, side);
@@ -2296,7 +2611,7 @@ static rif_status run_build(rif_ctx* c, const BuildArgs& A) {
       return st;
   }
   if (((kPlanesHalfJao<P> || (kPieces<P> > 0 && A.jao.Bj.p)) && (st = step_psplit<P>(c, A.psd))) ||
-      (st = step_jao_any<P>(c, A.jao)) || (st = step_kao<P>(c, A.kao)))
+      (st = step_jao_any<P>(c, A.jao)) || (st = step_kao_any<P>(c, A.kao)))
     return st;
   if ((st = hip(hipStreamWaitEvent(main, e_side, 0))) || (st = step1_coef(c, A.coef)) ||
       (st = hip(hipEventRecord(e_coef, main))))
@@ -2328,7 +2643,7 @@ static rif_status run_build_direct(rif_ctx* c, const BuildArgs& A) {
     OnStream on(c, side);
     if ((st = step1_gemm(c, A.hc))) return st;
   }
-  if ((st = step_psplit<P>(c, A.psc)) || (st = step_half_any<P>(c, A.half)) || (st = step_mo<P>(c, A.mo))) return st;
+  if ((st = step_psplit<P>(c, A.psc)) || (st = step_half_any<P>(c, A.half)) || (st = step_mo_any<P>(c, A.mo))) return st;
   if ((st = hip(hipEventRecord(e_mo, main)))) return st;
   {
     OnStream on(c, side);
@@ -2509,7 +2824,7 @@ static void group_offsets(const std::vector<Args>& a, TilesFn tiles, std::vector
     const int n = B->n;                                                                                    \
     return dispatch_##NAME<P>(v, [&](auto cfg) {                                                                  \
       using Cfg = decltype(cfg);                                                                           \
-      if constexpr (NVAR == 2 && Cfg::BM != Cfg::BN) {                                                     \
+      if constexpr (P != kF64 && NVAR == 2 && Cfg::BM != Cfg::BN) {                                        \
         return fail(B->c, RIF_ENOTSUP, LABEL ": non-square tile variant");                                 \
       } else {                                                                                             \
         if (g.total[v] == 0) return RIF_OK;                                                                \
@@ -2551,9 +2866,9 @@ static void group_offsets(const std::vector<Args>& a, TilesFn tiles, std::vector
 
 RIF_GROUP_SETUP(half, HalfArgs, "g_half_transform", 3, 4)
 RIF_GROUP_SETUP(halfp, HalfArgs, "g_half_transform_presplit", 4, 4)
-RIF_GROUP_SETUP(mo, MoArgs, "g_mo_transform", 4, 4)
+RIF_GROUP_SETUP(mo, MoArgs, "g_mo_transform", 2, 4)
 RIF_GROUP_SETUP(jao, JaoArgs, "g_jao", 3, 4)
-RIF_GROUP_SETUP(kao, KaoArgs, "g_kao", 2, 2)
+RIF_GROUP_SETUP(kao, KaoArgs, "g_kao", 3, 2)
 RIF_GROUP_SETUP(fock, FockArgs, "g_fock", 2, 4)
 #define RIF_GROUP_FIXED_P(NAME, ARGS, LABEL)                                                               \
   template <int P>                                                                                         \
@@ -2693,14 +3008,20 @@ static rif_status batch_setup(BatchImpl* B, const std::vector<BuildArgs>& A) {
   if constexpr (P == kF64) {
     if ((st = choose_strip(B->half, [&](int v) { return launch_half<P>(B, v); }))) return st;
     if ((st = choose_strip(B->jao, [&](int v) { return launch_jao<P>(B, v); }))) return st;
+    // (the largest molecule's choice: wide tiles are mostly idle on small ones)
+    if (!strips) B->kao.variant = 2;
+    else if ((st = pick(B->kao, 2, kao_default(kao[0].nb, kao[0].nw), [&](int v) { return launch_kao<P>(B, v); }))) return st;
     B->fock.variant = fock[0].strip ? 0 : 1;
+    B->mo.variant = 0;
+    for (auto& m : mo)
+      if (!mo_strip_fits(m.nb, m.na, m.nmo, m.nw)) B->mo.variant = 1;
   } else {
     if (!B->bpre && (st = choose(B->half, [&](int v) { return launch_half<P>(B, v); }))) return st;
+    if ((st = choose(B->mo, [&](int v) { return launch_mo<P>(B, v); }))) return st;
     if ((st = choose(B->jao, [&](int v) { return launch_jao<P>(B, v); }))) return st;
+    if ((st = choose(B->kao, [&](int v) { return launch_kao<P>(B, v); }))) return st;
     if ((st = choose(B->fock, [&](int v) { return launch_fock<P>(B, v); }))) return st;
   }
-  if ((st = choose(B->mo, [&](int v) { return launch_mo<P>(B, v); }))) return st;
-  if ((st = choose(B->kao, [&](int v) { return launch_kao<P>(B, v); }))) return st;
   return RIF_OK;
 }
 

@@ -31,6 +31,9 @@
 
 namespace rif {
 
+// Zeros, read for k rows past the end.
+static __device__ __attribute__((aligned(16))) double kDmaZeros[128];
+
 // First column of the pair staged at (even) position p of an n-long row, and the
 // column that position p holds (-1: none).  n >= 2.
 __host__ __device__ __forceinline__ int pair_start(int p, int n) { return (n & 1) && p == n - 1 ? n - 2 : p; }

@@ -1,6 +1,7 @@
-"""J and K (MO) at the sizes where the split over l and the reduction's shares
-change: one auxiliary function, fewer than eight, a single element, shares of
-1, 4 and 16 and remainders of each; the allocation-free call takes the same path.
+"""J and K (MO) at the sizes where the split over l and the reduction's tiles
+change: one auxiliary function, a single element, few splits (a thread per
+element), one and several chunks of 64 splits and their remainders; the
+allocation-free call takes the same path.
 
 Tolerance: sums of n_aux FP64 products, each step rounding at most 2^-53 of the
 sum of magnitudes: n_aux 2^-53, against the largest element, which for K (a sum
@@ -15,7 +16,7 @@ from gpu_util import host, relerr
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("na,nw", [(1, 1), (7, 1), (9, 2), (61, 5), (192, 10), (255, 16), (600, 48), (603, 47), (500, 99), (90, 130), (40, 300), (17, 520)])
+@pytest.mark.parametrize("na,nw", [(1, 1), (15, 2), (16, 3), (64, 4), (65, 4), (7, 1), (9, 2), (61, 5), (192, 10), (255, 16), (600, 48), (603, 47), (500, 99), (90, 130), (40, 300), (17, 520)])
 def test_jk_mo_matches_numpy(na, nw):
     import torch
     import paper_2012_15662_amd as rif
