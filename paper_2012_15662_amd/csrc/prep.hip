@@ -8,6 +8,8 @@
 //
 //   k_rowsum     ||G||_inf (max row sum of |G|), for the default delta
 //   k_bk_init    working copy of G, L = I, perm, step state
+//   k_bk_coop    the factorisation in one launch, up to 2048 auxiliary functions
+//                (k_bk_coop_l: L in the order of the pivots); above, per column:
 //   k_bk_pivot   one workgroup: the pivot decision at the current column, the
 //                symmetric interchange, the D block and the L column(s)
 //   k_bk_update  trailing update A -= L_k D_k L_k^T (all workgroups)
@@ -284,38 +286,55 @@ __global__ __launch_bounds__(256) void k_compose(int n, const double* __restrict
 }
 
 // ---- the factorisation in one cooperative launch -----------------------------
-// Row i of A lives in the LDS of workgroup i mod G for the whole factorisation;
-// its entries left of the current column, no longer needed as A, hold row i of
-// L.  Workgroups exchange data through single-write slots: each slot is filled
+// Workgroup 0 decides every step; the others hold A, a row's n elements in the
+// registers of their 512 threads (thread t has columns t, t + 512, ...), and
+// keep it up to date.  Rows and columns stay where they are: an interchange only
+// exchanges the positions that every thread keeps of its own columns (and every
+// workgroup of its rows), and ties are broken by position.
+//   - At the start of a panel of 8 to 16 positions the row holders publish the
+//     panel's columns (P); workgroup 0 takes them into registers, a row per
+//     thread, and takes the panel's steps alone: the maximum over the column, the
+//     pivot test, the L entries, and the update of the columns left in the panel.
+//     A step costs it one workgroup barrier and no exchange.
+//   - Each step's pivot column goes out as W[k], the kind of step as M1[k].  The
+//     row holders take the steps of a panel four at a time as they appear, form
+//     their rows' L entries from W and update their rows: rank-one updates in the
+//     order of the steps, as a step at a time would do them.
+//   - Where the first pivot test fails, M1[k] asks for column imax (CI) and row
+//     imax (RI); the row holders, which have all earlier steps applied, answer;
+//     M2[k] tells them the decision.
+// Data pass between workgroups through single-write slots: each is filled
 // beforehand with a signalling-NaN pattern that no arithmetic result takes
-// (arithmetic on NaNs yields quiet NaNs), written once with an agent-scope
-// atomic store, and read by polling it with agent-scope atomic loads until it
-// no longer holds that pattern.  Every wait is bounded; past the limit, or once
-// another workgroup has flagged a timeout, a workgroup flags it and returns.
-// Per step at column k:
-//   1. every workgroup reads column k (C1; each workgroup published its rows'
-//      entries of it at the end of the previous step, before the rest of its
-//      update) and forms colmax, imax and |A_kk| itself (the same data and
-//      order-free reductions, so the same decision everywhere);
-//   2. where the first pivot test fails: its rows' entries of column imax
-//      (CI) and, from the owners of rows imax, k and k+1, those whole rows (RI,
-//      RK, RK1: the only rows an interchange can move); every workgroup forms
-//      rowmax and takes the decision;
-//   3. every workgroup forms the pivot column(s) after the interchange from
-//      column k and column imax, swaps the interchanged columns in its rows,
-//      takes over a moved row (from RK, RK1 or RI), writes its L entries and
-//      updates its rows with the arithmetic of k_bk_pivot and k_bk_update.
-// Workgroup 0 keeps perm, the block sizes and D.
+// (arithmetic on NaNs yields quiet NaNs), written once with an agent-scope atomic
+// store, and read by polling it with agent-scope atomic loads until it no longer
+// holds that pattern.  Every wait is bounded; past the limit, or once another
+// workgroup has flagged a timeout, a workgroup flags it and returns.
+//
+// What bounds it: the chain of n steps in workgroup 0 (barrier, two reductions, a
+// division: 1.1 us at n = 1044) and one exchange to the row holders and back a
+// panel (8 us).  1.9 ms at n = 1044 where no interchange is needed and 5 where
+// most columns need the second test, 1.5 and 4.4 at n = 1020; with an exchange of
+// each column between all workgroups at every step it was 4.2 and 6.8.  512
+// threads: with 1024 the panel does not fit the registers above n = 1024, with 256
+// it does not above 1280; panels of 16 where it fits.  Waves without rows left do
+// no arithmetic.
 constexpr unsigned long long kBkEmpty = 0x7FF4C0FFEE5E7F11ull;   // signalling NaN
-constexpr size_t kBkLds = 150 * 1024;
+constexpr int kBkThreads = 512, kBkWaves = kBkThreads / 64;
+constexpr int kBkBatch = 4;    // steps the row holders take at once
+constexpr int kBkMaxN = 4 * kBkThreads;
+// For rows of up to 512 U elements: the positions of a panel (U times that in
+// doubles a thread) and the rows a workgroup holds, at most (n / 255 rounded up).
+constexpr int bk_panel(int U) { return U > 3 ? 8 : (U > 2 ? 12 : 16); }
+constexpr int bk_rows(int U) { return 2 * U + 1; }
+inline int bk_u(int n) { return (n + kBkThreads - 1) / kBkThreads; }
 
 struct BkcArgs {
-  int n, G;
+  int n, G;                      // G workgroups: the deciding one and G - 1 row holders
   const double* Gm;              // [n][n] the metric
-  double *L, *D;                 // [n][n] out
-  int *perm, *bsz;               // [n] out (bsz zero-filled beforehand)
-  double *C1, *CI;               // [n][n] slots: C1[k][i] = A_ik, CI[k][i] = A_i,imax
-  double *RK, *RK1, *RI;         // [n][n] slots: whole rows k, k+1, imax at step k
+  double *Lr, *D;                // [n][n] out; row i of Lr: the L entries of row i of Gm
+  int *perm, *bsz;               // [n] out (perm the identity, bsz zero-filled beforehand)
+  double *P, *W, *CI, *RI;       // [n][n] slots, by position and row (P, W, CI) or column (RI) of Gm
+  double *M1, *M2;               // [n] slots, by position
   int* err;
   long long spin;                // polls of one value before giving up; < 0: give up at once
 };
@@ -324,200 +343,487 @@ __device__ __forceinline__ void bk_put(double* p, double v) {
   __hip_atomic_store((unsigned long long*)p, (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ unsigned long long bk_peek(const double* p) {
-  return __hip_atomic_load((unsigned long long*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void bk_put_word(double* p, unsigned long long v) {
+  __hip_atomic_store((unsigned long long*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// dst[j] = slot src[j] for j in [j0, j1), strided over the workgroup
-__device__ bool bk_take_range(const double* src, double* dst, int j0, int j1, const int* err, long long spin) {
+__device__ __forceinline__ unsigned long long bk_peek(const double* p) {
+  return __hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Slot of a row of slots (uniform) and a byte offset in it.
+__device__ __forceinline__ const double* bk_at(const double* row, unsigned bytes) {
+  return (const double*)((const char*)row + bytes);
+}
+// Reads slots until none of those wanted is empty; the N of a thread (and those of
+// its wave) are in flight together.  All lanes of a wave call it.
+template <int N, class P, class Want>
+__device__ __forceinline__ bool bk_take(unsigned long long (&x)[N], P slot, Want want, const int* err, long long spin) {
   if (spin < 0) return false;
-  for (int j = j0 + (int)threadIdx.x; j < j1; j += 256) {
-    unsigned long long u = bk_peek(src + j);
-    for (long long s = 0; u == kBkEmpty; ++s) {
-      if (s >= spin || __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return false;
-      __builtin_amdgcn_s_sleep(1);
-      u = bk_peek(src + j);
-    }
-    dst[j] = __longlong_as_double((long long)u);
+  for (long long s = 0;; ++s) {
+    bool missing = false;
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = want(i) ? bk_peek(slot(i)) : 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) missing = missing || x[i] == kBkEmpty;
+    if (!__any(missing)) return true;
+    if (s >= spin || ((s & 15) == 15 && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0))
+      return false;
+    __builtin_amdgcn_s_sleep(1);
   }
-  return true;
+}
+__device__ __forceinline__ double bk_val(unsigned long long v) { return __longlong_as_double((long long)v); }
+// a value that all lanes hold, for the scalar unit
+__device__ __forceinline__ int bk_uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+// M1: 1 = the step at k is 1x1 without an interchange, 2 + imax = column and row
+// imax (a position) are wanted; M2: kstep + 4 kp
+constexpr unsigned long long kBkPlain = 1;
+
+// A barrier for data passed through the LDS: global stores in flight stay in
+// flight (a slot says itself that it is written), where __syncthreads would wait
+// the microsecond that they take.
+__device__ __forceinline__ void bk_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// Loads are done: on a rare path, so that the common one it joins need not wait.
+__device__ __forceinline__ void bk_loads_done() { __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8)); }
+
+// Max of values >= 0, none a signalling NaN: over groups of 8 lanes, every lane
+// getting it, and over the wave, lane 63 getting it.
+__device__ __forceinline__ double bk_max2(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+template <int kCtrl>
+__device__ __forceinline__ double bk_dpp(double x) {
+  const unsigned long long v = (unsigned long long)__double_as_longlong(x);
+  const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)v, kCtrl, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(v >> 32), kCtrl, 0xF, 0xF, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double bk_max8(double x) {
+  x = bk_max2(x, bk_dpp<0xB1>(x));          // quad_perm [1,0,3,2]
+  x = bk_max2(x, bk_dpp<0x4E>(x));          // quad_perm [2,3,0,1]
+  return bk_max2(x, bk_dpp<0x141>(x));      // row_half_mirror
+}
+__device__ __forceinline__ double bk_max64(double x) {
+  x = bk_max8(x);
+  x = bk_max2(x, bk_dpp<0x128>(x));        // row_ror:8
+  x = bk_max2(x, bk_dpp<0x142>(x));        // row_bcast:15
+  return bk_max2(x, bk_dpp<0x143>(x));     // row_bcast:31
+}
+// a b + c, the result in a register of its own: the columns of a panel move down
+// by one at each step without copies
+__device__ __forceinline__ double bk_fma(double a, double b, double c) {
+  double r;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
 }
 
-__global__ __launch_bounds__(256) void k_bk_coop(BkcArgs a) {
-  extern __shared__ double sm[];
-  const int n = a.n, G = a.G, g = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int R = g < n ? (n - g + G - 1) / G : 0;   // rows i = g + G t, t < R
-  double* rows = sm;                                // [R][n]
-  double* c1 = rows + (long)R * n;                  // column k
-  double* ci = c1 + n;                              // column imax
-  double* ri = ci + n;                              // row imax
-  double* ck = ri + n;                              // column k after the interchange
-  double* cq = ck + n;                              // column k+1 after the interchange (2x2)
-  for (long x = tid; x < (long)R * n; x += 256) {
-    const int t = (int)(x / n), j = (int)(x - (long)t * n);
-    rows[x] = a.Gm[(long)(g + G * t) * n + j];
-  }
-  if (g == 0)
-    for (int i = tid; i < n; i += 256) a.perm[i] = i;
-  __syncthreads();
-  auto fail = [&]() { atomicExch(a.err, 1); };
-  int k = 0;
+template <int U>
+struct BkPanelLds {
+  static constexpr int NB = bk_panel(U);
+  double red[2][kBkWaves], cand[2][NB];                 // by parity of the step
+  double red2[kBkWaves], cand2[NB + 1], candq[NB + 1], arr;
+  int redi[kBkWaves], fail;
+};
+
+// The inverse of a 2x2 block and the L entries of a row in its two columns, each
+// product sum with one rounding less: the second product rounded, the first not.
+struct BkBlock { double i00, i01, i11; };
+__device__ __forceinline__ BkBlock bk_block(double e00, double e10, double e11) {
+  const double det = fma(e00, e11, -(e10 * e10));
+  return {e11 / det, -e10 / det, e00 / det};
+}
+__device__ __forceinline__ void bk_l2(const BkBlock& v, double x0, double x1, double& l0, double& l1) {
+  l0 = fma(x0, v.i00, x1 * v.i01);
+  l1 = fma(x0, v.i01, x1 * v.i11);
+}
+
+// Workgroup 0: thread t has rows t + 512 u; C[p][u] is the entry in the column at
+// position k + p.
+template <int U>
+__device__ void bk_decide(const BkcArgs& a, BkPanelLds<U>& s) {
+  constexpr int NB = bk_panel(U);
+  const int n = a.n, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  int pos[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) pos[u] = tid + kBkThreads * u < n ? tid + kBkThreads * u : -1;
+  auto at = [&](int u) { return 8u * (unsigned)(tid + kBkThreads * u); };   // byte offset of the row in a row of slots
+  double C[NB][U];
+  int k = 0, b = 0;
+  if (tid == 0) s.fail = 0;
+  bk_barrier();
   while (k < n) {
-    const int t0 = k > g ? (k - g + G - 1) / G : 0;   // first row held here at or past k
-    // 1. column k
-    {
-      double* C1k = a.C1 + (long)k * n;
-      if (k == 0)
-        for (int t = wv; t < R; t += 4)
-          if (lane == 0) bk_put(C1k + g + G * t, rows[(long)t * n]);
-      const bool ok = bk_take_range(C1k, c1, k, n, a.err, a.spin);
-      if (!ok) fail();
-      if (__syncthreads_or(!ok)) return;
+    const int kend = min(k + NB, n);
+    bool ok = true;
+#pragma unroll
+    for (int h = 0; h < NB; h += NB / 2) {   // by halves, for the registers
+      unsigned long long x[NB / 2 * U];
+      ok = ok && bk_take(x, [&](int i) { return bk_at(a.P + (long)(k + h + i / U) * n, at(i % U)); },
+                         [&](int i) { return k + h + i / U < kend && pos[i % U] >= k; }, a.err, a.spin);
+#pragma unroll
+      for (int i = 0; i < NB / 2 * U; ++i) C[h + i / U][i % U] = ok ? bk_val(x[i]) : 0.0;
     }
-    // colmax / imax below the diagonal (lowest index on ties; NaNs never
-    // chosen; 0 and k+1 when the column is zero), the same in every wave
-    double cm = 0.0;
-    int im = n;
-    for (int i = k + 1 + lane; i < n; i += 64) {
-      const double v = fabs(c1[i]);
-      if (v > cm || (v == cm && i < im)) { cm = v; im = i; }
+    if (!ok) s.fail = 1;
+    bk_barrier();
+    if (bk_uniform(s.fail)) {
+      if (tid == 0) atomicExch(a.err, 1);
+      return;
     }
-    {
-      const double top = wave_max_dpp(cm);
-      im = wave_min_int_dpp(cm == top ? im : n);
-      cm = top;
-    }
-    const double absakk = fabs(c1[k]);
-    int kstep = 1, kp = k;
-    if (k + 1 < n && fmax(absakk, cm) != 0.0 && absakk < kAlpha * cm) {
-      // 2. column imax and row imax; rowmax over row imax left of the diagonal
-      //    (columns k..imax-1) and column imax below it
-      double* CIk = a.CI + (long)k * n;
-      double* RIk = a.RI + (long)k * n;
-      for (int t = t0 + wv; t < R; t += 4)
-        if (lane == 0) bk_put(CIk + g + G * t, rows[(long)t * n + im]);
-      if (im % G == g)
-        for (int j = tid; j < n; j += 256) bk_put(RIk + j, rows[(long)(im / G) * n + j]);
-      if (k % G == g)
-        for (int j = tid; j < n; j += 256) bk_put(a.RK + (long)k * n + j, rows[(long)(k / G) * n + j]);
-      if ((k + 1) % G == g)
-        for (int j = tid; j < n; j += 256) bk_put(a.RK1 + (long)k * n + j, rows[(long)((k + 1) / G) * n + j]);
-      bool ok = bk_take_range(CIk, ci, k, n, a.err, a.spin);
-      ok = ok && bk_take_range(RIk, ri, k, n, a.err, a.spin);
-      if (!ok) fail();
-      if (__syncthreads_or(!ok)) return;
-      double rm = 0.0;
-      for (int j = k + lane; j < n; j += 64)
-        if (j != im) rm = fmax(rm, fabs(j < im ? ri[j] : ci[j]));
-      rm = wave_max_dpp(rm);
-      if (absakk * rm >= kAlpha * cm * cm) {
-        kstep = 1; kp = k;
-      } else if (fabs(ri[im]) >= kAlpha * rm) {
-        kstep = 1; kp = im;
-      } else {
-        kstep = 2; kp = im;
+    bk_loads_done();
+    while (k < kend) {
+      // colmax below the diagonal; NaNs are never chosen.  No wave reduces or
+      // divides for rows it no longer has.
+      bool act[U], any = false;
+      {
+        double cm = 0.0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          act[u] = __any(pos[u] > k);
+          any = any || act[u];
+          if (act[u] && pos[u] > k) cm = fmax(cm, fabs(C[0][u]));
+          if ((unsigned)(pos[u] - k) < NB) s.cand[b][pos[u] - k] = C[0][u];
+        }
+        if (any) cm = bk_max64(cm);
+        if (lane == 63) s.red[b][wv] = cm;
       }
-    }
-    const int kk = k + kstep - 1;
-    auto pi = [&](int j) { return j == kk ? kp : (j == kp ? kk : j); };
-    // 3. pivot column(s) after the interchange (kk kp)
-    for (int j = k + tid; j < n; j += 256) {
+      bk_barrier();
+      double cm = s.red[b][lane & (kBkWaves - 1)], d = s.cand[b][0];
+      const double* cd = s.cand[b];
+      double l[U];   // on its way while the maxima are compared
+#pragma unroll
+      for (int u = 0; u < U; ++u) l[u] = C[0][u] / d;
+      cm = bk_max8(cm);
+      const double absakk = fabs(d);
+      int kstep = 1;
+      if (bk_uniform(k + 1 < n && fmax(absakk, cm) != 0.0 && absakk < kAlpha * cm)) {
+        // the first position of the maximum, its column and its row; rowmax over
+        // row imax left of the diagonal and column imax below it
+        int im = n;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (pos[u] > k && fabs(C[0][u]) == cm) im = min(im, pos[u]);
+        im = wave_min_int_dpp(im);
+        if (lane == 0) s.redi[wv] = im;
+        bk_barrier();
+        im = s.redi[0];
+#pragma unroll
+        for (int i = 1; i < kBkWaves; ++i) im = min(im, s.redi[i]);
+        im = bk_uniform(im);
+        if (tid == 0) bk_put_word(a.M1 + k, 2 + (unsigned long long)im);
+        unsigned long long x[2 * U];
+        ok = bk_take(x, [&](int i) { return bk_at((i < U ? a.CI : a.RI) + (long)k * n, at(i % U)); },
+                            [&](int i) { return pos[i % U] >= k; }, a.err, a.spin);
+        if (!ok) s.fail = 1;
+        bk_loads_done();
+        double ci[U], rm = 0.0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          ci[u] = bk_val(x[u]);
+          const double ri = bk_val(x[U + u]);
+          if (pos[u] >= k && pos[u] != im) rm = fmax(rm, fabs(pos[u] < im ? ri : ci[u]));
+          if (pos[u] == im) s.arr = ri;
+        }
+        rm = bk_max64(rm);
+        if (lane == 63) s.red2[wv] = rm;
+        bk_barrier();
+        if (bk_uniform(s.fail)) {
+          if (tid == 0) atomicExch(a.err, 1);
+          return;
+        }
+        rm = bk_max8(s.red2[lane & (kBkWaves - 1)]);
+        int kp = im;
+        if (absakk * rm >= kAlpha * cm * cm) kp = k;
+        else if (!(fabs(s.arr) >= kAlpha * rm)) kstep = 2;
+        kp = bk_uniform(kp);
+        kstep = bk_uniform(kstep);
+        if (tid == 0) bk_put_word(a.M2 + k, (unsigned long long)kstep + 4 * (unsigned long long)kp);
+        // the interchange of positions kk and kp: the column that leaves kk goes
+        // to kp, if kp is in the panel
+        const int kk = k + kstep - 1;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (kp != kk) {
+#pragma unroll
+            for (int p = 1; p < NB; ++p)
+              if (p == kp - k) C[p][u] = kstep == 1 ? C[0][u] : C[1][u];
+            if (kstep == 1) C[0][u] = ci[u];
+            if (pos[u] == kk) pos[u] = kp;
+            else if (pos[u] == kp) pos[u] = kk;
+          }
+          const int q = pos[u] - k;
+          if (q >= 0 && q <= NB) {
+            s.cand2[q] = C[0][u];
+            s.candq[q] = ci[u];
+          }
+          act[u] = __any(q > 0);
+        }
+        bk_barrier();
+        cd = s.cand2;
+        d = cd[0];
+        if (kstep == 1) {
+#pragma unroll
+          for (int u = 0; u < U; ++u) l[u] = C[0][u] / d;
+        }
+        if (kstep == 2) {
+          const double e00 = d, e10 = cd[1], e11 = s.candq[1];
+          const BkBlock inv = bk_block(e00, e10, e11);
+          if (tid == 0) {
+            a.D[(long)k * n + k] = e00;
+            a.D[(long)k * n + k + 1] = e10;
+            a.D[(long)(k + 1) * n + k] = e10;
+            a.D[(long)(k + 1) * n + k + 1] = e11;
+            a.bsz[k] = 2;
+            a.bsz[k + 1] = 0;
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const double x0 = C[0][u], x1 = ci[u];
+            if (pos[u] >= k) {
+              bk_put(a.W + (long)k * n + tid + kBkThreads * u, x0);
+              bk_put(a.W + (long)(k + 1) * n + tid + kBkThreads * u, x1);
+            }
+            double l0, l1;
+            bk_l2(inv, x0, x1, l0, l1);
+#pragma unroll
+            for (int p = 2; p < NB; ++p) {
+              C[p - 2][u] = bk_fma(-l1, s.candq[p], bk_fma(-l0, cd[p], C[p][u]));
+              asm volatile("" ::: "memory");   // or all of both columns is loaded ahead, into registers there are not
+            }
+          }
+        }
+      } else if (tid == 0) {
+        bk_put_word(a.M1 + k, kBkPlain);
+      }
       if (kstep == 1) {
-        ck[j] = kp == k ? c1[j] : ci[pi(j)];
-      } else {
-        ck[j] = c1[pi(j)];
-        cq[j] = ci[pi(j)];
+        if (tid == 0) {
+          a.D[(long)k * n + k] = d;
+          a.bsz[k] = 1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (pos[u] >= k) bk_put(a.W + (long)k * n + tid + kBkThreads * u, C[0][u]);
+          l[u] = d != 0.0 ? -l[u] : -0.0;
+        }
+        // the pivot column's entries in the panel, four at a time for all rows
+#pragma unroll
+        for (int p0 = 0; p0 < NB; p0 += 4) {
+          if (k + p0 >= kend) break;
+          double e[4];
+#pragma unroll
+          for (int p = 0; p < 4; ++p) e[p] = cd[p0 + p];
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (act[u]) {
+#pragma unroll
+              for (int p = 0; p < 4; ++p)
+                if (p0 + p > 0) C[p0 + p - 1][u] = bk_fma(l[u], e[p], C[p0 + p][u]);
+            }
+        }
       }
+      k += kstep;
+      b ^= 1;
     }
-    if (kp != kk) {
-      // the row moving into a position held here (its whole row, L part included)
-      const double* from = nullptr;
-      int tdst = -1;
-      if (kk % G == g) { from = a.RI + (long)k * n; tdst = kk / G; }                          // old row kp
-      else if (kp % G == g) { from = (kstep == 1 ? a.RK : a.RK1) + (long)k * n; tdst = kp / G; }   // old row kk
-      if (kk % G == g && kp % G == g) {   // both positions held here: swap in place
-        from = nullptr;
-        for (int j = tid; j < n; j += 256) {
-          const double x = rows[(long)(kk / G) * n + j];
-          rows[(long)(kk / G) * n + j] = rows[(long)(kp / G) * n + j];
-          rows[(long)(kp / G) * n + j] = x;
-        }
-      }
-      if (from) {
-        const bool ok = bk_take_range(from, rows + (long)tdst * n, 0, n, a.err, a.spin);
-        if (!ok) fail();
-        if (__syncthreads_or(!ok)) return;
-      }
-      __syncthreads();
-      // columns kk <-> kp in the rows still active
-      for (int t = t0 + wv; t < R; t += 4)
-        if (lane == 0) {
-          double* r = rows + (long)t * n;
-          const double x = r[kk];
-          r[kk] = r[kp];
-          r[kp] = x;
-        }
-      if (g == 0 && tid == 0) {
-        const int x = a.perm[kk];
-        a.perm[kk] = a.perm[kp];
-        a.perm[kp] = x;
-      }
-    }
-    __syncthreads();
-    // D block, L entries and the trailing update on the rows held here; each
-    // row's entry of the next pivot column k0 is published before the rest
-    const int k0 = k + kstep;
-    double* C1n = a.C1 + (long)(k0 < n ? k0 : 0) * n;
-    if (kstep == 1) {
-      const double d = ck[k];
-      if (g == 0 && tid == 0) { a.D[(long)k * n + k] = d; a.bsz[k] = 1; }
-      for (int t = (k0 > g ? (k0 - g + G - 1) / G : 0) + wv; t < R; t += 4) {
-        double* r = rows + (long)t * n;
-        const int i = g + G * t;
-        const double l = d != 0.0 ? ck[i] / d : 0.0;
-        if (lane == 0) bk_put(C1n + i, r[k0] - l * ck[k0]);   // next pivot column first
-        for (int j = k0 + lane; j < n; j += 64) r[j] = r[j] - l * ck[j];
-        if (lane == 0) r[k] = l;
-      }
-    } else {
-      const double e00 = ck[k], e10 = ck[k + 1], e11 = cq[k + 1];
-      const double det = e00 * e11 - e10 * e10;
-      const double i00 = e11 / det, i01 = -e10 / det, i11 = e00 / det;
-      if (g == 0 && tid == 0) {
-        a.D[(long)k * n + k] = e00;
-        a.D[(long)k * n + k + 1] = e10;
-        a.D[(long)(k + 1) * n + k] = e10;
-        a.D[(long)(k + 1) * n + k + 1] = e11;
-        a.bsz[k] = 2;
-        a.bsz[k + 1] = 0;
-      }
-      if ((k + 1) % G == g && tid == 0) rows[(long)((k + 1) / G) * n + k] = 0.0;   // L is I on the block
-      for (int t = (k0 > g ? (k0 - g + G - 1) / G : 0) + wv; t < R; t += 4) {
-        double* r = rows + (long)t * n;
-        const int i = g + G * t;
-        const double x0 = ck[i], x1 = cq[i];
-        const double l0 = x0 * i00 + x1 * i01, l1 = x0 * i01 + x1 * i11;
-        if (lane == 0) {   // next pivot column first
-          double v = r[k0] - l0 * ck[k0];
-          v -= l1 * cq[k0];
-          bk_put(C1n + i, v);
-        }
-        for (int j = k0 + lane; j < n; j += 64) {
-          double v = r[j] - l0 * ck[j];
-          v -= l1 * cq[j];
-          r[j] = v;
-        }
-        if (lane == 0) { r[k] = l0; r[k + 1] = l1; }
-      }
-    }
-    __syncthreads();
-    k = k0;
   }
-  // L: the left parts of the rows, unit diagonal, zero above
-  for (long x = tid; x < (long)R * n; x += 256) {
-    const int t = (int)(x / n), j = (int)(x - (long)t * n), i = g + G * t;
-    a.L[(long)i * n + j] = j < i ? rows[x] : (j == i ? 1.0 : 0.0);
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (pos[u] >= 0) a.perm[pos[u]] = tid + kBkThreads * u;
+}
+
+template <int U>
+struct BkRowsLds {
+  static constexpr int R = bk_rows(U);
+  double w[kBkBatch][R], l[kBkBatch][R], d[kBkBatch];   // pivot columns in the rows held here, L entries, pivots
+  double e[3];                                          // a 2x2 block
+  int rp[R], cnt, im, fail;                             // positions of the rows; the next steps
+};
+
+// A row holder: rows g + (G - 1) t in A[t][u], columns tid + 512 u.
+template <int U>
+__device__ void bk_rows_holder(const BkcArgs& a, BkRowsLds<U>& s) {
+  constexpr int R = bk_rows(U), B = kBkBatch, NB = bk_panel(U);
+  const int n = a.n, tid = threadIdx.x, Gw = a.G - 1, g = (int)blockIdx.x - 1;
+  auto col = [&](int u) { return tid + kBkThreads * u; };
+  int pos[U], own[U];   // position of the column; the row held here of the same index, or -1
+  double A[R][U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    pos[u] = col(u) < n ? col(u) : -1;
+    own[u] = col(u) < n && col(u) % Gw == g ? col(u) / Gw : -1;
+#pragma unroll
+    for (int t = 0; t < R; ++t) A[t][u] = g + Gw * t < n && col(u) < n ? a.Gm[(long)(g + Gw * t) * n + col(u)] : 0.0;
   }
+  if (tid < R) s.rp[tid] = g + Gw * tid < n ? g + Gw * tid : -1;
+  if (tid == 0) s.fail = 0;
+  bk_barrier();
+  auto failed = [&]() {
+    const bool f = bk_uniform(s.fail) != 0;
+    if (f && tid == 0) atomicExch(a.err, 1);
+    return f;
+  };
+  // rows at or past position k, in the columns at positions k .. k + NB - 1
+  auto publish = [&](int k) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (pos[u] >= k && pos[u] < k + NB) {
+#pragma unroll
+        for (int t = 0; t < R; ++t)
+          if (s.rp[t] >= k) bk_put(a.P + (long)pos[u] * n + g + Gw * t, A[t][u]);
+      }
+  };
+  publish(0);
+  int k = 0, kend = min(NB, n);
+  while (k < n) {
+    // Wave 0 watches the words of the next steps, one a lane: cnt plain steps, and
+    // imax where a step is none.  (All threads polling their own entries of W keep
+    // the deciding workgroup's stores from the same few channels: 2 us a step.)
+    if (tid < 64) {
+      const int left = min(B, kend - k);
+      unsigned long long m = 0;
+      int c = 0;
+      bool in = a.spin >= 0;
+      for (long long i = 0; in; ++i) {
+        m = tid < left ? bk_peek(a.M1 + k + tid) : kBkPlain;
+        c = (int)__builtin_ctzll(~__ballot(m == kBkPlain) | (1ull << 63));
+        const bool posted = c >= left || bk_uniform(__shfl(m != kBkEmpty, c));
+        if (posted) break;
+        if (i >= a.spin ||
+            ((i & 15) == 15 && __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0))
+          in = false;
+        __builtin_amdgcn_s_sleep(1);
+      }
+      c = min(c, left);
+      if (tid == c) s.im = c < left ? (int)(m - 2) : -1;
+      if (tid == 0) {
+        s.cnt = c;
+        if (!in) s.fail = 1;
+      }
+    }
+    bk_barrier();
+    if (failed()) return;
+    const int cnt = bk_uniform(s.cnt), im = bk_uniform(s.im);
+    unsigned long long x[B * U];
+    bool ok = bk_take(x, [&](int i) { return bk_at(a.W + (long)(k + i / U) * n, 8u * (unsigned)col(i % U)); },
+                            [&](int i) { return i / U < cnt && pos[i % U] >= k + i / U; }, a.err, a.spin);
+    if (!ok) s.fail = 1;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int q = 0; q < B; ++q) {
+        if (q < cnt && own[u] >= 0) s.w[q][own[u]] = bk_val(x[q * U + u]);
+        if (q < cnt && pos[u] == k + q) s.d[q] = bk_val(x[q * U + u]);
+      }
+    bk_barrier();
+    if (failed()) return;
+    if (cnt > 0) {
+      if (tid < B * R) {
+        const int q = tid / R, t = tid - q * R;
+        double l = 0.0;
+        if (q < cnt && s.rp[t] > k + q) {
+          const double d = s.d[q];
+          l = d != 0.0 ? s.w[q][t] / d : 0.0;
+          a.Lr[(long)(g + Gw * t) * n + k + q] = l;
+        }
+        s.l[q][t] = l;
+      }
+      bk_barrier();
+#pragma unroll
+      for (int q = 0; q < B; ++q)
+        if (q < cnt) {
+#pragma unroll
+          for (int t = 0; t < R; ++t)
+#pragma unroll
+            for (int u = 0; u < U; ++u) A[t][u] = fma(-s.l[q][t], bk_val(x[q * U + u]), A[t][u]);
+        }
+      k += cnt;
+    }
+    if (im >= 0) {
+      // column and row imax, then the decision
+#pragma unroll
+      for (int t = 0; t < R; ++t)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (pos[u] == im && s.rp[t] >= k) bk_put(a.CI + (long)k * n + g + Gw * t, A[t][u]);
+          if (s.rp[t] == im && pos[u] >= k) bk_put(a.RI + (long)k * n + col(u), A[t][u]);
+        }
+      unsigned long long dec[1], y[2 * U];
+      ok = bk_take(dec, [&](int) { return a.M2 + k; }, [](int) { return true; }, a.err, a.spin);
+      const int kstep = bk_uniform((int)(dec[0] & 3)), kp = bk_uniform((int)(dec[0] >> 2)), kk = k + kstep - 1;
+      ok = ok && bk_take(y, [&](int i) { return bk_at(a.W + (long)(k + i / U) * n, 8u * (unsigned)col(i % U)); },
+                                [&](int i) { return i / U < kstep && pos[i % U] >= k; }, a.err, a.spin);
+      if (!ok) s.fail = 1;
+      bk_loads_done();
+      bk_barrier();   // every thread has read the rows' positions and the last steps' L entries
+      if (failed()) return;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (pos[u] == kk) pos[u] = kp;
+        else if (pos[u] == kp) pos[u] = kk;
+        if (own[u] >= 0) {
+          s.w[0][own[u]] = bk_val(y[u]);
+          s.w[1][own[u]] = bk_val(y[U + u]);
+        }
+        if (pos[u] == k) s.e[0] = bk_val(y[u]);
+        if (pos[u] == k + 1) {
+          s.e[1] = bk_val(y[u]);
+          s.e[2] = bk_val(y[U + u]);
+        }
+      }
+      if (tid < R) {
+        const int r = s.rp[tid];
+        s.rp[tid] = r == kk ? kp : (r == kp ? kk : r);
+      }
+      bk_barrier();
+      if (tid < R) {
+        const int t = tid;
+        double l0 = 0.0, l1 = 0.0;
+        double* Lt = a.Lr + (long)(g + Gw * t) * n + k;
+        if (kstep == 1) {
+          if (s.rp[t] > k) {
+            const double d = s.e[0];
+            l0 = d != 0.0 ? s.w[0][t] / d : 0.0;
+            Lt[0] = l0;
+          }
+        } else {
+          if (s.rp[t] == k + 1) Lt[0] = 0.0;   // L is I on the block
+          if (s.rp[t] > k + 1) {
+            bk_l2(bk_block(s.e[0], s.e[1], s.e[2]), s.w[0][t], s.w[1][t], l0, l1);
+            Lt[0] = l0;
+            Lt[1] = l1;
+          }
+        }
+        s.l[0][t] = l0;
+        s.l[1][t] = l1;
+      }
+      bk_barrier();
+#pragma unroll
+      for (int t = 0; t < R; ++t)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          A[t][u] = fma(-s.l[0][t], bk_val(y[u]), A[t][u]);
+          if (kstep == 2) A[t][u] = fma(-s.l[1][t], bk_val(y[U + u]), A[t][u]);
+        }
+      k += kstep;
+    }
+    if (k >= kend && k < n) {
+      publish(k);
+      kend = min(k + NB, n);
+    }
+  }
+}
+
+template <int U>
+__global__ __launch_bounds__(kBkThreads) void k_bk_coop(BkcArgs a) {
+  __shared__ BkPanelLds<U> sp;
+  __shared__ BkRowsLds<U> sr;
+  if (blockIdx.x == 0) bk_decide<U>(a, sp);
+  else bk_rows_holder<U>(a, sr);
+}
+
+// L by positions: the rows' L entries, unit diagonal, zero above
+__global__ __launch_bounds__(256) void k_bk_coop_l(int n, const double* __restrict__ Lr, const int* __restrict__ perm,
+                                                   double* __restrict__ L) {
+  const int i = blockIdx.x;
+  const double* src = Lr + (long)perm[i] * n;
+  for (int j = threadIdx.x; j < n; j += 256) L[(long)i * n + j] = j < i ? src[j] : (j == i ? 1.0 : 0.0);
 }
 
 __global__ void k_bk_coop_reset(unsigned long long* slots, long count, int* err) {
@@ -533,8 +839,6 @@ __global__ void k_bk_coop_check(int n, const int* err, double* D, int* bsz) {
     bsz[i] = 1;
   }
 }
-
-size_t bk_coop_lds(int n, int G) { return (size_t)(((n + G - 1) / G) + 5L) * n * sizeof(double); }
 
 // X = L^-1 by columns, one wave per column j: x_j = 1 and, for i > j in order,
 // x_i = -sum_{j <= k < i} L[i][k] x_k (forward substitution on L x = e_j).
@@ -650,20 +954,21 @@ rif_status op_prepare_b(rif_ctx* c, int nb, int na, const double* T, const doubl
   const size_t oR = cv.take<int>(1);
   const long npk = (long)nb * (nb + 1) / 2;
   const size_t oBp = cv.take<double>((size_t)n * npk);   // packed solution
-  // the one-launch factorisation where the rows fit the LDS of at most one
-  // workgroup per CU (n_aux up to about 1600), else a pivot and an update
-  // launch per column
+  // the one-launch factorisation where a row fits four elements a thread and the
+  // rows the registers of one workgroup per CU, else a pivot and an update launch
+  // per column
   int G = 0;
-  {
+  if (n <= kBkMaxN) {
     int ncu = 0, coop = 0;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device) == hipSuccess &&
         hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, c->device) == hipSuccess && coop) {
-      G = std::min({ncu, n, 256});
-      if (bk_coop_lds(n, G) > kBkLds) G = 0;
+      G = std::min({ncu, n + 1, 256});
+      if (G < 2 || (n + G - 2) / (G - 1) > bk_rows(bk_u(n))) G = 0;
     }
     (void)hipGetLastError();
   }
-  const size_t oSlots = G ? cv.take<double>((size_t)5 * nn) : 0, oErr = G ? cv.take<int>(1) : 0;
+  const long nslots = 4 * nn + 2 * n;
+  const size_t oSlots = G ? cv.take<double>((size_t)nslots) : 0, oErr = G ? cv.take<int>(1) : 0;
   rif_status st = ws_reserve(c, cv.off);
   if (st) return st;
   char* w = (char*)c->ws;
@@ -685,31 +990,27 @@ rif_status op_prepare_b(rif_ctx* c, int nb, int na, const double* T, const doubl
       ba.n = n;
       ba.G = G;
       ba.Gm = Gm;
-      ba.L = L;
+      ba.Lr = A;
       ba.D = D;
       ba.perm = perm;
       ba.bsz = bsz;
       double* sl = (double*)(w + oSlots);
-      ba.C1 = sl;
-      ba.CI = sl + nn;
-      ba.RK = sl + 2 * nn;
-      ba.RK1 = sl + 3 * nn;
-      ba.RI = sl + 4 * nn;
+      ba.P = sl;
+      ba.W = sl + nn;
+      ba.CI = sl + 2 * nn;
+      ba.RI = sl + 3 * nn;
+      ba.M1 = sl + 4 * nn;
+      ba.M2 = ba.M1 + n;
       ba.err = (int*)(w + oErr);
       ba.spin = c->wait_limit;
-      const size_t lds = bk_coop_lds(n, G);
-      if (lds > 64 * 1024 &&
-          hipFuncSetAttribute((const void*)k_bk_coop, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
-              hipSuccess) {
-        (void)hipGetLastError();
-        return fail(c, RIF_EHIP, "factorisation: LDS attribute failed");
-      }
-      hipLaunchKernelGGL(k_bk_coop_reset, dim3((unsigned)std::min(4096L, (5 * nn + 255) / 256)), dim3(256), 0,
-                         c->stream, (unsigned long long*)sl, 5 * nn, ba.err);
+      hipLaunchKernelGGL(k_bk_coop_reset, dim3((unsigned)std::min(4096L, (nslots + 255) / 256)), dim3(256), 0,
+                         c->stream, (unsigned long long*)sl, nslots, ba.err);
       if ((st = check_launch(c, "prep_factorise_reset"))) return st;
       void* args[] = {&ba};
-      const hipError_t he =
-          hipLaunchCooperativeKernel((const void*)k_bk_coop, dim3(G), dim3(256), args, (unsigned)lds, c->stream);
+      const void* fns[] = {(const void*)k_bk_coop<1>, (const void*)k_bk_coop<2>, (const void*)k_bk_coop<3>,
+                           (const void*)k_bk_coop<4>};
+      const void* fn = fns[bk_u(n) - 1];
+      const hipError_t he = hipLaunchCooperativeKernel(fn, dim3(G), dim3(kBkThreads), args, 0, c->stream);
       if (he != hipSuccess) {
         (void)hipGetLastError();
         return fail(c, RIF_EHIP, std::string("cooperative launch of the factorisation failed: ") +
@@ -717,6 +1018,8 @@ rif_status op_prepare_b(rif_ctx* c, int nb, int na, const double* T, const doubl
       }
       hipLaunchKernelGGL(k_bk_coop_check, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, n,
                          (const int*)ba.err, D, bsz);
+      hipLaunchKernelGGL(k_bk_coop_l, dim3((unsigned)n), dim3(256), 0, c->stream, n, (const double*)A,
+                         (const int*)perm, L);
     } else {
       const unsigned gup = (unsigned)std::min(1024L, (nn + 255) / 256);
       for (int it = 0; it < n; ++it) {
