@@ -841,51 +841,115 @@ __global__ void k_bk_coop_check(int n, const int* err, double* D, int* bsz) {
 }
 
 // X = L^-1 by columns, one wave per column j: x_j = 1 and, for i > j in order,
-// x_i = -sum_{j <= k < i} L[i][k] x_k (forward substitution on L x = e_j).
-// The four waves of a workgroup take four adjacent columns and share each row
-// of L through a double-buffered LDS row: the next row's loads are issued
-// before the current row's dot products and stored after them.  Needs
-// n <= kLinvMaxN (eight row elements per thread).
-constexpr int kLinvMaxN = 2048;
-__global__ __launch_bounds__(256) void k_linv_rows(int n, const double* __restrict__ L, double* __restrict__ X) {
+// x_i = -sum_{j <= k < i} L[i][k] x_k (forward substitution on L x = e_j), lane t
+// summing k = j + t, j + t + 64, ... and wave_sum_dpp the lanes.  x stays in
+// registers: the blocks of 64 that are complete in xr, the one under way in xc.
+// The W waves of a workgroup take adjacent columns and share kLinvStage rows of L
+// at a time through the LDS, the loads of the next two stages in flight meanwhile.  The sums
+// over the complete blocks need none of the stage's own x and go first, so a row's
+// chain is one multiply-add, the wave's sum and the insertion.
+// What bounds it: that chain, n rows long for the first column, and the LDS reads
+// beside it: 410 us at n = 1044; a row at a time with x in the LDS and a barrier
+// each it was 894.
+constexpr int kLinvMaxN = 2048, kLinvStage = 4, kLinvBlocks = kLinvMaxN / 64, kLinvPad = 256;
+inline size_t linv_lds(int n) { return (size_t)2 * kLinvStage * (n + kLinvPad) * sizeof(double); }
+template <int W>
+__global__ __launch_bounds__(64 * W) void k_linv_rows(int n, const double* __restrict__ L, double* __restrict__ X) {
   extern __shared__ double sh[];
-  double* rowbuf = sh;         // [2][n]
-  double* xs = sh + 2L * n;    // [4][n]
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int j0 = blockIdx.x * 4, j = j0 + w;
-  double* x = xs + (long)w * n;
-  for (int k = lane; k < n; k += 64) x[k] = k == j ? 1.0 : 0.0;
-  const int i0 = j0 + 1;
-  if (i0 < n)
-    for (int k = threadIdx.x; k < i0; k += 256) rowbuf[k] = L[(long)i0 * n + k];
+  constexpr int S = kLinvStage, NT = 64 * W, V = W * 256 / NT;   // V: elements a thread loads of a row, n <= 256 W
+  const int NP = n + kLinvPad;   // the last block's group of four reads past the row; what it reads is zero
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, j0 = blockIdx.x * W, j = j0 + w;
+  for (int k = tid; k < 2 * S * NP; k += NT) sh[k] = 0.0;
+  double pa[S][V], pb[S][V];   // the rows of the next two stages, on their way
+  // rows ib .. up to their last chunk of NT left of the diagonal; past the diagonal
+  // a row meets x = 0, left of j0 it is not read
+  auto fetch = [&](double (&pre)[S][V], int ib) {
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+      if (NT * v < ib + S && NT * v < n) {
+        const int k = min(tid + NT * v, n - 1);
+#pragma unroll
+        for (int r = 0; r < S; ++r) pre[r][v] = L[(long)min(ib + r, n - 1) * n + k];
+      }
+  };
+  auto store = [&](const double (&pre)[S][V], int ib, double* buf) {
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+      if (NT * v < ib + S && tid + NT * v < n) {
+#pragma unroll
+        for (int r = 0; r < S; ++r) buf[r * NP + tid + NT * v] = pre[r][v];
+      }
+  };
+  fetch(pa, j0 + 1);
+  fetch(pb, j0 + 1 + S);
   __syncthreads();
-  for (int i = i0; i < n; ++i) {
-    const double* cur = rowbuf + (long)((i - i0) & 1) * n;
-    double* nxt = rowbuf + (long)((i - i0 + 1) & 1) * n;
-    const int in = i + 1;
-    double pre[kLinvMaxN / 256];
+  store(pa, j0 + 1, sh);
+  __syncthreads();
+  double xr[kLinvBlocks], xc = lane == 0 ? 1.0 : 0.0;
 #pragma unroll
-    for (int u = 0; u < kLinvMaxN / 256; ++u) {
-      const int k = threadIdx.x + 256 * u;
-      pre[u] = in < n && k < in ? L[(long)in * n + k] : 0.0;
-    }
-    if (j < n && i > j) {   // whole wave
-      double s = 0.0;
-      for (int k = j + lane; k < i; k += 64) s += cur[k] * x[k];
-      s = wave_sum_dpp(s);
-      if (lane == 0) x[i] = -s;
-    }
+  for (int u = 0; u < kLinvBlocks; ++u) xr[u] = 0.0;
+  int ub = 0;
+  // rows ib .. from one buffer; the next stage's go from next to the other, and
+  // the loads of the one after it start
+  auto stage = [&](int ib, const double* cur, double* other, double (&next)[S][V], double (&after)[S][V]) {
+    fetch(after, ib + 2 * S);
+    const double* row = cur + j + lane;
+    if (j < n && ib + S - 1 > j) {
+      double s[S], c[S];
 #pragma unroll
-    for (int u = 0; u < kLinvMaxN / 256; ++u) {
-      const int k = threadIdx.x + 256 * u;
-      if (in < n && k < in) nxt[k] = pre[u];
+      for (int r = 0; r < S; ++r) {
+        s[r] = 0.0;
+        c[r] = row[r * NP + 64 * ub];
+      }
+#pragma unroll
+      for (int u = 0; u < kLinvBlocks; u += 4) {
+        if (u >= ub) break;
+#pragma unroll
+        for (int v = u; v < u + 4; ++v)
+#pragma unroll
+          for (int r = 0; r < S; ++r) s[r] = fma(row[r * NP + 64 * v], xr[v], s[r]);
+      }
+#pragma unroll
+      for (int r = 0; r < S; ++r) {
+        const int i = ib + r;
+        if (i <= j || i >= n) continue;
+        const double x = -wave_sum_dpp(fma(c[r], xc, s[r]));
+        if (((i - j) & 63) == 0) {   // the block is complete: the rows left here take it before the next
+#pragma unroll
+          for (int u = 0; u < kLinvBlocks; ++u) xr[u] = u == ub ? xc : xr[u];
+          ++ub;
+#pragma unroll
+          for (int q = r + 1; q < S; ++q) {
+            s[q] = fma(c[q], xc, s[q]);
+            c[q] = row[q * NP + 64 * ub];
+          }
+          xc = 0.0;
+        }
+        if (lane == ((i - j) & 63)) xc = x;
+      }
     }
-    __syncthreads();
+    store(next, ib + S, other);
+    bk_barrier();
+  };
+  double* const buf1 = sh + (long)S * NP;
+  for (int ib = j0 + 1; ib < n; ib += 2 * S) {
+    stage(ib, sh, buf1, pb, pa);
+    if (ib + S < n) stage(ib + S, buf1, sh, pa, pb);
   }
-  // columns j0..j0+3 of X, four adjacent doubles per row
-  for (int y = threadIdx.x; y < 4 * n; y += 256) {
-    const int i = y >> 2, c = y & 3;
-    if (j0 + c < n) X[(long)i * n + j0 + c] = xs[(long)c * n + i];
+  // columns j0 .. j0 + W - 1 of X, W adjacent doubles per row
+  if (j < n) {
+    double* xs = sh + (long)w * n;
+    for (int k = lane; k < j; k += 64) xs[k] = 0.0;
+#pragma unroll
+    for (int u = 0; u < kLinvBlocks; ++u) {
+      const int i = j + lane + 64 * u;
+      if (i < n) xs[i] = u == ub ? xc : xr[u];
+    }
+  }
+  __syncthreads();
+  for (int y = tid; y < W * n; y += NT) {
+    const int i = y / W, c = y % W;
+    if (j0 + c < n) X[(long)i * n + j0 + c] = sh[(long)c * n + i];
   }
 }
 
@@ -1036,14 +1100,17 @@ rif_status op_prepare_b(rif_ctx* c, int nb, int na, const double* T, const doubl
     hipLaunchKernelGGL(k_bk_correct, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, n, D, bsz, del,
                        delta, Dih, nr);
     if (n <= kLinvMaxN) {
-      const size_t lds = (size_t)6 * n * sizeof(double);
+      // four columns a workgroup while that fills no more than the 256 CUs
+      const bool four = n <= 1024;
+      const void* fn = four ? (const void*)k_linv_rows<4> : (const void*)k_linv_rows<8>;
+      const size_t lds = linv_lds(n);
       if (lds > 64 * 1024 &&
-          hipFuncSetAttribute((const void*)k_linv_rows, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
-              hipSuccess) {
+          hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
         (void)hipGetLastError();
         return fail(c, RIF_EHIP, "L^-1: LDS attribute failed");
       }
-      hipLaunchKernelGGL(k_linv_rows, dim3((unsigned)((n + 3) / 4)), dim3(256), lds, c->stream, n, L, X);
+      if (four) hipLaunchKernelGGL(k_linv_rows<4>, dim3((unsigned)((n + 3) / 4)), dim3(256), lds, c->stream, n, L, X);
+      else hipLaunchKernelGGL(k_linv_rows<8>, dim3((unsigned)((n + 7) / 8)), dim3(512), lds, c->stream, n, L, X);
     } else {
       for (int k = 0; k + 1 < n; ++k) {
         const long work = (long)(n - k - 1) * (k + 1);
