@@ -33,6 +33,7 @@
 #include <string>
 
 #include "rif_internal.hpp"
+#include "strip64.hpp"
 #include "wave.hpp"
 
 namespace rif {
@@ -953,57 +954,146 @@ __global__ __launch_bounds__(64 * W) void k_linv_rows(int n, const double* __res
   }
 }
 
-// The solve works on the upper triangle of each slab only (T and b are
-// symmetric in mu, nu), with the slabs in pivot order: packed by rows,
-// Tp[i][o(mu) + nu - mu] = T[perm[i]][mu][nu] for nu >= mu,
-// o(mu) = mu nb - mu (mu - 1) / 2, so that b^T = M' Tp with M' = D~^(-1/2) L^-1
-// (the (P^T T)[i] = T[perm[i]] of the solve).  One workgroup per (i, mu) row,
-// grid-strided; reads and writes both run along nu.
-__global__ __launch_bounds__(256) void k_pack_upper(int nb, long rows, const double* __restrict__ T,
-                                                    const int* __restrict__ perm, double* __restrict__ Tp) {
-  const long npk = (long)nb * (nb + 1) / 2;
-  for (long rr = blockIdx.x; rr < rows; rr += gridDim.x) {
-    const long k = rr / nb;
-    const int mu = (int)(rr - k * nb);
-    const double* src = T + ((long)perm[k] * nb + mu) * nb;
-    double* dst = Tp + k * npk + (long)mu * nb - (long)mu * (mu - 1) / 2 - mu;
-    for (int nu = mu + threadIdx.x; nu < nb; nu += 256) dst[nu] = src[nu];
-  }
+// ---- the solve ---------------------------------------------------------------
+// b[k] = sum_i M'[k][i] T[perm[i]], a product over i whose columns are the pairs
+// (mu, nu): T and b are symmetric in them, so 8 x 16 blocks (mu x nu) with an
+// element on or above the diagonal are computed and stored both ways.  Rows k run in
+// tiles of up to 128 on the strip loop; a tile stops at the k past which its rows
+// of M' are zero.  An LDS load of the loop holds one row i of the 128 columns, so
+// the pivot order is a scalar base per load and T is read where it lies.
+//
+// What bounds it: the matrix cores (n_aux^2 x 128 flops a block).  Before, T was
+// packed in pivot order (240 us at n_bf 348, n_aux 1044), multiplied (1690) and the
+// packed result spread over b (430): PREPGEMM us in one pass here.
+struct SolveArgs {
+  int n, nb;
+  const double* Mt;   // [n][n] M'^T
+  const double* T;    // [n][nb][nb]
+  const int* perm;
+  double* b;          // [n][nb][nb]
+  int rows, nrt;      // rows k a tile (multiple of 16), row tiles
+  long nblk;          // column blocks
+};
+using SolveCfg = StripCfg<128, 8>;
+constexpr int kSolveMu = 8, kSolveNu = 16;
+
+// Column blocks by strips of 8 mu: strip r has the nu blocks from that of 8 r on.
+__host__ __device__ __forceinline__ int solve_cols(int nb) { return (pair_len(nb) + kSolveNu - 1) / kSolveNu; }
+__host__ __device__ __forceinline__ long solve_blocks(int nb) {
+  const int nr = (nb + kSolveMu - 1) / kSolveMu, nc = solve_cols(nb);
+  long s = 0;
+  for (int r = 0; r < nr; ++r) s += nc - r / 2;
+  return s;
 }
-// b[k] from the packed solution, by 64x64 tiles (rb <= cb) of each slab: the
-// tile's upper-triangle elements are read once along c into LDS and written
-// to (r, c) and, through the LDS transpose, to (c, r), both along rows.
-constexpr int kUT = 64;
-__global__ __launch_bounds__(256) void k_unpack_sym(int nb, long ntiles, const double* __restrict__ bp,
-                                                    double* __restrict__ b) {
-  __shared__ double t[kUT][kUT + 1];
-  const long npk = (long)nb * (nb + 1) / 2;
-  const int nbt = (nb + kUT - 1) / kUT, per = nbt * (nbt + 1) / 2;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (long tt = blockIdx.x; tt < ntiles; tt += gridDim.x) {
-    const long k = tt / per;
-    int rem = (int)(tt - k * per), rb = 0;
-    while (rem >= nbt - rb) { rem -= nbt - rb; ++rb; }
-    const int cb = rb + rem, r0 = rb * kUT, c0 = cb * kUT;
-    const double* src = bp + k * npk;
-    double* dst = b + k * (long)nb * nb;
-    __syncthreads();
-    for (int y = ty; y < kUT; y += 4) {
-      const int r = r0 + y, cc = c0 + tx;
-      if (r < nb && cc < nb && cc >= r) t[y][tx] = src[(long)r * nb - (long)r * (r - 1) / 2 + (cc - r)];
-    }
-    __syncthreads();
-    for (int y = ty; y < kUT; y += 4) {
-      const int r = r0 + y, cc = c0 + tx;   // (r, cc) from the upper triangle: itself or its mirror
-      if (r < nb && cc < nb) dst[(long)r * nb + cc] = cc >= r ? t[y][tx] : t[tx][y];
-    }
-    if (rb != cb) {
-      for (int y = ty; y < kUT; y += 4) {
-        const int r = c0 + y, cc = r0 + tx;   // lower tile (cb, rb): element (r, cc) = upper (cc, r)
-        if (r < nb && cc < nb) dst[(long)r * nb + cc] = t[tx][y];
+
+template <class L>
+struct SolveStage {
+  StripStage<L> st;   // its A loads; the B loads' bases are set here
+  const double* T;
+  const int* perm;
+  long slab;
+  int n;
+  __device__ __forceinline__ void issue(lds_char* dst, int kt) {
+#pragma unroll
+    for (int i = 0; i < L::NU; ++i) {
+      const int u = st.w + i * L::NW;
+      if (u >= L::NIA && st.have(i)) {
+        const int k = min(16 * kt + u - L::NIA, n - 1);   // rows past n: replaced by zeros in st.issue
+        st.base[i] = (const char*)(T + slab * perm[__builtin_amdgcn_readfirstlane(k)]);
       }
     }
+    st.issue(dst, n - 16 * kt);
   }
+};
+
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_prep_solve(SolveArgs a) {
+  __shared__ __attribute__((aligned(16))) char smem[strip_smem<SolveCfg>()];
+  const int n = a.n, nb = a.nb;
+  // the row tiles of a column block on one die, the longest first
+  long blk;
+  int rt;
+  {
+    const long t = blockIdx.x, per = (long)8 * a.nrt, full = a.nblk / 8 * per;
+    if (t < full) {
+      blk = t / per * 8 + t % 8;
+      rt = (int)(t % per / 8);
+    } else {
+      blk = a.nblk / 8 * 8 + (t - full) / a.nrt;
+      rt = (int)((t - full) % a.nrt);
+    }
+    rt = a.nrt - 1 - rt;
+  }
+  int r = 0;
+  const int nc = solve_cols(nb);
+  {
+    // strips 2 j and 2 j + 1 have nc - j blocks each
+    long rem = blk;
+    int j = 0;
+    while (rem >= 2l * (nc - j)) rem -= 2l * (nc - j++);
+    r = 2 * j;
+    if (rem >= nc - j) { rem -= nc - j; ++r; }
+    blk = rem + j;
+  }
+  const int mu0 = r * kSolveMu, nu0 = (int)blk * kSolveNu, m0 = rt * a.rows;
+  const int plen = pair_len(n), ncol = pair_len(nb);
+  const int tm = (min(a.rows, plen - m0) + 15) / 16;
+  with_frags(tm, [&](auto frags) {
+    using L = Strip<SolveCfg, decltype(frags)::value>;
+    SolveStage<L> ld;
+    ld.T = a.T;
+    ld.perm = a.perm;
+    ld.slab = (long)nb * nb;
+    ld.n = n;
+    ld.st.init(
+        a.Mt, n, [&](int x) { return pair_start(min(m0 + x, plen - 2), n); }, a.T, 0,
+        [&](int x) {
+          return min(mu0 + x / kSolveNu, nb - 1) * nb + pair_start(min(nu0 + x % kSolveNu, ncol - 2), nb);
+        });
+    StripAcc<L> acc;
+    // M' is zero right of its first superdiagonal
+    const int K = min(n, m0 + L::BM + 1);
+    strip_mainloop<L>((K + 15) / 16, ld.st.w, acc, smem, [&](int kt, lds_char* dst) { ld.issue(dst, kt); });
+    // b[k][mu][nu] from the registers, b[k][nu][mu] through the LDS, a row of
+    // fragments at a time: 8 mu of a nu lie together
+    const int lane = threadIdx.x & 63;
+    double* sh = (double*)smem;
+    constexpr int RI = 16 * L::WVM, MS = kSolveNu + 1, RS = kSolveMu * MS;
+    static_assert(RI * RS * 8 <= strip_smem<SolveCfg>(), "LDS of the transposition");
+#pragma unroll
+    for (int i = 0; i < L::FM; ++i) {
+      const int mrow = acc.wm + 16 * i, g = L::WVM == 2 && acc.wm ? 16 : 0;
+#pragma unroll
+      for (int j = 0; j < L::FN; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int q = (lane >> 4) + 4 * e, x = acc.wn + 16 * j + (lane & 15);
+          const int k = m0 + mrow + q < plen ? pair_column(m0 + mrow + q, n) : -1;
+          const int mu = mu0 + x / kSolveNu, nu = nu0 + x % kSolveNu < ncol ? pair_column(nu0 + x % kSolveNu, nb) : -1;
+          if (k >= 0 && mu < nb && nu >= mu) a.b[((long)k * nb + mu) * nb + nu] = acc.v[i][j][e];
+          sh[(g + q) * RS + x / kSolveNu * MS + x % kSolveNu] = acc.v[i][j][e];
+        }
+      __syncthreads();
+      for (int y = threadIdx.x; y < RI * 128; y += SolveCfg::NT) {
+        const int q = y >> 7, nup = (y >> 3) & 15, mu = mu0 + (y & 7);
+        const int m = m0 + (q >= 16 ? L::FM * 16 : 0) + 16 * i + (q & 15);
+        const int k = m < plen ? pair_column(m, n) : -1, nu = nu0 + nup < ncol ? pair_column(nu0 + nup, nb) : -1;
+        if (k >= 0 && mu < nb && nu > mu) a.b[((long)k * nb + nu) * nb + mu] = sh[q * RS + (y & 7) * MS + nup];
+      }
+      __syncthreads();
+    }
+  });
+}
+
+// A single pair or a single function, which the loads by pairs do not take.
+__global__ __launch_bounds__(256) void k_prep_solve_small(int n, long npair, const double* __restrict__ Mt,
+                                                          const double* __restrict__ T, const int* __restrict__ perm,
+                                                          double* __restrict__ b) {
+  const long e = (long)blockIdx.x * 256 + threadIdx.x;
+  if (e >= n * npair) return;
+  const long k = e / npair, x = e - k * npair;
+  double s = 0.0;
+  for (int i = 0; i < n; ++i) s = fma(Mt[(long)i * n + k], T[perm[i] * npair + x], s);
+  b[e] = s;
 }
 
 rif_status op_prepare_b(rif_ctx* c, int nb, int na, const double* T, const double* Gm, double delta,
@@ -1016,8 +1106,6 @@ rif_status op_prepare_b(rif_ctx* c, int nb, int na, const double* T, const doubl
   const size_t oP = cv.take<int>(n), oB = cv.take<int>(n), oS = cv.take<BkState>(1);
   const size_t oPart = cv.take<double>((size_t)n), oDel = cv.take<double>(1);
   const size_t oR = cv.take<int>(1);
-  const long npk = (long)nb * (nb + 1) / 2;
-  const size_t oBp = cv.take<double>((size_t)n * npk);   // packed solution
   // the one-launch factorisation where a row fits four elements a thread and the
   // rows the registers of one workgroup per CU, else a pivot and an update launch
   // per column
@@ -1123,23 +1211,25 @@ rif_status op_prepare_b(rif_ctx* c, int nb, int na, const double* T, const doubl
   }
   {
     ProfScope ps(c, "prep_solve_gemm");
-    // b^T[k][mu nu] = sum_i M'[k][i] T[perm[i]][mu nu] on the packed upper
-    // triangles (A operand M'^T, i-major; B the packed T in pivot order,
-    // staged in b's own buffer, which is free until the unpacking writes it),
-    // then mirrored into b
-    double* Tp = b;
-    double* bp = (double*)(w + oBp);
-    const long rows = (long)n * nb;
-    const unsigned g = (unsigned)std::min(rows, 65536L);
-    hipLaunchKernelGGL(k_pack_upper, dim3(g), dim3(256), 0, c->stream, nb, rows, T, (const int*)perm, Tp);
-    if ((st = check_launch(c, "prep_pack"))) return st;
-    // M' is zero right of its first superdiagonal: row tile m0 needs k < m0 + BM + 1 only
-    if ((st = op_gemm_big(c, n, (int)npk, n, Mt, n, Tp, npk, bp, npk, true))) return st;
-    const int nbt = (nb + kUT - 1) / kUT;
-    const long ntiles = (long)n * (nbt * (nbt + 1) / 2);
-    hipLaunchKernelGGL(k_unpack_sym, dim3((unsigned)std::min(ntiles, 65536L)), dim3(256), 0, c->stream, nb, ntiles,
-                       (const double*)bp, b);
-    if ((st = check_launch(c, "prep_unpack"))) return st;
+    if (n < 2 || nb < 2) {
+      const long ne = (long)n * nb * nb;
+      hipLaunchKernelGGL(k_prep_solve_small, dim3((unsigned)((ne + 255) / 256)), dim3(256), 0, c->stream, n,
+                         (long)nb * nb, (const double*)Mt, T, (const int*)perm, b);
+    } else {
+      SolveArgs sa{};
+      sa.n = n;
+      sa.nb = nb;
+      sa.Mt = Mt;
+      sa.T = T;
+      sa.perm = perm;
+      sa.b = b;
+      sa.nblk = solve_blocks(nb);
+      // 128 rows a tile; 64 where that leaves CUs without their two workgroups
+      sa.rows = sa.nblk * ((n + 127) / 128) >= 512 ? 128 : 64;
+      sa.nrt = (pair_len(n) + sa.rows - 1) / sa.rows;
+      hipLaunchKernelGGL(k_prep_solve, dim3((unsigned)(sa.nblk * sa.nrt)), dim3(SolveCfg::NT), 0, c->stream, sa);
+    }
+    if ((st = check_launch(c, "prep_solve"))) return st;
   }
   if (perm_out && hipMemcpyAsync(perm_out, perm, sizeof(int) * n, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
     return fail(c, RIF_EHIP, "copying perm failed");

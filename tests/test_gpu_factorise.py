@@ -63,3 +63,30 @@ def test_factorisation_backward_error(ctx, n, kind):
     err = np.abs(G[np.ix_(perm, perm)] - L @ D @ L.T)
     bound = 8 * n * U * (np.abs(L) @ np.abs(D) @ np.abs(L).T)
     assert np.all(err <= bound), (err / np.maximum(bound, 1e-300)).max()
+
+
+@pytest.mark.parametrize("n,n_bf", [(1, 1), (1, 5), (2, 2), (3, 1), (3, 3), (15, 16), (16, 17), (17, 15), (31, 8),
+                                    (64, 9), (65, 33), (127, 24), (129, 31), (144, 48), (257, 50), (300, 113)])
+def test_solve_matches_float64(ctx, n, n_bf):
+    """The solve at the edges of its tiles (rows of 16 to 128, blocks of 8 x 16
+    pairs, odd sizes).  With X = L^-1, computed by substitution, the inverse is
+    wrong by at most c n u |X| |L| |X| and the sum over i by n u |M'| |T|, which is
+    no larger: 8 n u of the first bounds both and the reference's own rounding."""
+    import torch
+    print("case solve:", n, n_bf, flush=True)
+    rng = np.random.default_rng(7 * n + n_bf)
+    G = rng.standard_normal((n, n)) * (0.3 / n ** 0.5)
+    G = np.diag(rng.uniform(0.5, 2.0, n)) + (G + G.T) * 0.2
+    T = rng.standard_normal((n, n_bf, n_bf))
+    T = T + T.transpose(0, 2, 1)
+    b, perm, L, D, nr = ctx.prepare_b(torch.from_numpy(T).cuda(), torch.from_numpy(G).cuda(), factors=True)
+    ctx.sync()
+    b, perm, L, D = b.cpu().numpy(), perm.cpu().numpy(), L.cpu().numpy(), D.cpu().numpy()
+    d = np.diagonal(D)
+    assert int(nr.cpu()[0]) == 0 and np.array_equal(D, np.diag(d)) and np.all(d > 0)
+    X = np.linalg.inv(L)
+    Tp = T[perm].reshape(n, -1)
+    ref = ((X / np.sqrt(d)[:, None]) @ Tp).reshape(b.shape)
+    bound = 8 * n * U * (np.abs(X) @ np.abs(L) @ np.abs(X) / np.sqrt(d)[:, None]) @ np.abs(Tp)
+    assert np.all(np.abs(b - ref).reshape(n, -1) <= np.maximum(bound, 8 * U * np.abs(Tp).max()))
+    assert np.array_equal(b, b.transpose(0, 2, 1))
