@@ -964,7 +964,8 @@ __global__ __launch_bounds__(64 * W) void k_linv_rows(int n, const double* __res
 //
 // What bounds it: the matrix cores (n_aux^2 x 128 flops a block).  Before, T was
 // packed in pivot order (240 us at n_bf 348, n_aux 1044), multiplied (1690) and the
-// packed result spread over b (430): PREPGEMM us in one pass here.
+// packed result spread over b (430): 1570 us in one pass here, at 74% of
+// the cycles in matrix instructions.
 struct SolveArgs {
   int n, nb;
   const double* Mt;   // [n][n] M'^T
@@ -993,14 +994,19 @@ struct SolveStage {
   const int* perm;
   long slab;
   int n;
-  __device__ __forceinline__ void issue(lds_char* dst, int kt) {
+  int p, next;   // perm of the 64 rows under way and the next 64, one a lane
+  // rows past n: replaced by zeros in st.issue
+  __device__ __forceinline__ int rows64(int k0) const { return perm[min(k0 + (int)(threadIdx.x & 63), n - 1)]; }
+  __device__ __forceinline__ void issue(lds_char* dst, int kt) {   // called for kt = 0, 1, 2, ...
+    if (kt % 4 == 0) {
+      p = next;
+      next = rows64(16 * kt + 64);
+    }
 #pragma unroll
     for (int i = 0; i < L::NU; ++i) {
       const int u = st.w + i * L::NW;
-      if (u >= L::NIA && st.have(i)) {
-        const int k = min(16 * kt + u - L::NIA, n - 1);   // rows past n: replaced by zeros in st.issue
-        st.base[i] = (const char*)(T + slab * perm[__builtin_amdgcn_readfirstlane(k)]);
-      }
+      if (u >= L::NIA && st.have(i))
+        st.base[i] = (const char*)(T + slab * __builtin_amdgcn_readlane(p, kt % 4 * 16 + u - L::NIA));
     }
     st.issue(dst, n - 16 * kt);
   }
@@ -1009,20 +1015,10 @@ struct SolveStage {
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_prep_solve(SolveArgs a) {
   __shared__ __attribute__((aligned(16))) char smem[strip_smem<SolveCfg>()];
   const int n = a.n, nb = a.nb;
-  // the row tiles of a column block on one die, the longest first
-  long blk;
-  int rt;
-  {
-    const long t = blockIdx.x, per = (long)8 * a.nrt, full = a.nblk / 8 * per;
-    if (t < full) {
-      blk = t / per * 8 + t % 8;
-      rt = (int)(t % per / 8);
-    } else {
-      blk = a.nblk / 8 * 8 + (t - full) / a.nrt;
-      rt = (int)((t - full) % a.nrt);
-    }
-    rt = a.nrt - 1 - rt;
-  }
+  // the longest row tiles first: the tiles in flight share their rows of M', and
+  // the short ones fill the end
+  long blk = blockIdx.x % a.nblk;
+  const int rt = a.nrt - 1 - (int)(blockIdx.x / a.nblk);
   int r = 0;
   const int nc = solve_cols(nb);
   {
@@ -1044,6 +1040,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
     ld.perm = a.perm;
     ld.slab = (long)nb * nb;
     ld.n = n;
+    ld.next = ld.rows64(0);
     ld.st.init(
         a.Mt, n, [&](int x) { return pair_start(min(m0 + x, plen - 2), n); }, a.T, 0,
         [&](int x) {
