@@ -110,6 +110,10 @@ struct OnView {
   int* weak;
 };
 
+// Problems that k_on_opt_small takes
+constexpr int kOnSmall = 128;
+__host__ __device__ inline bool on_small(const OnProblem& P) { return P.n_omega <= kOnSmall; }
+
 // E(x) and dE/dx for the problem; writes n, dn and gout.  Returns E.
 __device__ double on_eval(const OnView& v, const double* x, double* gout, double* red) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -195,6 +199,7 @@ __device__ double dot(const double* a, const double* b, int n, double* red) {
 __global__ __launch_bounds__(kOnThreads) void k_on_opt(const OnProblem* __restrict__ probs) {
   __shared__ double red[kOnThreads];
   const OnProblem& P = probs[blockIdx.x];
+  if (on_small(P)) return;
   const int tid = threadIdx.x;
   OnView v;
   v.nw = P.n_omega; v.npairs = P.n_pairs; v.ncwo = P.n_cwo; v.nv = P.n_pairs * P.n_cwo;
@@ -324,6 +329,431 @@ __global__ __launch_bounds__(kOnThreads) void k_on_opt(const OnProblem* __restri
     *P.iters = it;
     *P.status = status;
   }
+}
+
+// ---- up to 128 orbitals in Omega ----------------------------------------------
+// The same optimisation, every sum in the order of k_on_opt, with one problem in
+// the registers and the LDS of eight waves:
+//   - J and K stay in registers for the whole run (rows p = wave + 8 r, columns
+//     lane and lane + 64);
+//   - sines and cosines of the variables are taken once an evaluation, a variable
+//     per thread, and so are the square roots and the quotient of a row and the
+//     intra-pair terms, a pair of orbitals per thread;
+//   - the row sums of eight rows are taken together (lane swaps halve the values
+//     with each of the first two steps);
+//   - L-BFGS runs in wave 0 with its vectors in registers, so that a scalar product
+//     is six additions across the lanes and no barrier.
+// What bounds it: the chain of an evaluation (six barriers) and of the recursion.
+// k_on_opt takes a workgroup barrier for every step of every sum, and the sines and
+// cosines of the derivatives again for each product: 2430 -> 600 us for 200
+// problems of up to 112 orbitals.
+constexpr int kOnSmallThreads = 512, kOnSmallWaves = kOnSmallThreads / 64;
+constexpr int kOnRows = kOnSmall / kOnSmallWaves;
+
+struct OnLds {
+  double x[kOnSmall], cs[kOnSmall], sn[kOnSmall], w[kOnSmall], g[kOnSmall];
+  double n[kOnSmall], ph[kOnSmall], dphp[kOnSmall], dn[kOnSmall], row[kOnSmall];
+  double S[kHist][kOnSmall], Y[kHist][kOnSmall], rho[kHist];
+  double te[kOnSmall * (kKmax + 9)], td[kOnSmall * (kKmax + 9)];   // intra-pair terms [p][member of p's pair]
+  int weak[kOnSmall], pair[kOnSmall], slot[kOnSmall];
+  int bad, odd, done;
+};
+
+// lane ^ 4: rows of 16 lanes moved up by 4 and down by 4, each where it applies
+__device__ __forceinline__ int lane_xor4(int x) {
+  const int up = __builtin_amdgcn_update_dpp(x, x, 0x104, 0xF, 0x5, false);      // row_shl:4 into banks 0, 2
+  return __builtin_amdgcn_update_dpp(up, x, 0x114, 0xF, 0xA, false);             // row_shr:4 into banks 1, 3
+}
+// v + (v of lane ^ 8), then ^ 4, ^ 2, ^ 1
+__device__ __forceinline__ double sum_in_row(double v) {
+  v += dpp_move<0x128>(v);   // row_ror:8
+  const long long u = __double_as_longlong(v);
+  v += __longlong_as_double(((long long)lane_xor4((int)(u >> 32)) << 32) | (unsigned)lane_xor4((int)u));
+  v += dpp_move<0x4E>(v);    // quad_perm [2,3,0,1]
+  return v + dpp_move<0xB1>(v);
+}
+// a + (a of lane ^ kDist) in the lanes without the bit, b + ... in those with it
+template <bool kHalves>
+__device__ __forceinline__ double sum_two(double a, double b) {
+  const long long u = __double_as_longlong(a), w = __double_as_longlong(b);
+  const auto l = kHalves ? __builtin_amdgcn_permlane32_swap((unsigned)u, (unsigned)w, false, false)
+                         : __builtin_amdgcn_permlane16_swap((unsigned)u, (unsigned)w, false, false);
+  const auto h = kHalves ? __builtin_amdgcn_permlane32_swap((unsigned)(u >> 32), (unsigned)(w >> 32), false, false)
+                         : __builtin_amdgcn_permlane16_swap((unsigned)(u >> 32), (unsigned)(w >> 32), false, false);
+  return __longlong_as_double(((long long)h[0] << 32) | (unsigned)l[0]) +
+         __longlong_as_double(((long long)h[1] << 32) | (unsigned)l[1]);
+}
+// The sum over the lanes in the order of block_sum's tree below 64: ^ 32, 16, 8, 4, 2, 1.
+__device__ __forceinline__ double tree_sum(double v) {
+  v = sum_two<true>(v, v);
+  v = sum_two<false>(v, v);
+  return sum_in_row(v);
+}
+
+// The factors of K_pq in e and dsum for q in p's pair
+__device__ __forceinline__ void pair_term(int p, int q, int npairs, double np, double nq, double& te, double& td) {
+  const double sg = (p >= npairs && q >= npairs) ? 1.0 : -1.0;
+  te = p == q ? np : sg * sqrt(np * nq);
+  td = p == q ? 0.0 : 2.0 * sg * 0.5 * sqrt(nq / fmax(np, 1e-300));
+}
+
+// A product that is rounded before it is added, as k_on_opt's compiled sums have it.
+__device__ __forceinline__ double rounded_product(double a, double b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+// q's terms in p's row: those of another pair, and of p's own
+__device__ __forceinline__ void other_terms(int functional, double np, double php, double dphp, double nq, double phq,
+                                            double J, double K, double& e, double& ds) {
+  double bb = -np * nq, db = -nq;
+  if (functional == RIF_PNOF7) {
+    bb = fma(-php, phq, bb);
+    db = fma(-dphp, phq, db);
+  }
+  e += fma(2.0 * np * nq, J, rounded_product(bb, K));
+  ds = fma(2.0, fma(2.0 * nq, J, rounded_product(db, K)), ds);
+}
+__device__ __forceinline__ void own_terms(double te, double td, double K, double& e, double& ds) {
+  e += rounded_product(te, K);
+  ds = fma(td, K, ds);
+}
+
+struct OnRegs {
+  double J[kOnRows][2], K[kOnRows][2];
+};
+
+// dn and the energy rows at s.x, then the gradient in s.g; every thread gets E.
+__device__ __forceinline__ double on_eval_small(const OnProblem& P, OnLds& s, const OnRegs& r) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nw = P.n_omega, npairs = P.n_pairs, m = P.n_cwo, nv = npairs * m;
+  if (tid < nv) s.cs[tid] = cos(s.x[tid]);
+  else if (tid >= 256 && tid - 256 < nv) s.sn[tid - 256] = sin(s.x[tid - 256]);
+  __syncthreads();
+  if (tid < npairs) {
+    const double* cs = s.cs + tid * m;
+    const double* sn = s.sn + tid * m;
+    const double ng = 0.5 * (1.0 + cs[0] * cs[0]);
+    s.n[tid] = ng;
+    double q = 1.0;
+    for (int k = 0; k < m; ++k) {
+      const double w = k < m - 1 ? q * cs[1 + k] * cs[1 + k] : q;
+      s.w[tid * m + k] = w;
+      s.n[s.weak[tid * m + k]] = (1.0 - ng) * w;
+      if (k < m - 1) q *= sn[1 + k] * sn[1 + k];
+    }
+  }
+  __syncthreads();
+  if (tid < nw) {
+    const double np = s.n[tid], ph = sqrt(np * (1.0 - np));
+    s.ph[tid] = ph;
+    s.dphp[tid] = (1.0 - 2.0 * np) / (2.0 * fmax(ph, 1e-300));
+  }
+  const bool odd = s.odd;   // a strong orbital outside its pair: the members are not the table's
+  for (int t = tid; t < nw * (m + 1) && !odd; t += kOnSmallThreads) {
+    const int p = t / (m + 1), j = t - p * (m + 1), gp = s.pair[p];
+    const int q = j == 0 ? gp : s.weak[gp * m + j - 1];
+    const double np = s.n[p], nq = s.n[q];
+    pair_term(p, q, npairs, np, nq, s.te[t], s.td[t]);
+  }
+  __syncthreads();
+  double nq[2], phq[2];
+  int gq[2], sq[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const int q = lane + 64 * c;
+    nq[c] = q < nw ? s.n[q] : 0.0;
+    phq[c] = q < nw ? s.ph[q] : 0.0;
+    gq[c] = q < nw ? s.pair[q] : -1;
+    sq[c] = q < nw ? s.slot[q] : 0;
+  }
+  if (odd) {
+    for (int p = wave; p < nw; p += kOnSmallWaves) {
+      const double np = s.n[p], php = s.ph[p], dphp = s.dphp[p];
+      double e = 0.0, ds = 0.0;
+      for (int c = 0; c < 2; ++c) {
+        const int q = lane + 64 * c;
+        if (q >= nw) continue;
+        const double Jpq = P.J[(long)p * nw + q], Kpq = P.K[(long)p * nw + q];
+        if (s.pair[p] == gq[c]) {
+          double te, td;
+          pair_term(p, q, npairs, np, nq[c], te, td);
+          own_terms(te, td, Kpq, e, ds);
+        } else {
+          other_terms(P.functional, np, php, dphp, nq[c], phq[c], Jpq, Kpq, e, ds);
+        }
+      }
+      e = tree_sum(e);
+      ds = tree_sum(ds);
+      if (lane == 0) {
+        s.dn[p] = 2.0 * P.Hpp[p] + P.K[(long)p * nw + p] + ds;
+        s.row[p] = 2.0 * np * P.Hpp[p] + e;
+      }
+    }
+  }
+#pragma unroll
+  for (int r0 = 0; r0 < kOnRows; r0 += 8) {
+    if (odd || wave + kOnSmallWaves * r0 >= nw) break;
+    double e[8], ds[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int p = min(wave + kOnSmallWaves * (r0 + i), nw - 1), gp = s.pair[p];
+      const double np = s.n[p], php = s.ph[p], dphp = s.dphp[p];
+      e[i] = ds[i] = 0.0;
+      asm volatile("" ::: "memory");   // no row's reads ahead of the last row's: the registers hold J and K
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const double Jpq = r.J[r0 + i][c], Kpq = r.K[r0 + i][c];
+        const bool same = gp == gq[c];
+        const int t = p * (m + 1) + (same ? sq[c] : 0);
+        const double te = s.te[t], td = s.td[t];
+        double eo = e[i], dso = ds[i], ei = e[i], di = ds[i];
+        other_terms(P.functional, np, php, dphp, nq[c], phq[c], Jpq, Kpq, eo, dso);
+        own_terms(te, td, Kpq, ei, di);
+        if (gq[c] >= 0) {
+          e[i] = same ? ei : eo;
+          ds[i] = same ? di : dso;
+        }
+      }
+    }
+    // values 4 j + {0, 2, 1, 3} in the rows of 16 lanes of v[j]: e of rows 0 - 7, then ds
+    double v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const double* src = j < 2 ? e + 4 * j : ds + 4 * (j - 2);
+      v[j] = sum_in_row(sum_two<false>(sum_two<true>(src[0], src[1]), sum_two<true>(src[2], src[3])));
+    }
+    if ((lane & 15) == 0) {
+      const int i = ((lane >> 4 & 1) << 1) | (lane >> 5);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int p = wave + kOnSmallWaves * (r0 + 4 * j + i);
+        if (p < nw) {
+          const double Hp = P.Hpp[p];
+          s.dn[p] = 2.0 * Hp + P.K[(long)p * nw + p] + v[2 + j];
+          s.row[p] = 2.0 * s.n[p] * Hp + v[j];
+        }
+      }
+    }
+  }
+  __syncthreads();
+  // rows p = j, j + 4, ... in order for j = 0 .. 3, then (0 + 2) + (1 + 3)
+  double E = 0.0;
+  for (int p = lane & 3; p < nw; p += 4) E += s.row[p];
+  E += dpp_move<0x4E>(E);
+  E += dpp_move<0xB1>(E);
+  if (tid < nv) {
+    const int g = tid / m, j = tid - g * m;
+    const double* cs = s.cs + g * m;
+    const double* sn = s.sn + g * m;
+    const double c = cs[0], si = sn[0];
+    if (j == 0) {
+      const double dh = c * si;
+      double t = -c * si * s.dn[g];
+      for (int k = 0; k < m; ++k) t += dh * s.w[g * m + k] * s.dn[s.weak[g * m + k]];
+      s.g[tid] = t;
+    } else {
+      const double h = 0.5 * si * si;
+      double u = 0.0;
+      for (int k = 0; k < m; ++k) {
+        double v = 0.0;
+        if (k == m - 1 || j - 1 <= k) {
+          v = 1.0;
+          for (int i = 0; i < (k < m - 1 ? k : m - 1); ++i)
+            v *= (i == j - 1) ? 2.0 * sn[1 + i] * cs[1 + i] : sn[1 + i] * sn[1 + i];
+          if (k < m - 1) v *= (j - 1 == k) ? -2.0 * cs[1 + k] * sn[1 + k] : cs[1 + k] * cs[1 + k];
+        }
+        u += h * v * s.dn[s.weak[g * m + k]];
+      }
+      s.g[tid] = u;
+    }
+  }
+  __syncthreads();
+  return E;
+}
+
+__global__ __launch_bounds__(kOnSmallThreads) void k_on_opt_small(const OnProblem* __restrict__ probs) {
+  __shared__ OnLds s;
+  const OnProblem& P = probs[blockIdx.x];
+  if (!on_small(P)) return;   // k_on_opt's
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nw = P.n_omega, npairs = P.n_pairs, m = P.n_cwo, nv = npairs * m;
+  if (tid == 0) s.bad = s.odd = s.done = 0;
+  for (int i = tid; i < nv; i += kOnSmallThreads) s.weak[i] = 0;
+  __syncthreads();
+  for (int p = tid; p < nw; p += kOnSmallThreads) {
+    const int g = on_pair(P.pair_of, p, npairs, m);
+    s.pair[p] = g;
+    s.slot[p] = 0;
+    if (p < npairs && g != p) s.odd = 1;
+  }
+  __syncthreads();
+  if (tid < npairs) {
+    int k = 0;
+    for (int p = npairs; p < nw; ++p)
+      if (s.pair[p] == tid) {
+        if (k < m) {
+          s.weak[tid * m + k] = p;
+          s.slot[p] = 1 + k;
+        }
+        ++k;
+      }
+    if (k != m) s.bad = 1;
+  }
+  if (tid < nv) s.x[tid] = P.gamma[tid];
+  __syncthreads();
+  if (s.bad) {
+    if (tid == 0) { *P.status = 3; *P.iters = 0; }
+    return;
+  }
+  OnRegs r;
+#pragma unroll
+  for (int i = 0; i < kOnRows; ++i)
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int p = min(wave + kOnSmallWaves * i, nw - 1), q = min(lane + 64 * c, nw - 1);
+      r.J[i][c] = P.J[(long)p * nw + q];
+      r.K[i][c] = P.K[(long)p * nw + q];
+    }
+  // Wave 0 keeps the vectors, elements lane and lane + 64; the others only evaluate.
+  double x[2], g[2], d[2], alpha[kHist];
+  double E = 0.0, step = 1.0, gd = 0.0;
+  int it = 0, hist = 0, head = 0, status = 1, ls = 0, stage = 0;   // stage: first point, line search, final point
+#pragma unroll
+  for (int c = 0; c < 2; ++c) x[c] = wave == 0 && lane + 64 * c < nv ? s.x[lane + 64 * c] : 0.0;
+  auto dot = [&](const double (&a)[2], const double (&b)[2]) {
+    double t[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) t[c] = fma(a[c], b[c], 0.0);
+    return tree_sum(t[0] + t[1]);
+  };
+  auto load = [&](const double* v, double (&out)[2]) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) out[c] = lane + 64 * c < nv ? v[lane + 64 * c] : 0.0;
+  };
+  while (true) {
+    const double En = on_eval_small(P, s, r);
+    if (wave == 0) {
+      double xn[2], gn[2];
+      load(s.x, xn);
+      load(s.g, gn);
+      bool top = stage == 0, stop = false;
+      if (stage == 1) {
+        const double epsE = 1e-12 * fabs(E);
+        bool ok = En <= E + 1e-4 * step * gd;
+        if (!ok && En <= E + epsE) {
+          const double gnd = dot(gn, d);
+          ok = gnd >= 0.9 * gd && gnd <= -0.8 * gd;
+        }
+        if (ok) {
+          double sy[2], t[2];
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            sy[c] = xn[c] - x[c];
+            t[c] = gn[c] - g[c];
+            if (lane + 64 * c < nv) {
+              s.S[head][lane + 64 * c] = sy[c];
+              s.Y[head][lane + 64 * c] = t[c];
+            }
+          }
+          const double q = dot(sy, t);
+          if (q > 1e-300) {
+            if (lane == 0) s.rho[head] = 1.0 / q;
+            head = (head + 1) % kHist;
+            hist = hist < kHist ? hist + 1 : kHist;
+          }
+          ++it;
+          top = true;
+        } else {
+          step *= 0.5;
+          if (++ls == 50) { status = 2; stop = true; }
+        }
+      }
+      if (top) {
+        E = En;
+        double gm = 0.0;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          x[c] = xn[c];
+          g[c] = gn[c];
+          gm = fmax(gm, fabs(g[c]));
+        }
+        gm = wave_max_dpp(gm);
+        if (gm <= P.tol) { status = 0; stop = true; }
+        else if (it >= P.max_it) { status = 1; stop = true; }
+        else {
+          // two-loop recursion: d = -H g
+#pragma unroll
+          for (int c = 0; c < 2; ++c) d[c] = g[c];
+#pragma unroll
+          for (int j = 0; j < kHist; ++j)
+            if (j < hist) {
+              const int h = (head - 1 - j + kHist) % kHist;
+              double S[2], Y[2];
+              load(s.S[h], S);
+              load(s.Y[h], Y);
+              const double a = s.rho[h] * dot(S, d);
+              alpha[j] = a;
+#pragma unroll
+              for (int c = 0; c < 2; ++c) d[c] -= a * Y[c];
+            }
+          double scale;
+          if (hist > 0) {
+            const int h = (head - 1 + kHist) % kHist;
+            double Y[2];
+            load(s.Y[h], Y);
+            scale = 1.0 / (s.rho[h] * dot(Y, Y));
+          } else {
+            scale = fmin(1.0, 1.0 / gm);
+          }
+#pragma unroll
+          for (int c = 0; c < 2; ++c) d[c] *= scale;
+#pragma unroll
+          for (int j = kHist - 1; j >= 0; --j)
+            if (j < hist) {
+              const int h = (head - 1 - j + kHist) % kHist;
+              double S[2], Y[2];
+              load(s.S[h], S);
+              load(s.Y[h], Y);
+              const double b = s.rho[h] * dot(Y, d), a = alpha[j];
+#pragma unroll
+              for (int c = 0; c < 2; ++c) d[c] += (a - b) * S[c];
+            }
+#pragma unroll
+          for (int c = 0; c < 2; ++c) d[c] = -d[c];
+          gd = dot(g, d);
+          if (!(gd < 0.0)) {   // not a descent direction: restart from steepest descent
+#pragma unroll
+            for (int c = 0; c < 2; ++c) d[c] = -g[c] * fmin(1.0, 1.0 / gm);
+            hist = 0;
+            gd = dot(g, d);
+          }
+          step = 1.0;
+          ls = 0;
+          stage = 1;
+        }
+      }
+      // the next point: along d, or the final one once more so that n matches x
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        if (lane + 64 * c < nv) s.x[lane + 64 * c] = stop ? x[c] : x[c] + step * d[c];
+      if (stage == 2) {
+        E = En;
+        if (lane == 0) {
+          s.done = 1;
+          *P.energy = E;
+          *P.iters = it;
+          *P.status = status;
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+          if (lane + 64 * c < nv) P.gamma[lane + 64 * c] = x[c];
+      }
+      if (stop) stage = 2;
+    }
+    __syncthreads();
+    if (s.done) break;
+  }
+  for (int p = tid; p < nw; p += kOnSmallThreads) P.occ[p] = s.n[p];
 }
 
 // ---- features, targets and warm start ------------------------------------
@@ -891,7 +1321,10 @@ rif_status op_on_optimize(rif_ctx* c, int n, const OnProblem* probs) {
   rif_status st = upload_problems(c, n, probs, &d);
   if (st) return st;
   ProfScope ps(c, "on_opt");
-  hipLaunchKernelGGL(k_on_opt, dim3(n), dim3(kOnThreads), 0, c->stream, d);
+  bool small = false, large = false;
+  for (int i = 0; i < n; ++i) (on_small(probs[i]) ? small : large) = true;
+  if (small) hipLaunchKernelGGL(k_on_opt_small, dim3(n), dim3(kOnSmallThreads), 0, c->stream, d);
+  if (large) hipLaunchKernelGGL(k_on_opt, dim3(n), dim3(kOnThreads), 0, c->stream, d);
   return check_launch(c, "on_opt");
 }
 
