@@ -298,7 +298,8 @@ rif_status rif_hpp(rif_ctx *ctx, int n_bf, int n_mo, int n_omega, const double *
                    double *Hpp);
 /* L-BFGS (history 8; backtracking with the Armijo test, or the approximate
  * Wolfe conditions once energy changes are below rounding noise) in FP64, one
- * workgroup per problem, all problems in one launch.  probs is a HOST array
+ * workgroup per problem; one launch for the problems with up to 128 orbitals in
+ * Omega, one for the larger.  probs is a HOST array
  * (copied). */
 rif_status rif_on_optimize(rif_ctx *ctx, int n_prob, const rif_on_problem *probs);
 /* Per-pair MLP features X [rows][39] (optionally standardised: (x - mu)/sigma
@@ -454,7 +455,9 @@ rif_status rif_pnof_optimize(rif_ctx *ctx, const rif_instance *inst, rif_prec pr
 
 /* Tile-shape selection for the MFMA kernels.  Each GEMM-shaped kernel has up
  * to four tile variants (0: 128x128, 1: 64x64, 2: 128x64, 3: 64x128 outputs
- * per workgroup).  mode 0 picks one per shape with a wave-quantisation
+ * per workgroup; in FP64 the half transform, J^q, K^q and the Fock step have
+ * two, 0: 128 and 1: 64 columns by up to 128 rows, as many as n_omega asks for,
+ * and the MO transform one).  mode 0 picks one per shape with a wave-quantisation
  * model; mode 1 (autotune) times every variant on the first call with a new
  * shape -- synchronising the stream once -- and reuses the fastest for that
  * shape afterwards.  Results are identical to FP64 rounding across variants. */
