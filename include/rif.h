@@ -337,19 +337,19 @@ rif_status rif_adam(rif_ctx *ctx, int n, float *theta, const float *grad, float 
  *   P L D~^(1/2) b^T = T,  T[k][mu nu] = (mu nu|k),
  * is solved: b^T = D~^(-1/2) L^-1 P^T T.  Then sum_k b^k b^k = T^T G~^-1 T with
  * G~ = P L D~ L^T P^T (= G if nothing was raised).  Device pointers:
- *   T [n_aux][n_bf][n_bf] (symmetric in mu, nu: only nu >= mu is read),
+ *   T [n_aux][n_bf][n_bf] (symmetric in mu, nu: only nu >= mu is used),
  *   G [n_aux][n_aux] symmetric
- *   b [n_aux][n_bf][n_bf] out, exactly symmetric in mu, nu (the solve runs on
- *   the packed upper triangles; b's buffer also stages them)
+ *   b [n_aux][n_bf][n_bf] out, exactly symmetric in mu, nu (the solve computes
+ *   the upper triangles and stores them both ways); must not overlap T
  *   optional (NULL to skip): perm [n_aux] (P^T x)[i] = x[perm[i]]; L and D
  *   [n_aux][n_aux] dense; n_raised: number of raised eigenvalues
  * delta <= 0 takes 2^-26 * max_k sum_l |G_kl|.  The factorisation runs as
- * one cooperative launch where the metric's rows fit the LDS of at most 256
- * workgroups (n_aux up to about 1600; its waits are bounded by
+ * one cooperative launch where the metric's rows fit the registers of at most
+ * 256 workgroups (n_aux up to 2048; its waits are bounded by
  * rif_set_wait_limit, and a timed-out one leaves b all NaN), else as a pivot
- * and an update launch per column.  Uses 6 n_aux^2 + n_aux n_bf (n_bf + 1) / 2
- * doubles of the context arena, plus 5 n_aux^2 for the one-launch
- * factorisation's exchange slots.  Asynchronous.  RIF_EINVAL for sizes
+ * and an update launch per column.  Uses 6 n_aux^2 doubles of the context
+ * arena, plus 4 n_aux^2 + 2 n_aux for the one-launch factorisation's exchange
+ * slots.  Asynchronous.  RIF_EINVAL for sizes
  * (n_aux < 46341) or NULL T, G, b. */
 rif_status rif_prepare_b(rif_ctx *ctx, int n_bf, int n_aux, const double *T, const double *G, double delta,
                          double *b, int *perm, double *L, double *D, int *n_raised);
