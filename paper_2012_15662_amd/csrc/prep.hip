@@ -298,7 +298,7 @@ __global__ __launch_bounds__(256) void k_compose(int n, const double* __restrict
 //     pivot test, the L entries, and the update of the columns left in the panel.
 //     A step costs it one workgroup barrier and no exchange.
 //   - Each step's pivot column goes out as W[k], the kind of step as M1[k].  The
-//     row holders take the steps of a panel four at a time as they appear, form
+//     row holders take the steps of a panel two at a time as they appear, form
 //     their rows' L entries from W and update their rows: rank-one updates in the
 //     order of the steps, as a step at a time would do them.
 //   - Where the first pivot test fails, M1[k] asks for column imax (CI) and row
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(256) void k_compose(int n, const double* __restrict
 //
 // What bounds it: the chain of n steps in workgroup 0 (barrier, two reductions, a
 // division: 1.1 us at n = 1044) and one exchange to the row holders and back a
-// panel (8 us).  1.9 ms at n = 1044 where no interchange is needed and 5 where
+// panel (7 us).  1.8 ms at n = 1044 where no interchange is needed and 5 where
 // most columns need the second test, 1.5 and 4.4 at n = 1020; with an exchange of
 // each column between all workgroups at every step it was 4.2 and 6.8.  512
 // threads: with 1024 the panel does not fit the registers above n = 1024, with 256
@@ -321,7 +321,8 @@ __global__ __launch_bounds__(256) void k_compose(int n, const double* __restrict
 // no arithmetic.
 constexpr unsigned long long kBkEmpty = 0x7FF4C0FFEE5E7F11ull;   // signalling NaN
 constexpr int kBkThreads = 512, kBkWaves = kBkThreads / 64;
-constexpr int kBkBatch = 4;    // steps the row holders take at once
+constexpr int kBkBatch = 2;    // steps the row holders take at once: 4 are 1 us later at a panel's end, 3 half
+                               // of that (preparation at n = 1044: 3866, 3829, 3787 us with 4, 3, 2)
 constexpr int kBkMaxN = 4 * kBkThreads;
 // For rows of up to 512 U elements: the positions of a panel (U times that in
 // doubles a thread) and the rows a workgroup holds, at most (n / 255 rounded up).
