@@ -1,12 +1,10 @@
 // FP64 GEMM out[m][n] = sum_k A[k][m] B[k][n] (both operands k-major, row
 // strides lda, ldb, ldo) with the tile shape chosen per problem.  It serves the
-// large one-off product outside the build, the solve of the b preparation
-// (n_aux x n_bf(n_bf+1)/2 x n_aux), where the build's fixed 64x64 small-GEMM
-// tile leaves MFMA time unused.  With lower_a, A is zero past its first
-// superdiagonal (A[k][m] = 0 for k > m + 1) and each row tile stops its k range
-// there, so only exact zeros are skipped.  Same engine,
-// loader and main loop as the build's GEMM steps (mfma_engine.hpp); tiles run
-// m-fastest, so consecutive workgroups share the panel of B.
+// large one-off product outside the build, the four-centre integrals from b
+// (n_bf (n_bf + 1) / 2 x n_bf^2 x n_aux), where the build's fixed small-GEMM tiles
+// leave MFMA time unused.  Same engine, loader and main loop as the build's GEMM
+// steps (mfma_engine.hpp); tiles run m-fastest, so consecutive workgroups share the
+// panel of B.
 #include <algorithm>
 
 #include "mfma_engine.hpp"
@@ -23,7 +21,6 @@ struct BigGemm {
   long ldb;
   double* out;
   long ldo;
-  int lower;   // A[k][m] = 0 for k > m + 1: a row tile m0 stops at k = m0 + BM + 1
 };
 
 using E64 = EngineOf<kF64>::type;
@@ -48,7 +45,7 @@ k_gemm_big(BigGemm a) {
   const int nmt = (a.M + Cfg::BM - 1) / Cfg::BM;
   const int m0 = (int)(t % nmt) * Cfg::BM, n0 = (int)(t / nmt) * Cfg::BN;
   const int M = a.M, N = a.N;
-  const int K = a.lower ? min(a.K, m0 + Cfg::BM + 1) : a.K;   // only exact zeros are skipped
+  const int K = a.K;
   XCSrc<double, Cfg::BM, E64::BK, Cfg::NT, E64::KV> la;
   la.init(a.A, a.lda, K, [&](int x, long& o) { o = m0 + x; return m0 + x < M; });
   XCSrc<double, Cfg::BN, E64::BK, Cfg::NT, E64::KV> lb;
@@ -84,8 +81,8 @@ double big_cost(const BigGemm& a) {
 }  // namespace
 
 rif_status op_gemm_big(rif_ctx* c, int M, int N, int K, const double* A, long lda, const double* B, long ldb,
-                       double* out, long ldo, bool lower_a) {
-  const BigGemm a{M, N, K, A, lda, B, ldb, out, ldo, lower_a ? 1 : 0};
+                       double* out, long ldo) {
+  const BigGemm a{M, N, K, A, lda, B, ldb, out, ldo};
   auto run = [&](int v) -> rif_status {
     return with_big(v, [&](auto cfg) {
       using Cfg = decltype(cfg);
@@ -99,7 +96,7 @@ rif_status op_gemm_big(rif_ctx* c, int M, int N, int K, const double* A, long ld
     const double e = with_big(v, [&](auto cfg) { return big_cost<decltype(cfg)>(a); });
     if (e < best) { best = e; hv = v; }
   }
-  const int v = pick_variant(c, "gemm", {M, N, K, lower_a ? 1 : 0}, kBigVariants, hv, run);
+  const int v = pick_variant(c, "gemm", {M, N, K, 0}, kBigVariants, hv, run);
   if (v < 0) return RIF_EHIP;
   ProfScope ps(c, "gemm");
   return run(v);
