@@ -19,8 +19,9 @@
 //                above 2048 auxiliary functions
 //   k_compose    M'^T[i][k] = sum_r D~^(-1/2)[k][r] X[r][i]  (M' = D~^(-1/2) L^-1,
 //                zero right of its first superdiagonal)
-//   then b^T = M T on the FP64 MFMA GEMM (tile chosen per shape), over the packed upper triangles of
-//   the slabs (k_pack_upper before, k_unpack_sym after).
+//   k_prep_solve b^T = M T from T to b, on the 8 x 16 blocks of (mu, nu) with an
+//                element on or above the diagonal (k_prep_solve_small: a single
+//                function or pair)
 //
 // Pivot rule (alpha = (1 + sqrt 17)/8) at column k, with colmax/imax the
 // largest |A_ik| below the diagonal (lowest index on ties) and rowmax the
