@@ -96,10 +96,8 @@ struct Planes { const unsigned short* p; long ps; int ld; };
 struct HalfArgs {
   int nb, nw, nmo; long nr; const double* b; const double* C; void* bh; Planes Cs; Planes Bs; const float* bf;
 };
-// The FP64 strip tiles stage column pairs (two columns at least) at 32-bit
-// offsets (fifteen rows of a slab's width from the tile's first element); the
-// 64 x 64 tile staged through registers takes what is left.
-inline bool strip_fits(int nb, int nmo, int nw) { return nb >= 2 && nw >= 2 && nb < 5900 && nmo < 5900; }
+// FP64 operands that strips do not take (strip_fits) go to the 64 x 64 tile staged
+// through registers.
 // b pre-split once per call: element (r, mu) = b[r*n_bf + mu] (row r = l*n_bf + nu;
 // b symmetric) into the mode's pieces, rows zero-filled from n_bf up to ld;
 // FP32 mode: a float copy.
@@ -635,12 +633,6 @@ __device__ __forceinline__ bool up_block(long r, int nb, int tmu, int& mu0, int&
   nu0 = (jao_first_col(bi, tmu, kJaoTNU) + (int)r) * kJaoTNU;
   return true;
 }
-// Offset of the pair at (even) tile column x from the operand's start: row
-// mu0 + x / 16, position nu0 + x % 16 (odd n_bf: the last pair one early).
-__device__ __forceinline__ long up_offset(int x, int mu0, int nu0, int nb) {
-  const int mu = mu0 + x / kJaoTNU, p = nu0 + x % kJaoTNU;
-  return mu < nb && p < nb ? (long)mu * nb + pair_start(p, nb) : 0;
-}
 // FP64 J^q on strip tiles.  The mirrored half goes through LDS (a row's TMU
 // elements of one nu side by side) so that a store instruction writes whole
 // 64-byte pieces: written straight from the accumulators, one 8-byte element
@@ -659,7 +651,7 @@ __device__ __forceinline__ void jao_strip(const JaoArgs& a, long t, char* smem) 
     using L = Strip<Cfg, decltype(frags)::value>;
     StripStage<L> st;
     st.init(a.d, nw, [&](int x) -> long { return q0 + x < nw ? pair_start(q0 + x, nw) : 0; },
-            a.b, B2, [&](int x) -> long { return up_offset(x, mu0, nu0, nb); });
+            a.b + (long)mu0 * nb, B2, [&](int x) -> long { return block_offset(x, mu0, nu0, nb); });
     StripAcc<L> acc;
     strip_mainloop(cdiv(na, 16), st.w, acc, smem, [&](int kt, lds_char* s) { st.issue(s, na - 16 * kt); });
     const int kr = (threadIdx.x & 63) >> 4, xc = threadIdx.x & 15, nu = pair_column(nu0 + xc, nb);
@@ -1237,7 +1229,7 @@ __device__ __forceinline__ void fock_strip(const FockArgs& a, long t, char* smem
   const long blk = t / nqt;
   if (!up_block(blk, nb, TMU, mu0, nu0)) return;
   const int q0 = (int)(t % nqt) * 16 * tm;
-  const long B2 = (long)nb * nb;
+  const long B2 = (long)nb * nb, row0 = (long)mu0 * nb;
   double* Pr = a.Yp + blk * TMU * nw;
   double* Pc = a.Yp + jao_active(nb, TMU, kJaoTNU) * TMU * nw + blk * 16 * nw;
   with_frags(tm, [&](auto frags) {
@@ -1245,10 +1237,10 @@ __device__ __forceinline__ void fock_strip(const FockArgs& a, long t, char* smem
     StripStage<L> st;
     // A and B are symmetric: row t of either holds the coefficients of slab t along q
     st.init(a.Ac, nw, [&](int x) -> long { return q0 + x < nw ? pair_start(q0 + x, nw) : 0; },
-            (const double*)a.Jn, B2, [&](int x) -> long { return up_offset(x, mu0, nu0, nb); });
+            (const double*)a.Jn + row0, B2, [&](int x) -> long { return block_offset(x, mu0, nu0, nb); });
     StripAcc<L> acc;
     strip_mainloop(2 * nks, st.w, acc, smem, [&](int kt, lds_char* s) {
-      if (kt == nks) st.rebase(a.Bc, (const double*)a.Kn);
+      if (kt == nks) st.rebase(a.Bc, (const double*)a.Kn + row0);
       st.issue(s, nw - 16 * (kt < nks ? kt : kt - nks));
     });
     const int lane = threadIdx.x & 63, kr = lane >> 4, xc = lane & 15, nu = pair_column(nu0 + xc, nb);

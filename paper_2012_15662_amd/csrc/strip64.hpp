@@ -85,9 +85,36 @@ __device__ __forceinline__ void with_frags(int tm, F&& f) {
   else if constexpr (TM > 1) with_frags<TM - 1>(tm, f);
 }
 
+// Byte offset of lane's part of 1 KB load u of a stage from its operand's base (A of
+// row stride lda for u < NIA, else B); fa(x) / fb(x) as in StripStage.
+template <class L, class FA, class FB>
+__host__ __device__ __forceinline__ long strip_offset(int u, int lane, long lda, FA fa, long ldb, FB fb) {
+  const bool isA = u < L::NIA;
+  const int v = (isA ? u : u - L::NIA) * 64 + lane;
+  const int k = isA ? v / (L::BM / 2) : v / (L::BN / 2);
+  int x = 2 * (isA ? v % (L::BM / 2) : v % (L::BN / 2));
+  if ((!isA || L::TM % 2 == 0) && (k & 1)) x ^= 16;
+  return 8 * ((isA ? fa(x) : fb(x)) + k * (isA ? lda : ldb));
+}
+
+// Whether the FP64 build steps' operands are staged by strips: column pairs (two
+// columns at least) at lane offsets of 32 bits.  The farthest are those of a slab
+// per k row (J^q, Fock): 15 slabs and a block's rows, 8 (15 n_bf^2 + 8 n_bf) bytes,
+// below 2^32 up to n_bf = 5982.
+inline bool strip_fits(int nb, int nmo, int nw) { return nb >= 2 && nw >= 2 && nb < 5900 && nmo < 5900; }
+
+// The pair at (even) column x of the block of (mu, nu) that starts at row mu0 and
+// position nu0 (16 nu a row): its offset from element (mu0, 0) of the slab, in
+// doubles (odd n_bf: the last pair one early).  Pairs that are not there read
+// that row's first.
+__host__ __device__ __forceinline__ long block_offset(int x, int mu0, int nu0, int nb) {
+  const int m = x / 16, p = nu0 + x % 16;
+  return mu0 + m < nb && p < nb ? (long)m * nb + pair_start(p, nb) : 0;
+}
+
 // Direct-load staging of both operands.  fa(x) / fb(x): offset of the (even)
 // tile column x from A / B in doubles; offsets plus 15 rows must fit 32 bits of
-// bytes.
+// bytes, so whatever a tile's lanes share goes into A / B.
 template <class L>
 struct StripStage {
   unsigned off[L::NU];
@@ -101,13 +128,8 @@ struct StripStage {
 #pragma unroll
     for (int i = 0; i < L::NU; ++i) {
       const int u = w + i * L::NW;
-      const bool isA = u < L::NIA;
-      const int v = (isA ? u : u - L::NIA) * 64 + lane;
-      const int k = isA ? v / (L::BM / 2) : v / (L::BN / 2);
-      int x = 2 * (isA ? v % (L::BM / 2) : v % (L::BN / 2));
-      if ((!isA || L::TM % 2 == 0) && (k & 1)) x ^= 16;
-      off[i] = 8u * (unsigned)((isA ? fa(x) : fb(x)) + k * (isA ? lda : ldb));
-      inc[i] = 128 * (isA ? lda : ldb);
+      off[i] = (unsigned)strip_offset<L>(u, lane, lda, fa, ldb, fb);
+      inc[i] = 128 * (u < L::NIA ? lda : ldb);
     }
     rebase(A, B);
   }
