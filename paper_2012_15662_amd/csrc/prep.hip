@@ -978,7 +978,7 @@ struct SolveArgs {
   long nblk;          // column blocks
 };
 using SolveCfg = StripCfg<128, 8>;
-constexpr int kSolveMu = 8, kSolveNu = 16;
+constexpr int kSolveMu = 8, kSolveNu = 16;   // (the blocks of block_offset)
 
 // Column blocks by strips of 8 mu: strip r has the nu blocks from that of 8 r on.
 __host__ __device__ __forceinline__ int solve_cols(int nb) { return (pair_len(nb) + kSolveNu - 1) / kSolveNu; }
@@ -1038,16 +1038,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
   with_frags(tm, [&](auto frags) {
     using L = Strip<SolveCfg, decltype(frags)::value>;
     SolveStage<L> ld;
-    ld.T = a.T;
+    ld.T = a.T + (long)mu0 * nb;   // (a slab may pass 2^32 bytes, a lane's offset from the block's first row not)
     ld.perm = a.perm;
     ld.slab = (long)nb * nb;
     ld.n = n;
     ld.next = ld.rows64(0);
     ld.st.init(
-        a.Mt, n, [&](int x) { return pair_start(min(m0 + x, plen - 2), n); }, a.T, 0,
-        [&](int x) {
-          return min(mu0 + x / kSolveNu, nb - 1) * nb + pair_start(min(nu0 + x % kSolveNu, ncol - 2), nb);
-        });
+        a.Mt, n, [&](int x) -> long { return pair_start(min(m0 + x, plen - 2), n); }, a.T, 0,
+        [&](int x) { return block_offset(x, mu0, nu0, nb); });
     StripAcc<L> acc;
     // M' is zero right of its first superdiagonal
     const int K = min(n, m0 + L::BM + 1);

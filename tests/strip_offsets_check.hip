@@ -52,6 +52,8 @@ int main() {
     step<StripCfg<128, 8>>("J^q, Fock", nb, true);
     step<StripCfg<64, 4>>("J^q, 64 columns", nb, true);
   }
+  // the preparation's solve: one slab in the base of each load, n_bf^2 up to 2^30
+  for (int nb : {2, 3, 16, 17, 23170, 23171, 32767, 32768}) step<StripCfg<128, 8>>("solve", nb, false);
   printf("%ld checks, %ld failures\n", n_check, n_fail);
   return n_fail != 0;
 }

@@ -1,7 +1,8 @@
 """FP64 steps at the largest slabs that strip tiles take, where 16 rows of one n_bf^2
 slab each reach the end of 32-bit offsets: a build at odd n_bf 5795 with 17
 auxiliary functions and 16 orbitals (two k slices in J^q, one in each half of the
-Fock step), against plain torch products in FP64.
+Fock step), against plain torch products in FP64; and the preparation's solve where
+one slab passes 2^32 bytes.
 
 Tolerance: chains of FP64 contractions of at most n_bf terms, each rounding at most
 2^-53 of its sum of magnitudes: normwise 1e-11 covers them with a factor of 10 and
@@ -62,4 +63,26 @@ def test_build_at_the_largest_slabs():
         assert err(o["Kn"][q], Kq) < TOL, ("Kn", q)
         Y += Jq @ (C * A[:, q]) + Kq @ (C * B[:, q])
     assert err(o["lam"], C.T @ Y) < TOL
+    ctx.close()
+
+
+def test_prepare_with_slabs_past_32_bits():
+    import torch
+    import paper_2012_15662_amd as rif
+    nb, n = 23201, 3
+    print(f"case prepare n_bf {nb}, n_aux {n}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(6)
+    T = torch.empty((n, nb, nb), dtype=torch.float64, device="cuda")
+    for k in range(n):
+        T[k] = symmetric(nb, 1.0, gen)
+    G = np.array([[4.0, 0.5, -0.25], [0.5, 3.0, 0.75], [-0.25, 0.75, 2.0]])   # no interchange: b^T = chol(G)^-1 T
+    M = np.linalg.inv(np.linalg.cholesky(G))
+    ctx = rif.Context()
+    b = ctx.prepare_b(T, torch.from_numpy(G).cuda())
+    ctx.sync()
+    for k in range(n):
+        for r in range(0, nb, 2048):
+            ref = sum(float(M[k, i]) * T[i, r:r + 2048] for i in range(n))
+            assert err(b[k, r:r + 2048], ref) < 1e-13, (k, r)
     ctx.close()
