@@ -255,7 +255,8 @@ rif_status rif_build_direct(rif_ctx *ctx, const rif_instance *inst, rif_prec pre
  * the batch's own workspace and uploads a work-list per step; it chooses
  * each step's tile variant for the batch as a whole (timing the candidates if
  * autotuning is on).  rif_batch_run enqueues one persistent grouped launch per
- * step covering all molecules; with use_graph != 0 the first run captures the
+ * step covering all molecules (in RIF_FP64 a second one for the molecules whose
+ * sizes rif_build gives another kernel); with use_graph != 0 the first run captures the
  * sequence in a hipGraph on the context's stream and every run replays it.
  * The instance pointers are baked into the plan: keep them valid and
  * unchanged while the batch lives.  Results for each molecule equal

@@ -2755,11 +2755,15 @@ rif_status op_build_direct(rif_ctx* c, int prec, int functional, const rif_insta
 // Batched builds of many molecules.  Every step is one persistent grouped
 // launch over a work-list spanning all molecules (largest molecules first, so
 // the small ones fill the tail), each step's tile variant chosen for the
-// batch as a whole.  The launch sequence can be captured in a hipGraph once
+// batch as a whole.  In FP64 a molecule's kernel (strips or not) is the one that
+// rif_build gives it, so a step can take two launches: with every molecule on the
+// register-staged tile as soon as one was below the MO transform's line, 16
+// molecules of n_bf 60 - 400 took 5277 us, now 5000.  The launch sequence can be captured in a hipGraph once
 // and replayed; nothing in it allocates or sets memory.
 
 struct GroupStep {
   std::string name;
+  int n = 0;                 // molecules
   int nvar = 1;              // tile variants available (1 for fixed steps)
   int variant = 0;
   void* args_d = nullptr;    // device array of per-molecule argument blocks
@@ -2775,6 +2779,9 @@ struct BatchImpl {
   void* ws = nullptr;        // workspace of all molecules
   std::vector<void*> dev;    // device allocations to free
   GroupStep psc, psd, half, halfp, mo, jkp, jkr, jao, kao, hc, coef, energy, fock, fred, lam, grad;
+  // FP64: the molecules that a step's strip tiles do not take, on the register-staged
+  // tile in a launch of their own, as rif_build has them
+  GroupStep half_r, mo_r, jao_r, kao_r, fock_r;
   bool bpre = false;         // every molecule's b pre-split (grouped halfp in place of half)
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -2788,17 +2795,16 @@ static void group_offsets(const std::vector<Args>& a, TilesFn tiles, std::vector
 
 #define RIF_GROUP_SETUP(NAME, ARGS, LABEL, NV64, NVO)                                                      \
   template <int P>                                                                                         \
-  static rif_status setup_##NAME(BatchImpl* B, const std::vector<ARGS>& a) {                              \
+  static rif_status setup_##NAME(BatchImpl* B, GroupStep& g, const std::vector<ARGS>& a) {                \
     constexpr int NVAR = P == kF64 ? NV64 : NVO;                                                           \
-    GroupStep& g = B->NAME;                                                                                \
     g.name = LABEL;                                                                                        \
     g.nvar = NVAR;                                                                                         \
-    const int n = (int)a.size();                                                                           \
+    const int n = g.n = (int)a.size();                                                                     \
     std::vector<long> offs((size_t)NVAR * (n + 1));                                                        \
     g.total.assign(NVAR, 0);                                                                               \
     g.grid.assign(NVAR, 0);                                                                                \
     for (int v = 0; v < NVAR; ++v) {                                                                       \
-      dispatch_##NAME<P>(v, [&](auto cfg) {                                                                       \
+      dispatch_##NAME<P>(v, [&](auto cfg) {                                                                \
         using Cfg = decltype(cfg);                                                                         \
         long acc = 0;                                                                                      \
         for (int i = 0; i < n; ++i) {                                                                      \
@@ -2811,6 +2817,7 @@ static void group_offsets(const std::vector<Args>& a, TilesFn tiles, std::vector
         return 0;                                                                                          \
       });                                                                                                  \
     }                                                                                                      \
+    if (n == 0) return RIF_OK;                                                                             \
     if (hipMalloc(&g.args_d, sizeof(ARGS) * n) != hipSuccess ||                                           \
         hipMalloc((void**)&g.off_d, sizeof(long) * offs.size()) != hipSuccess)                            \
       return fail(B->c, RIF_ENOMEM, "batch: device allocation failed");                                    \
@@ -2822,11 +2829,11 @@ static void group_offsets(const std::vector<Args>& a, TilesFn tiles, std::vector
     return RIF_OK;                                                                                         \
   }                                                                                                        \
   template <int P>                                                                                         \
-  static rif_status launch_##NAME(BatchImpl* B, int v) {                                                   \
+  static rif_status launch_##NAME(BatchImpl* B, const GroupStep& g, int v) {                              \
     constexpr int NVAR = P == kF64 ? NV64 : NVO;                                                           \
-    GroupStep& g = B->NAME;                                                                                \
-    const int n = B->n;                                                                                    \
-    return dispatch_##NAME<P>(v, [&](auto cfg) {                                                                  \
+    const int n = g.n;                                                                                     \
+    if (n == 0) return RIF_OK;                                                                             \
+    return dispatch_##NAME<P>(v, [&](auto cfg) {                                                           \
       using Cfg = decltype(cfg);                                                                           \
       if constexpr (P != kF64 && NVAR == 2 && Cfg::BM != Cfg::BN) {                                        \
         return fail(B->c, RIF_ENOTSUP, LABEL ": non-square tile variant");                                 \
@@ -2967,21 +2974,38 @@ static rif_status batch_setup(BatchImpl* B, const std::vector<BuildArgs>& A) {
     return fail(B->c, RIF_EINVAL, "batch: give b_split for every molecule or for none");
   B->bpre = npre > 0;
   if constexpr (P != kF64) {
-    if (B->bpre && (st = setup_halfp<P>(B, half))) return st;
+    if (B->bpre && (st = setup_halfp<P>(B, B->halfp, half))) return st;
+  } else {
+    // each molecule's kernels are those that rif_build gives it
+    auto part = [](auto& a, auto&& strip) {
+      std::decay_t<decltype(a)> s, rest;
+      for (auto& x : a) (strip(x) ? s : rest).push_back(x);
+      a.swap(s);
+      return rest;
+    };
+    const auto half_r = part(half, [](const HalfArgs& a) { return strip_fits(a.nb, a.nmo, a.nw); });
+    const auto mo_r = part(mo, [](const MoArgs& a) { return mo_strip_fits(a.nb, a.na, a.nmo, a.nw); });
+    const auto jao_r = part(jao, [](const JaoArgs& a) { return strip_fits(a.nb, a.nw, a.nw); });
+    const auto kao_r = part(kao, [](const KaoArgs& a) { return strip_fits(a.nb, a.nb, 2); });
+    const auto fock_r = part(fock, [](const FockArgs& a) { return a.strip != 0; });
+    if ((st = setup_half<P>(B, B->half_r, half_r)) || (st = setup_mo<P>(B, B->mo_r, mo_r)) ||
+        (st = setup_jao<P>(B, B->jao_r, jao_r)) || (st = setup_kao<P>(B, B->kao_r, kao_r)) ||
+        (st = setup_fock<P>(B, B->fock_r, fock_r)))
+      return st;
   }
   if ((st = setup_psc<P>(B, psc)) || (st = setup_psd<P>(B, psd)) ||
-      (!B->bpre && (st = setup_half<P>(B, half))) || (st = setup_mo<P>(B, mo)) || (st = setup_jkp<P>(B, jk)) ||
-      (st = setup_jkr<P>(B, jk)) || (st = setup_jao<P>(B, jao)) || (st = setup_kao<P>(B, kao)) ||
-      (st = setup_hc(B, hc)) || (st = setup_coef(B, coef)) || (st = setup_energy(B, en)) ||
-      (st = setup_fock<P>(B, fock)) || (st = setup_fred(B, fred)) || (st = setup_lam(B, lam)) ||
-      (st = setup_grad(B, grad)))
+      (!B->bpre && (st = setup_half<P>(B, B->half, half))) || (st = setup_mo<P>(B, B->mo, mo)) ||
+      (st = setup_jkp<P>(B, jk)) || (st = setup_jkr<P>(B, jk)) || (st = setup_jao<P>(B, B->jao, jao)) ||
+      (st = setup_kao<P>(B, B->kao, kao)) || (st = setup_hc(B, hc)) || (st = setup_coef(B, coef)) ||
+      (st = setup_energy(B, en)) || (st = setup_fock<P>(B, B->fock, fock)) || (st = setup_fred(B, fred)) ||
+      (st = setup_lam(B, lam)) || (st = setup_grad(B, grad)))
     return st;
   // tile variants for the grouped GEMM steps: measured if autotuning, else the
   // variant with the fewest tile-area rounds
   auto pick = [&](GroupStep& g, int nvar, int hv, const std::function<rif_status(int)>& run) {
     long key = 0;
     for (int v = 0; v < nvar; ++v) key = key * 1000003 + g.total[v];
-    g.variant = pick_variant(B->c, g.name.c_str(), {P, B->n, key}, nvar, hv, run);
+    g.variant = pick_variant(B->c, g.name.c_str(), {P, g.n, key}, nvar, hv, run);
     return g.variant < 0 ? RIF_EHIP : RIF_OK;
   };
   auto choose = [&](GroupStep& g, const std::function<rif_status(int)>& run) {
@@ -2997,34 +3021,28 @@ static rif_status batch_setup(BatchImpl* B, const std::vector<BuildArgs>& A) {
     }
     return pick(g, g.nvar, hv, run);
   };
-  // FP64: strips for the whole batch, or the register-staged tile if one
-  // molecule does not take them
-  bool strips = P == kF64;
-  for (auto& h : half) strips = strips && strip_fits(h.nb, h.nmo, h.nw);
-  auto choose_strip = [&](GroupStep& g, const std::function<rif_status(int)>& run) -> rif_status {
-    if (strips) return pick(g, 2, strip_default(g.total[0], g.total[1]), run);
-    g.variant = 2;
-    return RIF_OK;
+  auto choose_strip = [&](GroupStep& g, int hv, const std::function<rif_status(int)>& run) -> rif_status {
+    return g.n ? pick(g, 2, hv, run) : RIF_OK;
   };
   if constexpr (P != kF64) {
-    if (B->bpre && (st = choose(B->halfp, [&](int v) { return launch_halfp<P>(B, v); }))) return st;
-  }
-  if constexpr (P == kF64) {
-    if ((st = choose_strip(B->half, [&](int v) { return launch_half<P>(B, v); }))) return st;
-    if ((st = choose_strip(B->jao, [&](int v) { return launch_jao<P>(B, v); }))) return st;
-    // (the largest molecule's choice: wide tiles are mostly idle on small ones)
-    if (!strips) B->kao.variant = 2;
-    else if ((st = pick(B->kao, 2, kao_default(kao[0].nb, kao[0].nw), [&](int v) { return launch_kao<P>(B, v); }))) return st;
-    B->fock.variant = fock[0].strip ? 0 : 1;
-    B->mo.variant = 0;
-    for (auto& m : mo)
-      if (!mo_strip_fits(m.nb, m.na, m.nmo, m.nw)) B->mo.variant = 1;
+    if (B->bpre && (st = choose(B->halfp, [&](int v) { return launch_halfp<P>(B, B->halfp, v); }))) return st;
+    if (!B->bpre && (st = choose(B->half, [&](int v) { return launch_half<P>(B, B->half, v); }))) return st;
+    if ((st = choose(B->mo, [&](int v) { return launch_mo<P>(B, B->mo, v); }))) return st;
+    if ((st = choose(B->jao, [&](int v) { return launch_jao<P>(B, B->jao, v); }))) return st;
+    if ((st = choose(B->kao, [&](int v) { return launch_kao<P>(B, B->kao, v); }))) return st;
+    if ((st = choose(B->fock, [&](int v) { return launch_fock<P>(B, B->fock, v); }))) return st;
   } else {
-    if (!B->bpre && (st = choose(B->half, [&](int v) { return launch_half<P>(B, v); }))) return st;
-    if ((st = choose(B->mo, [&](int v) { return launch_mo<P>(B, v); }))) return st;
-    if ((st = choose(B->jao, [&](int v) { return launch_jao<P>(B, v); }))) return st;
-    if ((st = choose(B->kao, [&](int v) { return launch_kao<P>(B, v); }))) return st;
-    if ((st = choose(B->fock, [&](int v) { return launch_fock<P>(B, v); }))) return st;
+    if ((st = choose_strip(B->half, strip_default(B->half.total[0], B->half.total[1]),
+                           [&](int v) { return launch_half<P>(B, B->half, v); })) ||
+        (st = choose_strip(B->jao, strip_default(B->jao.total[0], B->jao.total[1]),
+                           [&](int v) { return launch_jao<P>(B, B->jao, v); })) ||
+        // (the largest molecule's choice: wide tiles are mostly idle on small ones)
+        (st = choose_strip(B->kao, kao.empty() ? 0 : kao_default(kao[0].nb, kao[0].nw),
+                           [&](int v) { return launch_kao<P>(B, B->kao, v); })))
+      return st;
+    B->mo.variant = B->fock.variant = 0;
+    B->half_r.variant = B->jao_r.variant = B->kao_r.variant = 2;
+    B->mo_r.variant = B->fock_r.variant = 1;
   }
   return RIF_OK;
 }
@@ -3038,24 +3056,35 @@ static rif_status batch_enqueue(BatchImpl* B) {
     ProfScope ps(c, B->STEP.name.c_str());                       \
     if ((st = launch_##STEP __VA_ARGS__(B, B->STEP.variant))) return st; \
   }
+#define RIF_G2(STEP, LIST)                                            \
+  if (B->LIST.n) {                                                    \
+    ProfScope ps(c, B->LIST.name.c_str());                            \
+    if ((st = launch_##STEP<P>(B, B->LIST, B->LIST.variant))) return st; \
+  }
   RIF_G(psc, <P>)
   if constexpr (P != kF64) {
-    if (B->bpre) RIF_G(halfp, <P>)
+    if (B->bpre) RIF_G2(halfp, halfp)
   }
-  if (!B->bpre) RIF_G(half, <P>)
-  RIF_G(mo, <P>)
+  if (!B->bpre) RIF_G2(half, half)
+  RIF_G2(half, half_r)
+  RIF_G2(mo, mo)
+  RIF_G2(mo, mo_r)
   RIF_G(jkp, <P>)
   RIF_G(jkr, <P>)
   if (kPlanesHalfJao<P>) RIF_G(psd, <P>)
-  RIF_G(jao, <P>)
-  RIF_G(kao, <P>)
+  RIF_G2(jao, jao)
+  RIF_G2(jao, jao_r)
+  RIF_G2(kao, kao)
+  RIF_G2(kao, kao_r)
   RIF_G(hc)
   RIF_G(coef)
   RIF_G(energy)
-  RIF_G(fock, <P>)
+  RIF_G2(fock, fock)
+  RIF_G2(fock, fock_r)
   RIF_G(fred)
   RIF_G(lam)
   RIF_G(grad)
+#undef RIF_G2
 #undef RIF_G
   return RIF_OK;
 }
@@ -3074,11 +3103,9 @@ rif_status op_batch_create(rif_ctx* c, int prec, int functional, int n, const ri
   std::vector<Plan> plans;
   std::vector<size_t> base;
   size_t total = 0;
-  bool strips = true;   // one Fock kernel for the whole batch
-  for (int k = 0; k < n; ++k) strips = strips && strip_fits(inst[k].n_bf, inst[k].n_mo, inst[k].n_pairs * (1 + inst[k].n_cwo));
   for (int k = 0; k < n; ++k) {
     const rif_instance& in = inst[B->order[k]];
-    plans.emplace_back(in.n_bf, in.n_aux, in.n_pairs, in.n_cwo, in.n_mo, strips);
+    plans.emplace_back(in.n_bf, in.n_aux, in.n_pairs, in.n_cwo, in.n_mo);
     base.push_back(total);
     total += (plans.back().bytes + 255) & ~size_t(255);
   }
