@@ -2311,8 +2311,9 @@ struct Plan {
   size_t o_part, o_hc, o_a, o_b, o_yp, o_y, o_ep, o_lp, o_cs, o_ds, bytes;
   size_t o_ydp, o_zt, o_bt, bytes_direct;   // the gradient without per-MO AO matrices
   int fock_strip;   // the FP64 Fock step on strip tiles
-  // strip: whether the workspace may hold that step's partials
-  Plan(int nb_, int na_, int npairs_, int ncwo_, int nmo_, bool strip = true) {
+  Plan() = default;
+  // strip: room for that step's partials
+  Plan(int nb_, int na_, int npairs_, int ncwo_, int nmo_, bool strip) {
     nb = nb_; na = na_; npairs = npairs_; ncwo = ncwo_; nmo = nmo_;
     nw = npairs * (1 + ncwo);
     const long w2 = (long)nw * nw;
@@ -2375,6 +2376,16 @@ struct BuildArgs {
   GemmArgs hc; CoefArgs coef; EnergyArgs energy; FockArgs fock; FockRedArgs fred; GemmArgs lam; GradArgs grad;
   YdzArgs ydz; YdArgs yd; FockRedArgs ydred;
 };
+// The plan of a build with J^q and K^q: the Fock step's strips where the mode has
+// them and the arena can hold their partials.
+static rif_status build_plan(rif_ctx* c, int prec, const rif_instance& in, Plan* out) {
+  const Plan lean(in.n_bf, in.n_aux, in.n_pairs, in.n_cwo, in.n_mo, false);
+  const Plan full(in.n_bf, in.n_aux, in.n_pairs, in.n_cwo, in.n_mo, prec == RIF_FP64);
+  bool got = false;
+  const rif_status st = ws_reserve_either(c, full.bytes, lean.bytes, &got);
+  *out = got ? full : lean;
+  return st;
+}
 static BuildArgs make_build_args(const Plan& pl, const rif_instance& in, int prec, int functional, char* ws,
                                  int* flag) {
   BuildArgs A;
@@ -2414,7 +2425,7 @@ static BuildArgs make_build_args(const Plan& pl, const rif_instance& in, int pre
   A.coef = CoefArgs{functional, nw, pl.npairs, pl.ncwo, in.pair_of, in.occ, in.J, in.K, Ac, Bc, Ep};
   A.energy = EnergyArgs{nw, pl.npairs, pl.ncwo, nb, nmo, pl.nparts, in.pair_of, in.occ, in.C, HC, Ep, in.energy,
                         flag};
-  A.fock = FockArgs{nb, nw, nmo, pl.fock_nsplit, in.Jn, in.Kn, Ac, Bc, in.C, Yp, prec == RIF_FP64 && pl.fock_strip};
+  A.fock = FockArgs{nb, nw, nmo, pl.fock_nsplit, in.Jn, in.Kn, Ac, Bc, in.C, Yp, pl.fock_strip};
   A.fred = FockRedArgs{nb, nw, pl.fock_nsplit, Yp, in.occ, HC, Y, A.fock.strip};
   A.lam = GemmArgs{nmo, nw, nb, in.C, (long)nmo, Y, (long)nw, Lp, (long)nw, pl.lam_split, pl.small_kc,
                    (long)nmo * nw};
@@ -2569,14 +2580,13 @@ rif_status op_energy_grad(rif_ctx* c, int prec, int functional, int nb, int nmo,
                           const double* J, const double* K, const void* Jn, const void* Kn, double* energy,
                           double* lambda, double* grad) {
   if (!prec_ok(prec)) return fail(c, RIF_ENOTSUP, "precision mode not available");
-  Plan pl(nb, 1, npairs, ncwo, nmo);
-  if (!ws_fits(c, pl.bytes)) pl = Plan(nb, 1, npairs, ncwo, nmo, false);
-  rif_status st = ws_reserve(c, pl.bytes);
-  if (st) return st;
   rif_instance in{};
   in.n_bf = nb; in.n_aux = 1; in.n_pairs = npairs; in.n_cwo = ncwo; in.n_mo = nmo;
   in.H = H; in.C = C; in.occ = occ; in.pair_of = pair_of; in.J = (double*)J; in.K = (double*)K;
   in.Jn = (void*)Jn; in.Kn = (void*)Kn; in.energy = energy; in.lambda = lambda; in.grad = grad;
+  Plan pl;
+  const rif_status st = build_plan(c, prec, in, &pl);
+  if (st) return st;
   const BuildArgs A = make_build_args(pl, in, prec, functional, (char*)c->ws, c->dflag);
   RIF_PREC_SWITCH(prec, run_energy_grad<P>(c, A))
 }
@@ -2684,9 +2694,8 @@ rif_status op_build(rif_ctx* c, int prec, int functional, const rif_instance& in
   if (!prec_ok(prec)) return fail(c, RIF_ENOTSUP, "precision mode not available");
   rif_status st = ensure_side(c);
   if (st) return st;
-  Plan pl(in.n_bf, in.n_aux, in.n_pairs, in.n_cwo, in.n_mo);
-  if (!ws_fits(c, pl.bytes)) pl = Plan(in.n_bf, in.n_aux, in.n_pairs, in.n_cwo, in.n_mo, false);
-  if ((st = ws_reserve(c, pl.bytes))) return st;
+  Plan pl;
+  if ((st = build_plan(c, prec, in, &pl))) return st;
   const BuildArgs A = make_build_args(pl, in, prec, functional, (char*)c->ws, c->dflag);
   RIF_PREC_SWITCH(prec, run_build<P>(c, A))
 }
@@ -3102,15 +3111,22 @@ rif_status op_batch_create(rif_ctx* c, int prec, int functional, int n, const ri
   std::stable_sort(B->order.begin(), B->order.end(), [&](int x, int y) { return cost(x) > cost(y); });
   std::vector<Plan> plans;
   std::vector<size_t> base;
-  size_t total = 0;
-  for (int k = 0; k < n; ++k) {
-    const rif_instance& in = inst[B->order[k]];
-    plans.emplace_back(in.n_bf, in.n_aux, in.n_pairs, in.n_cwo, in.n_mo);
-    base.push_back(total);
-    total += (plans.back().bytes + 255) & ~size_t(255);
-  }
-  if (hipMalloc(&B->ws, std::max(total, (size_t)256)) != hipSuccess) {
+  auto allocate = [&](bool strip) {
+    plans.clear();
+    base.clear();
+    size_t total = 0;
+    for (int k = 0; k < n; ++k) {
+      const rif_instance& in = inst[B->order[k]];
+      plans.emplace_back(in.n_bf, in.n_aux, in.n_pairs, in.n_cwo, in.n_mo, strip);
+      base.push_back(total);
+      total += (plans.back().bytes + 255) & ~size_t(255);
+    }
+    if (hipMalloc(&B->ws, std::max(total, (size_t)256)) == hipSuccess) return true;
     (void)hipGetLastError();
+    B->ws = nullptr;
+    return false;
+  };
+  if (!(prec == RIF_FP64 && allocate(true)) && !allocate(false)) {
     delete B;
     return fail(c, RIF_ENOMEM, "batch: workspace allocation failed");
   }

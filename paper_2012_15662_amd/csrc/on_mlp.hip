@@ -1386,9 +1386,10 @@ rif_status op_mlp_backward(rif_ctx* c, int nrows, const float* X, const float* M
   Carve full = cv;
   const size_t o_part = full.take<double>((size_t)splits * n);
   const size_t o_da = full.take<float>((size_t)nrows * kNhid);
-  const bool lean = !ws_fits(c, full.off);
-  rif_status st = ws_reserve(c, lean ? cv.off : full.off);
+  bool roomy = false;
+  rif_status st = ws_reserve_either(c, full.off, cv.off, &roomy);
   if (st) return st;
+  const bool lean = !roomy;
   char* ws = (char*)c->ws;
   double* lp = (double*)(ws + o_lp);
   float* dZ = (float*)(ws + o_dz);

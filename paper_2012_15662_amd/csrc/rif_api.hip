@@ -31,10 +31,23 @@ rif_status ws_reserve(rif_ctx* c, size_t bytes) {
   if (hipMalloc(&c->ws, want) != hipSuccess) {
     (void)hipGetLastError();
     c->ws = nullptr;
+    if (!c->ws_denied || bytes < c->ws_denied) c->ws_denied = bytes;
     return fail(c, RIF_ENOMEM, "hipMalloc of " + std::to_string(want) + " workspace bytes failed");
   }
   c->ws_bytes = want;
   return RIF_OK;
+}
+
+rif_status ws_reserve_either(rif_ctx* c, size_t full, size_t lean, bool* got_full) {
+  *got_full = full <= c->ws_bytes ||
+              ((!c->ws_limit || full <= c->ws_limit) && (!c->ws_denied || full < c->ws_denied));
+  if (*got_full) {
+    const rif_status st = ws_reserve(c, full);
+    if (st != RIF_ENOMEM || full <= lean) return st;
+    *got_full = false;
+    c->err.clear();
+  }
+  return ws_reserve(c, lean);
 }
 
 rif_status check_launch(rif_ctx* c, const char* what) {
@@ -185,6 +198,7 @@ rif_status rif_set_stream(rif_ctx* c, void* stream) {
 rif_status rif_set_workspace_limit(rif_ctx* c, unsigned long long bytes) {
   if (!c) return RIF_EINVAL;
   c->ws_limit = (size_t)bytes;
+  c->ws_denied = 0;
   return RIF_OK;
 }
 

@@ -18,6 +18,7 @@ struct rif_ctx {
   void* ws = nullptr;
   size_t ws_bytes = 0;
   size_t ws_limit = 0;
+  size_t ws_denied = 0;       // smallest size that the device had no memory for (0: none so far)
   int* dflag = nullptr;       // device status word for device-side validation
   // profiling
   bool prof = false;
@@ -59,10 +60,11 @@ enum : int { kBadOcc = 1, kBadSum = 2, kBadMap = 4, kBadCount = 8, kNonFinite = 
 rif_status fail(rif_ctx* c, rif_status s, const std::string& msg);
 // Ensures the arena holds at least `bytes`; returns RIF_OK or RIF_ENOMEM/RIF_EHIP.
 rif_status ws_reserve(rif_ctx* c, size_t bytes);
-// Whether the arena may hold `bytes` (rif_set_workspace_limit).
-inline bool ws_fits(const rif_ctx* c, size_t bytes) {
-  return bytes <= c->ws_bytes || !c->ws_limit || bytes <= c->ws_limit;
-}
+// The same for a call that works faster in `full` bytes but needs `lean` only: full
+// where the limit (rif_set_workspace_limit) and the device's memory allow it, which
+// got_full reports.  A size that the device refused is not asked for again until the
+// limit is set anew, so that a call that has run finds its arena in place.
+rif_status ws_reserve_either(rif_ctx* c, size_t full, size_t lean, bool* got_full);
 
 // Carves aligned sub-buffers from the arena.
 struct Carve {
