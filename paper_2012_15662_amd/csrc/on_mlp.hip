@@ -1033,7 +1033,7 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_fwd(int nrows, const float*
 // Backward through the activations: loss partials (one per workgroup), dZ of
 // the loss, then dA_l[row][i] = (sum_o dY[row][o] W[i][o]) (1 - h[row][i]^2) for
 // l = 2, 1, 0 (the gradients at the pre-activations, which the weight
-// gradients read; a null one is not stored).
+// gradients read); a null output is not stored.
 template <int RT>
 __global__ __launch_bounds__(kMlpThreads) void k_mlp_bwd(int nrows, const float* __restrict__ T,
                                                          const float* __restrict__ M,
@@ -1063,14 +1063,17 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_bwd(int nrows, const float*
         sdp += dp[k] * p[k];
       }
 #pragma unroll
-      for (int k = 0; k < kNout; ++k) dZ[row * kNout + k] = g[k] = (float)(p[k] * (dp[k] - sdp));
+      for (int k = 0; k < kNout; ++k) {
+        g[k] = (float)(p[k] * (dp[k] - sdp));
+        if (dZ) dZ[row * kNout + k] = g[k];
+      }
     }
 #pragma unroll
     for (int k = 0; k < 16; ++k) act[0][tid * kActLd + k] = g[k];
     red[tid] = l;
   }
   __syncthreads();
-  if (tid == 0) {
+  if (tid == 0 && lpart) {
     double s = 0.0;
     for (int i = 0; i < ROWS; ++i) s += red[i];
     lpart[blockIdx.x] = s;
@@ -1378,12 +1381,14 @@ rif_status op_mlp_backward(rif_ctx* c, int nrows, const float* X, const float* M
   // workgroups for each wide layer (two of them fill the chip)
   int chunk = 128 * cdiv_i(nrows, 128 * 160), splits = cdiv_i(nrows, chunk);
   Carve cv;
-  const size_t o_lp = cv.take<double>((size_t)nl);
   const size_t o_dz = cv.take<float>((size_t)nrows * kNout);
   // the rest only if the arena may hold it (rif_set_workspace_limit): without
   // it each gradient is one split, stored straight into grad, and the third
-  // dA shares dA's first buffer in a second backward pass
+  // dA shares dA's first buffer in a second backward pass.  The loss partials (half
+  // a byte a row) come from that pass and take dZ's place (28 bytes a row), which
+  // layer 0's gradients have no use for
   Carve full = cv;
+  const size_t o_lp = full.take<double>((size_t)nl);
   const size_t o_part = full.take<double>((size_t)splits * n);
   const size_t o_da = full.take<float>((size_t)nrows * kNhid);
   bool roomy = false;
@@ -1391,17 +1396,17 @@ rif_status op_mlp_backward(rif_ctx* c, int nrows, const float* X, const float* M
   if (st) return st;
   const bool lean = !roomy;
   char* ws = (char*)c->ws;
-  double* lp = (double*)(ws + o_lp);
   float* dZ = (float*)(ws + o_dz);
+  double* lp = lean ? (double*)dZ : (double*)(ws + o_lp);
   float *d2 = dA, *d1 = dA + (long)nrows * kNhid, *d0 = lean ? dA : (float*)(ws + o_da);
-  auto back = [&](float* p2, float* p1, float* p0) {
+  auto back = [&](float* pz, float* p2, float* p1, float* p0, double* pl) {
     ProfScope ps(c, "mlp_dgrad");
     if (wide)
-      hipLaunchKernelGGL(k_mlp_bwd<2>, dim3(nl), dim3(kMlpThreads), 0, c->stream, nrows, T, M, theta, H, Z, dZ, p2, p1,
-                         p0, lp);
+      hipLaunchKernelGGL(k_mlp_bwd<2>, dim3(nl), dim3(kMlpThreads), 0, c->stream, nrows, T, M, theta, H, Z, pz, p2, p1,
+                         p0, pl);
     else
-      hipLaunchKernelGGL(k_mlp_bwd<1>, dim3(nl), dim3(kMlpThreads), 0, c->stream, nrows, T, M, theta, H, Z, dZ, p2, p1,
-                         p0, lp);
+      hipLaunchKernelGGL(k_mlp_bwd<1>, dim3(nl), dim3(kMlpThreads), 0, c->stream, nrows, T, M, theta, H, Z, pz, p2, p1,
+                         p0, pl);
     return check_launch(c, "mlp_dgrad");
   };
   if (lean) { chunk = nrows; splits = 1; }
@@ -1413,10 +1418,10 @@ rif_status op_mlp_backward(rif_ctx* c, int nrows, const float* X, const float* M
     return check_launch(c, "mlp_wgrad");
   };
   if (lean) {
-    if ((st = back(d2, d1, nullptr)) || (st = weights_of(0, 3)) || (st = back(nullptr, nullptr, d0)) ||
-        (st = weights_of(3, 1)))
+    if ((st = back(dZ, d2, d1, nullptr, nullptr)) || (st = weights_of(0, 3)) ||
+        (st = back(nullptr, nullptr, nullptr, d0, lp)) || (st = weights_of(3, 1)))
       return st;
-  } else if ((st = back(d2, d1, d0)) || (st = weights_of(0, 4))) {
+  } else if ((st = back(dZ, d2, d1, d0, lp)) || (st = weights_of(0, 4))) {
     return st;
   }
   ProfScope ps(c, "mlp_reduce");

@@ -139,8 +139,21 @@ static void builds() {
   }
 }
 
+// The network's backward pass runs in the gradients at its logits and one double
+// for every 256 rows.
+static void training() {
+  for (int rows : {1, 40, 257, 4096, 6001, 13001, 100003}) {
+    float x = 0.f;
+    auto back = [&](rif_ctx* c) { return rif_mlp_backward(c, rows, &x, &x, &x, &x, &x, &x, &x, &x, &word); };
+    const size_t need = ((rows + 255) / 256 * sizeof(double) + 255) / 256 * 256 + (size_t)rows * 7 * sizeof(float);
+    check(runs_with(need, back), "rif_mlp_backward", rows, need);
+    on_a_full_device("rif_mlp_backward on a full device", back);
+  }
+}
+
 int main() {
   builds();
+  training();
   printf("%d checks, %d failures\n", n_check, n_fail);
   return n_fail != 0;
 }
