@@ -346,12 +346,11 @@ rif_status rif_adam(rif_ctx *ctx, int n, float *theta, const float *grad, float 
  *   [n_aux][n_aux] dense; n_raised: number of raised eigenvalues
  * delta <= 0 takes 2^-26 * max_k sum_l |G_kl|.  The factorisation runs as
  * one cooperative launch where the metric's rows fit the registers of at most
- * 256 workgroups (n_aux up to 2048; its waits are bounded by
- * rif_set_wait_limit, and a timed-out one leaves b all NaN), else as a pivot
- * and an update launch per column.  Uses 6 n_aux^2 doubles of the context
- * arena, plus 4 n_aux^2 + 2 n_aux for the one-launch factorisation's exchange
- * slots.  Asynchronous.  RIF_EINVAL for sizes
- * (n_aux < 46341) or NULL T, G, b. */
+ * 256 workgroups (n_aux up to 2048) and the context arena may hold its exchange
+ * slots, 4 n_aux^2 + 2 n_aux doubles beside the 6 n_aux^2 that are always used
+ * (its waits are bounded by rif_set_wait_limit, and a timed-out one leaves b all
+ * NaN), else as a pivot and an update launch per column.  Asynchronous.
+ * RIF_EINVAL for sizes (n_aux < 46341) or NULL T, G, b. */
 rif_status rif_prepare_b(rif_ctx *ctx, int n_bf, int n_aux, const double *T, const double *G, double delta,
                          double *b, int *perm, double *L, double *D, int *n_raised);
 

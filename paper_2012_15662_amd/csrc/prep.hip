@@ -1103,9 +1103,9 @@ rif_status op_prepare_b(rif_ctx* c, int nb, int na, const double* T, const doubl
   const size_t oP = cv.take<int>(n), oB = cv.take<int>(n), oS = cv.take<BkState>(1);
   const size_t oPart = cv.take<double>((size_t)n), oDel = cv.take<double>(1);
   const size_t oR = cv.take<int>(1);
-  // the one-launch factorisation where a row fits four elements a thread and the
-  // rows the registers of one workgroup per CU, else a pivot and an update launch
-  // per column
+  // the one-launch factorisation where a row fits four elements a thread, the rows
+  // the registers of one workgroup per CU and its slots the arena, else a pivot and an
+  // update launch per column
   int G = 0;
   if (n <= kBkMaxN) {
     int ncu = 0, coop = 0;
@@ -1117,9 +1117,12 @@ rif_status op_prepare_b(rif_ctx* c, int nb, int na, const double* T, const doubl
     (void)hipGetLastError();
   }
   const long nslots = 4 * nn + 2 * n;
+  const size_t columns = cv.off;
   const size_t oSlots = G ? cv.take<double>((size_t)nslots) : 0, oErr = G ? cv.take<int>(1) : 0;
-  rif_status st = ws_reserve(c, cv.off);
+  bool roomy = false;
+  rif_status st = ws_reserve_either(c, cv.off, columns, &roomy);
   if (st) return st;
+  if (!roomy) G = 0;
   char* w = (char*)c->ws;
   double *A = (double*)(w + oA), *L = (double*)(w + oL), *D = (double*)(w + oD), *X = (double*)(w + oX);
   double *Mt = (double*)(w + oM), *Dih = (double*)(w + oDih), *part = (double*)(w + oPart);

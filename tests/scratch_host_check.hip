@@ -151,9 +151,22 @@ static void training() {
   }
 }
 
+// The preparation runs column by column in six n_aux^2 matrices, with the packed
+// triangles' n_aux n_bf (n_bf + 1) / 2 to spare.
+static void preparation() {
+  for (int n : {40, 1044, 1601, 1800, 2048, 2049})
+    for (int nb : {1, 12, 60}) {
+      auto prep = [&](rif_ctx* c) { return rif_prepare_b(c, nb, n, &word, &word, 0.0, &word, nullptr, nullptr, nullptr, nullptr); };
+      const size_t nn = (size_t)n * n, need = 8 * (6 * nn + 2 * (size_t)n + (size_t)n * nb * (nb + 1) / 2) + 12 * 256;
+      check(runs_with(need, prep), "rif_prepare_b", n, nb);
+      if (n > 400) on_a_full_device("rif_prepare_b on a full device", prep);
+    }
+}
+
 int main() {
   builds();
   training();
+  preparation();
   printf("%d checks, %d failures\n", n_check, n_fail);
   return n_fail != 0;
 }
