@@ -455,12 +455,13 @@ rif_status rif_pnof_optimize(rif_ctx *ctx, const rif_instance *inst, rif_prec pr
 
 /* Tile-shape selection for the MFMA kernels.  Each GEMM-shaped kernel has up
  * to four tile variants (0: 128x128, 1: 64x64, 2: 128x64, 3: 64x128 outputs
- * per workgroup; in FP64 the half transform, J^q, K^q and the Fock step have
- * two, 0: 128 and 1: 64 columns by up to 128 rows, as many as n_omega asks for,
- * and the MO transform one).  mode 0 picks one per shape with a wave-quantisation
+ * per workgroup; in FP64 the half transform, J^q and K^q have two, 0: 128 and 1:
+ * 64 columns by up to 128 rows, as many as n_omega asks for, and the MO transform
+ * and the Fock step one, which is never timed).  mode 0 picks one per shape with a wave-quantisation
  * model; mode 1 (autotune) times every variant on the first call with a new
  * shape -- synchronising the stream once -- and reuses the fastest for that
- * shape afterwards.  Results are identical to FP64 rounding across variants. */
+ * shape afterwards; while the stream is being captured, a shape that has no
+ * usable choice yet takes mode 0's.  Results are identical to FP64 rounding across variants. */
 rif_status rif_autotune(rif_ctx *ctx, int mode);
 /* Force variant v (0..3, clamped to what each kernel has) for every kernel;
  * -1 returns to automatic selection. */

@@ -59,11 +59,15 @@ rif_status check_launch(rif_ctx* c, const char* what) {
 int pick_variant(rif_ctx* c, const char* kernel, std::initializer_list<long> shape, int nvar, int heuristic,
                  const std::function<rif_status(int)>& run) {
   if (c->force_variant >= 0) return std::min(c->force_variant, nvar - 1);
-  if (c->tune_mode == 0) return heuristic;
+  if (c->tune_mode == 0 || nvar == 1) return heuristic;
   std::string key = kernel;
   for (long v : shape) key += " " + std::to_string(v);
   for (auto& t : c->tune)
     if (t.key == key && t.variant < nvar) return t.variant;   // (a loaded entry may name too many)
+  // nothing can be timed into a graph: a shape without a usable entry takes the default
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) (void)hipGetLastError();
+  else if (cap != hipStreamCaptureStatusNone) return heuristic;
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess) return -1;
   if (hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); return -1; }

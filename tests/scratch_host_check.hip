@@ -1,7 +1,8 @@
 // Host-side check of what scratch memory the library asks for and how it does with
-// less (tests/test_scratch_host.py).  The HIP runtime's calls are answered here: device
-// memory is numbers from a counter, an allocation past `device_free` fails, launches
-// and copies do nothing.  So whole entry points run on a machine without a GPU.
+// less, and of calls under stream capture with saved tile choices
+// (tests/test_scratch_host.py).  The HIP runtime's calls are answered here: device
+// memory is numbers from a counter, an allocation past `device_free` fails, a wait
+// fails while `capturing`, launches and copies do nothing.  So whole entry points run on a machine without a GPU.
 #include <stdio.h>
 #include <string.h>
 
@@ -11,6 +12,7 @@
 
 static size_t device_free = ~size_t(0);   // largest single allocation that succeeds
 static size_t n_malloc = 0, n_denied = 0, n_launch = 0, n_coop = 0;
+static bool capturing = false;
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
   static size_t next = 1 << 20;
@@ -23,9 +25,19 @@ hipError_t hipMalloc(void** p, size_t n) {
 hipError_t hipFree(void*) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
 hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { ++n_launch; return hipSuccess; }
 hipError_t hipLaunchCooperativeKernel(const void*, dim3, dim3, void**, unsigned, hipStream_t) { ++n_coop; return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return capturing ? hipErrorStreamCaptureUnsupported : hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return capturing ? hipErrorStreamCaptureUnsupported : hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
+  *s = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)16; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1.f; return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)16; return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t)16; return hipSuccess; }
@@ -163,10 +175,34 @@ static void preparation() {
     }
 }
 
+// A program that loads tile choices saved by an earlier version (four FP64 variants a
+// step, the Fock step's splits in its key) and captures its build after a first run.
+static void saved_choices() {
+  const rif_instance in = molecule(348, 1044, 24, 4, 348);
+  const char* saved =
+      "half_transform 0 348 363312 120 348 -> 2 | 0.60 0.62 0.58 0.61\n"
+      "mo_transform 0 348 1044 120 348 -> 3 | 0.22 0.25 0.24 0.21\n"
+      "jao 0 348 1044 120 -> 3 | 0.31 0.33 0.32 0.30\n"
+      "kao 0 348 1044 120 -> 1 | 0.35 0.33\n"
+      "fock 0 348 120 348 42 -> 0 | 0.16 0.18 0.17 0.17\n";
+  rif_ctx c;
+  check(rif_tune_load(&c, saved) == RIF_OK, "saved choices load");
+  check(rif_build(&c, &in, RIF_FP64, RIF_PNOF7) == RIF_OK, "first build");   // the arena
+  c.tune_mode = 1;
+  capturing = true;
+  check(rif_build(&c, &in, RIF_FP64, RIF_PNOF7) == RIF_OK, "captured build with saved choices");
+  capturing = false;
+  const size_t launches = n_launch;
+  check(rif_build(&c, &in, RIF_FP64, RIF_PNOF7) == RIF_OK && n_launch > launches, "build after it");
+  // a step with one kernel has nothing to time
+  for (auto& t : c.tune) check(t.ms.size() > 1, t.key.c_str(), t.ms.size());
+}
+
 int main() {
   builds();
   training();
   preparation();
+  saved_choices();
   printf("%d checks, %d failures\n", n_check, n_fail);
   return n_fail != 0;
 }
