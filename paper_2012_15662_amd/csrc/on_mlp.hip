@@ -657,7 +657,7 @@ __global__ __launch_bounds__(kOnSmallThreads) void k_on_opt_small(const OnProble
           }
           const double q = dot(sy, t);
           if (q > 1e-300) {
-            if (lane == 0) s.rho[head] = 1.0 / q;
+            s.rho[head] = 1.0 / q;   // every lane the same: what a lane reads it has written
             head = (head + 1) % kHist;
             hist = hist < kHist ? hist + 1 : kHist;
           }
