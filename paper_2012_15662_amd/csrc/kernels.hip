@@ -371,8 +371,8 @@ inline bool b_presplit(const HalfArgs& a) {
 // chunks swizzled, chunk c at slot c ^ (x % 8)).  Lane group kr of step (h, m)
 // takes k = 2 (kr + 4 h) + m: one 16-byte read of B per step pair, and A rows two
 // apart, which the padding puts on different banks.  An odd n_bf is a row of
-// n_bf + 1 positions (pair_column): position n_bf - 1 repeats n_bf - 2 and meets
-// a zero row of C.  Tiles: the largest blocks first, every group of l of one
+// n_bf + 1 positions (pair_column): position n_bf - 1 repeats n_bf - 2, counts as
+// zero (an infinity stays one) and meets a zero row of C.  Tiles: the largest blocks first, every group of l of one
 // block after another, so the short ones fill the end of the launch (block after
 // block per group of l left a third of the CUs idle for the last 50 us of 190).
 // Stores: b_mo[l][q][p] in 128-byte pieces, b_mo[l][p][q] in 32-byte ones that
@@ -482,6 +482,7 @@ __device__ __forceinline__ void mo_strip(const MoArgs& a, long t, char* smem_gen
       for (int j = 0; j < L::FN; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
     const int wm = (w / L::WVN) * L::FM * 16, wl = (w % L::WVN) * L::FN;   // first row, first l of this wave
     const int nk = cdiv(K, 16);
+    const int twice = nb & 1 ? (nb - 1) / 2 : -1;   // chunk whose first position is a repeated one
 #pragma unroll
     for (int j = 0; j < L::S - 1; ++j)
       if (j < nk) issue(j, sm + j * L::ST);
@@ -505,6 +506,10 @@ __device__ __forceinline__ void mo_strip(const MoArgs& a, long t, char* smem_gen
           const lds_f64* q = Bs + ((wl + j) * 16 + xc) * 16 + 2 * (c ^ (xc & 7));
           b[j][0] = q[0];
           b[j][1] = q[1];
+        }
+        if ((unsigned)(twice - 8 * kt) < 8u) {   // the last slice of an odd row
+#pragma unroll
+          for (int j = 0; j < L::FN; ++j) b[j][0] = 8 * kt + c == twice ? 0.0 : b[j][0];
         }
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
