@@ -457,7 +457,7 @@ rif_status rif_pnof_optimize(rif_ctx *ctx, const rif_instance *inst, rif_prec pr
  * to four tile variants (0: 128x128, 1: 64x64, 2: 128x64, 3: 64x128 outputs
  * per workgroup; in FP64 the half transform, J^q and K^q have two, 0: 128 and 1:
  * 64 columns by up to 128 rows, as many as n_omega asks for, and the MO transform
- * and the Fock step one, which is never timed).  mode 0 picks one per shape with a wave-quantisation
+ * and the Fock step one).  mode 0 picks one per shape with a wave-quantisation
  * model; mode 1 (autotune) times every variant on the first call with a new
  * shape -- synchronising the stream once -- and reuses the fastest for that
  * shape afterwards; while the stream is being captured, a shape that has no

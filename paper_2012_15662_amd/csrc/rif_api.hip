@@ -59,7 +59,7 @@ rif_status check_launch(rif_ctx* c, const char* what) {
 int pick_variant(rif_ctx* c, const char* kernel, std::initializer_list<long> shape, int nvar, int heuristic,
                  const std::function<rif_status(int)>& run) {
   if (c->force_variant >= 0) return std::min(c->force_variant, nvar - 1);
-  if (c->tune_mode == 0 || nvar == 1) return heuristic;
+  if (c->tune_mode == 0) return heuristic;
   std::string key = kernel;
   for (long v : shape) key += " " + std::to_string(v);
   for (auto& t : c->tune)

@@ -194,8 +194,6 @@ static void saved_choices() {
   capturing = false;
   const size_t launches = n_launch;
   check(rif_build(&c, &in, RIF_FP64, RIF_PNOF7) == RIF_OK && n_launch > launches, "build after it");
-  // a step with one kernel has nothing to time
-  for (auto& t : c.tune) check(t.ms.size() > 1, t.key.c_str(), t.ms.size());
 }
 
 int main() {
