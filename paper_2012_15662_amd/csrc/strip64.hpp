@@ -167,8 +167,12 @@ struct StripStage {
   }
 };
 
-__device__ __forceinline__ void strip_barrier() {   // no fence: loads in flight stay in flight
+// A barrier past which any wave may fill or write the LDS that this one has read: its
+// LDS operations are done, its global loads in flight stay in flight (no fence).  The
+// wait is not left to the MFMAs that use the values: some are moved past the barrier.
+__device__ __forceinline__ void strip_barrier() {
   asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));   // lgkmcnt(0)
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
