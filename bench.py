@@ -37,7 +37,7 @@ HBM_GBS = 8000.0
 # were taken on: a figure is reported only while those sources are unchanged.
 # The runs and their command lines are in profiles/.
 TRAFFIC = {
-    ("half_transform", "c6h12", "fp64"): {"src": "e79216cae053439d", "fetch": 1079052405, "write": 348779520,
+    ("half_transform", "c6h12", "fp64"): {"src": "a5ce8d9bde716cbe", "fetch": 1079546798, "write": 348779520,
                                          "profile": "profiles/fp64_c6h12_counters.md"},
 }
 

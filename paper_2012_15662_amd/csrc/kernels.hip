@@ -103,12 +103,14 @@ struct HalfArgs {
 // FP32 mode: a float copy.
 struct BSplitArgs { const double* b; long nr; int nb, ld; void* out; long ps; };
 struct MoArgs { int nb, na, nw, nmo; const void* bh; const double* C; void* bmo; double* d; Planes Cs; };
-// (and 16 rows of b_half, n_aux n_bf apart, at 32-bit offsets).  From 192 tiles on:
-// below, both triangles of b_mo stay products of their own, as small molecules'
-// orbital loops have them.  Such a loop starts from a F^lambda whose block outside
-// Omega is zero, so part of its first eigenvectors is set by the last bits of
-// what it is given; mirrored elements would change them.  The launch takes 9 us
-// there (7 with strips), of a few hundred for an inner iteration.
+// (and 16 rows of b_half, n_aux n_bf apart, at 32-bit offsets).  From 192 tiles on,
+// which is not a line of speed (below it the launch takes 9 us, with strips 7, of a
+// few hundred for an inner iteration): both triangles of b_mo stay products of their
+// own there, as small molecules' orbital loops have them.  Such a loop starts from a
+// F^lambda whose block outside Omega is zero, so part of its first eigenvectors is
+// set by the last bits of what it is given, and mirrored elements would change
+// them.  192 lies just above what molecules of up to n_bf 140 reach (n_omega a
+// quarter of it).
 inline bool mo_strip_fits(int nb, int na, int nmo, int nw);
 // Bj: b pre-split for J^q (piece planes with rows r = mu*n_bf + nu and
 // k = l contiguous), or unset (split on load).
@@ -889,9 +891,11 @@ __device__ void jaop_tile(const JaoArgs& a, long, char* smem) { jaop_persistent<
 // The mirrored half is transposed in LDS, 16 x 16 per wave, so that both halves
 // store whole 128-byte pieces.  Per launch, against 64 x 64 tiles of
 // 64-bit-addressed direct loads before: 2.40 -> 2.17 ms at the cyclodecane-like
-// size, 54 -> 51 us at n_bf 201 / n_omega 48 (odd: register-staged before), 330 us
-// either way at the cyclohexane-like size, where the tiles' last round leaves a
-// fifth of the launch half empty.
+// size, 54 -> 51 us at n_bf 201 / n_omega 48 (odd: register-staged before), but
+// 0.330 -> 0.340 - 0.350 ms at the cyclohexane-like size (J^q and K^q together 629 ->
+// 603 us): the tiles' last round leaves a fifth of the launch half empty, and with the
+// diagonal tiles so long after a q's others b_half comes from HBM twice (873 MB a
+// launch for 349).
 template <class Cfg, int TM_, bool kDiag>
 struct KaoStrip {
   static constexpr int TM = TM_, BM = 16 * TM, BN = Cfg::BN, NW = Cfg::NWAVES;
@@ -1268,7 +1272,7 @@ __device__ __forceinline__ void fock_strip(const FockArgs& a, long t, char* smem
           const int ml = acc.wn / 16 + j, mu = mu0 + ml;
           const double F = acc.v[i][j][e];
           if (ok && mu < nu) c = fma(F, a.C[(long)mu * a.nmo + q], c);
-          // over the block's nu: the sixteen lanes of a row, the same bits in each
+          // over the block's nu: the sixteen lanes of a row, of which the first's sum is kept
           double r = ok && mu <= nu ? F * cn : 0.0;
           r += dpp_move<0xB1>(r);
           r += dpp_move<0x4E>(r);

@@ -1,5 +1,6 @@
 // FP64 MFMA main loop for products of two x-contiguous operands (element (x, k)
-// at base[k ld + x]): the half transform, J^q and the Fock step.
+// at base[k ld + x]): the half transform, J^q, K^q, the Fock step and the solve of
+// the preparation.
 //
 // What bounds these kernels is how much of a slice's time the matrix cores are
 // busy.  A 16-deep slice of a 128 x 128 tile holds 32 v_mfma_f64_16x16x4 (64
@@ -180,18 +181,7 @@ __device__ __forceinline__ void strip_barrier() {
 template <class L>
 struct StripAcc {
   d4 v[L::FM][L::FN];
-  int wm, wn;   // this wave's first row and column
-  // f(m, x, value) for every element this lane holds
-  template <class F>
-  __device__ __forceinline__ void for_each(F&& f) const {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int i = 0; i < L::FM; ++i)
-#pragma unroll
-      for (int j = 0; j < L::FN; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) f(wm + 16 * i + (lane >> 4) + 4 * e, wn + 16 * j + (lane & 15), v[i][j][e]);
-  }
+  int wm, wn;   // this wave's first row and column; element e of a lane: row lane / 16 + 4 e, column lane % 16
 };
 
 // nk slices; issue(kt, stage) stages slice kt (called once per slice, in order).
