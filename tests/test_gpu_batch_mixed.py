@@ -16,7 +16,7 @@ from tests.gpu_util import host, relerr, to_dev
 pytestmark = pytest.mark.gpu
 KEYS = ("b_half", "b_mo", "d", "J", "K", "Jn", "Kn", "energy", "lam", "grad")
 SMALL = [(61, 183, 5, 2, 71), (100, 300, 8, 2, 72), (37, 111, 3, 2, 73)]
-LARGE = [(160, 520, 43, 2, 74), (201, 603, 16, 2, 75), (143, 515, 14, 4, 76)]
+LARGE = [(160, 520, 43, 2, 74), (201, 603, 16, 2, 75), (143, 515, 14, 4, 76), (175, 703, 23, 4, 77)]
 
 
 def mo_tiles(nb, na, npair, ncwo, seed=0):
